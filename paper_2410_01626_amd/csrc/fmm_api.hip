@@ -13,6 +13,7 @@
 #include <vector>
 
 #include "fmm_kernels.hip"
+#include "m2l_mma.hip"
 #include "exclusions.hip"
 #include "adjoint.hip"
 #include "fmmcph.h"
@@ -55,6 +56,17 @@ struct Workspace {
     double *hc_e = nullptr, *hc_dl = nullptr;
     void* msplit = nullptr;    // bf16x3: source expansions split into hi/lo (replicas x (nbox + 1) rows)
     void* m2l_part = nullptr;  // matrix-core M2L: partial sums of the offset chunks
+    int nchunk = 0;            // offset chunks the partials are laid out for
+};
+
+// What the host needs of the compile-time sizes of the FP32 / FP64 M2L.
+struct MmaShape {
+    int npart = 0;     // row parts of an operator
+    int rtb = 0;       // row tiles of a part
+    int a_chunks = 0;  // 16-byte chunks of a part's image
+    int nf = 0;        // whole chunks of 16 k
+    int groups = 0;    // 16-column groups per work-group, at most
+    int narrow = 0;    // row tiles of a wavefront in the narrow form
 };
 
 struct fmm_plan_s {
@@ -102,6 +114,16 @@ struct fmm_plan_s {
     int16_t* olist = nullptr;
     int16_t* cstart = nullptr;
     void *bank_mma = nullptr;
+    // FP32 / FP64 M2L (m2l_mma.hip): work items of one offset chunk (FP64, when
+    // the scratch array has no room for partials), the offset lists with their
+    // operator slots, a row of zeros, the reflection signs and the largest
+    // chunk count the static scratch is checked for
+    fmmk::M2LTask* tasks1 = nullptr;
+    int n_tasks1 = 0;
+    int32_t* mlist = nullptr;
+    void *zrow = nullptr, *mma_masks = nullptr;
+    MmaShape mma;
+    int scratch_nchunk = 0;
     void* sign_tab = nullptr;  // bf16x3: reflection sign-bit masks [class][k chunk of 8]
     int m2l_nbuf = 1;        // bf16x3: LDS staging buffers (2: copy of the next offset overlaps)
     bool m2l_rs = false;     // bf16x3 with resident sources (one tile per class, parity-group chunks)
@@ -189,9 +211,10 @@ bool dev_alloc(fmm_plan_t p, void** ptr, size_t bytes) {
 // Lay out a plan's per-evaluation buffers for up to N atoms, S sites and RM
 // expansion slots (adjoint: with the adjoint's buffers) from base, each
 // buffer aligned to 256 bytes; returns the arena size.  base = NULL only
-// sizes it.  The matrix-core M2L geometry (mg, m2l_mode) must be set.
+// sizes it.  The matrix-core M2L geometry (mg, m2l_mode) must be set; nchunk:
+// the offset chunks to hold partial sums for (the plan's, or 1).
 size_t ws_layout(const fmm_plan_s* P, int64_t N, int64_t S, size_t RM, bool adjoint, char* base,
-                 Workspace* w) {
+                 Workspace* w, int nchunk) {
     N = std::max<int64_t>(N, 1);
     S = std::max<int64_t>(S, 1);
     Workspace tmp;
@@ -258,8 +281,8 @@ size_t ws_layout(const fmm_plan_s* P, int64_t N, int64_t S, size_t RM, bool adjo
     }
     if (P->m2l_mode == 3) take(w->msplit, msplit_bytes(P, RM));
     else w->msplit = nullptr;
-    if (P->m2l_mode != 0 && P->mg.nchunk > 1)
-        take(w->m2l_part, RM * P->mg.nchunk * P->mg.nt_all * Kp * ts);
+    w->nchunk = nchunk;
+    if (P->m2l_mode != 0 && nchunk > 1) take(w->m2l_part, RM * nchunk * P->mg.nt_all * Kp * ts);
     else w->m2l_part = nullptr;
     return off;
 }
@@ -355,13 +378,74 @@ float from_bf16(uint16_t h) {
 
 int round_up(int v, int m) { return (v + m - 1) / m * m; }
 
-// LDS row stride (elements) of a matrix-core operand: f32 rows are padded to
-// 2 mod 32 words (16-lane groups reading 4 consecutive k hit distinct banks),
-// f64 rows to an odd number of elements, bf16 rows to 8 mod 64 elements.
-int lds_stride(int mode, int kp) {
-    if (mode == 1) { int s = kp; while (s % 32 != 2) ++s; return s; }
-    if (mode == 2) return kp + 2;  // even: 16-byte aligned rows
-    int s = kp; while (s % 64 != 40 && s % 64 != 8) s += 8; return s;
+// fn(std::integral_constant<int, p>) for the order p of a plan.
+template <class Fn>
+void for_order(int p, Fn&& fn) {
+    switch (p) {
+#define FMM_ORDER(PV) case PV: fn(std::integral_constant<int, PV>{}); break;
+        FMM_ORDER(1) FMM_ORDER(2) FMM_ORDER(3) FMM_ORDER(4) FMM_ORDER(5) FMM_ORDER(6) FMM_ORDER(7) FMM_ORDER(8)
+        FMM_ORDER(9) FMM_ORDER(10) FMM_ORDER(11) FMM_ORDER(12) FMM_ORDER(13) FMM_ORDER(14) FMM_ORDER(15)
+#undef FMM_ORDER
+        default: break;
+    }
+}
+
+template <typename T>
+MmaShape mma_shape(int p) {
+    MmaShape m;
+    for_order(p, [&](auto pc) {
+        using D = fmmk::MmaDims<T, decltype(pc)::value>;
+        m = {D::NPART, D::RTB, D::a_chunks, D::NF, D::kGroups, D::kNarrow};
+    });
+    return m;
+}
+
+// Launch shape of one FP32 / FP64 M2L: 16-column groups per work-group and row
+// tiles per wavefront.
+struct MmaLaunch {
+    int groups, rtw;
+};
+
+// Time of one FP64 M2L launch (in clock cycles, to compare shapes): rounds of
+// 256 work-groups of c.groups column groups and `steps` offsets each.  A step
+// takes the products of the fullest SIMD (64 cycles each) or the L1 lookups
+// (one per 64 bytes of operator, two per 64 bytes of the unaligned source
+// rows), and a barrier; the start and the stores take about 6,000 cycles;
+// partials are written and read at about 1 KB per cycle.
+double mma_cost(const MmaShape& m, int KP, int64_t groups, int64_t tasks, MmaLaunch c, int steps, double part_bytes) {
+    const int64_t tiles = (groups + c.groups - 1) / c.groups, blocks = tasks * tiles;
+    const int waves = c.groups * ((m.rtb + c.rtw - 1) / c.rtw);
+    const double prod = (double)((waves + 3) / 4) * c.rtw * (KP / 4) * 64;
+    const double look = m.a_chunks * 16 / 64.0 + waves * 16.0 * KP * 8 / 32.0;
+    return (double)((blocks + 255) / 256) * ((std::max(prod, look) + 600.0) * steps + 6000.0) + 2.0 * part_bytes / 1024.0;
+}
+
+// The launch shape for R replicas.  FP32: as many column groups as a
+// work-group holds, in even tiles (its work-groups are short and share CUs; a
+// wider tile reads an operator for more columns).  FP64: the cheapest (the wide
+// form on ties).
+MmaLaunch mma_launch(const MmaShape& m, bool fp64, int KP, int64_t ncol, int64_t tasks, int64_t R, int nchunk,
+                     double part_bytes, double* cost) {
+    const int64_t groups = (R * ncol * (fp64 ? 8 : 1) + 15) / 16;
+    MmaLaunch best{1, m.rtb};
+    if (!fp64) {
+        const int64_t tiles = (groups + m.groups - 1) / m.groups;
+        best.groups = (int)((groups + tiles - 1) / tiles);
+        return best;
+    }
+    double bc = 0.0;
+    bool first = true;
+    for (int rtw : {m.rtb, m.narrow})
+        for (int c = 1; c <= m.groups && c <= groups; ++c) {
+            const double t = mma_cost(m, KP, groups, tasks, {c, rtw}, (189 + nchunk - 1) / nchunk, part_bytes);
+            if (first || t < bc) {
+                bc = t;
+                best = {c, rtw};
+            }
+            first = false;
+        }
+    if (cost) *cost = bc;
+    return best;
 }
 
 Geo make_geo(const fmm_plan_s* p) {
@@ -454,29 +538,48 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
     T* loc = (T*)P->ws.loc;
     T* part = (T*)P->ws.m2l_part;
     const T* mult = (const T*)P->ws.mult;
-    // resident sources with offset chunks: the root (periodic trees of depth >= 2,
-    // whose level-1 M2M leaves the root shares) in an extra M2L work-group and
-    // the chunk sums in the downward pass, so no reduction launch
-    // (only where a downward launch follows: it forms every leaf's expansion)
-    const bool rs_fused = P->m2l_rs && mg.nchunk > 1 && (!g.periodic || (want_root && g.depth >= 2)) &&
-                          g.depth - 1 >= (g.periodic ? 0 : g.lmin);
-    switch (P->m2l_mode * 16 + P->m2l_rt) {
-#define FMM_M2L_F32(RTV)                                                                    \
-    case 16 + RTV:                                                                          \
-        k_m2l_f32<RTV><<<nt, 64 * kM2LWaves, lds, st>>>(g, mg, P->tasks, P->olist, P->cstart, (const float*)mult, \
-                                             (const float*)P->bank_mma, (float*)loc,         \
-                                             (float*)part);                                  \
-        break;
-#define FMM_M2L_F64(RTV)                                                                      \
-    case 32 + RTV:                                                                            \
-        k_m2l_f64<RTV><<<nt, 64 * kM2LWaves, lds, st>>>(g, mg, P->tasks, P->olist, P->cstart, (const double*)mult, \
-                                             (const double*)P->bank_mma, (double*)loc,         \
-                                             (double*)part);                                   \
-        break;
+    const int nchunk = P->ws.nchunk;
+    // offset chunks in trees of depth <= 3 (bf16x3: with resident sources): the
+    // root (periodic trees of depth >= 2, whose level-1 M2M leaves the root
+    // shares) in an extra M2L work-group and the chunk sums in the downward
+    // pass, so no reduction launch (only where a downward launch follows: it
+    // forms every leaf's expansion).  FP32 / FP64: only with enough downward
+    // blocks to share the sums (30k box, FP32: 133 -> 126 us per evaluation;
+    // with 16 blocks, 2,300 atoms at depth 2, p = 10: 96.7 -> 108 us), and not
+    // in deeper trees, whose blocks would sum the same ancestors' partials many
+    // times.
+    const int64_t down_blocks = g.depth < 1 ? 0 : (int64_t)R * (g.depth <= 3 ? 2 : 1) << (3 * (g.depth - 1));
+    const bool sum_down = (P->m2l_mode == 3 ? P->m2l_rs : g.depth <= 3 && down_blocks >= 96) && nchunk > 1 &&
+                          (!g.periodic || (want_root && g.depth >= 2)) && g.depth - 1 >= (g.periodic ? 0 : g.lmin);
+    if (P->m2l_mode != 3) {
+        // one chunk where the workspace holds no partials (static scratch)
+        const bool own = nchunk == mg.nchunk;
+        const M2LTask* tasks = own ? P->tasks : P->tasks1;
+        const unsigned nx = own ? (unsigned)P->n_tasks : (unsigned)P->n_tasks1;
+        const MmaArgs ma{R, mg.ncol, P->fp64 ? 1 : 0, nchunk, mg.nt_all};
+        const int64_t groups = ((int64_t)R * mg.ncol * (P->fp64 ? 8 : 1) + 15) / 16;
+        const MmaLaunch ml = mma_launch(P->mma, P->fp64, mg.KP, mg.ncol, nx, R, nchunk, 0.0, nullptr);
+        const bool root = sum_down && want_root;
+        const RootArgs ra{P->ws.root_part, P->ws.box_part, P->latT, P->lat_seg,
+                          P->ws.root_m, root ? P->ws.root_l : nullptr, P->ws.dom};
+        const dim3 grid(nx + (root ? 1u : 0u), (unsigned)((groups + ml.groups - 1) / ml.groups));
+        const int threads = 64 * ml.groups * (P->mma.rtb / ml.rtw);
+        for_order(g.p, [&](auto pc) {
+            constexpr int PV = decltype(pc)::value;
+            // FP32 above order 10 runs the plain kernel
+            if constexpr (sizeof(T) == 8 || PV <= 10) {
+                using D = MmaDims<T, PV>;
+                auto kern = ml.rtw == D::RTB ? k_m2l_mma<T, PV, D::RTB> : k_m2l_mma<T, PV, D::kNarrow>;
+                kern<<<grid, threads, 0, st>>>(g, ma, tasks, P->mlist, (const T*)P->ws.mult, (const T*)P->zrow,
+                                               (const uint4*)P->bank_mma, (const uint64_t*)P->mma_masks, loc, part, ra);
+            }
+        });
+    } else {
+        switch (P->m2l_rt) {
 #define FMM_M2L_BF(RTV)                                                                         \
-    case 48 + RTV:                                                                              \
+    case RTV:                                                                                   \
         if (P->m2l_rs)                                                                          \
-            launch_m2l_rs<RTV>(P, g, mg, nt, (float*)loc, (float*)part, rs_fused && want_root);  \
+            launch_m2l_rs<RTV>(P, g, mg, nt, (float*)loc, (float*)part, sum_down && want_root);  \
         else                                                                                    \
             k_m2l_bf16x3<RTV><<<nt, kM2LThreads, lds, st>>>(g, mg, P->tasks, P->olist, P->cstart, \
                                                 (const uint4*)P->ws.msplit,                        \
@@ -484,26 +587,28 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
                                                 (const uint4*)P->sign_tab, (float*)loc,         \
                                                 (float*)part);                                  \
         break;
-        FMM_M2L_F32(1) FMM_M2L_F32(2) FMM_M2L_F32(3) FMM_M2L_F32(4)
-        FMM_M2L_F32(5) FMM_M2L_F32(6) FMM_M2L_F32(7) FMM_M2L_F32(8)
-        FMM_M2L_F64(1) FMM_M2L_F64(2) FMM_M2L_F64(3) FMM_M2L_F64(4)
-        FMM_M2L_F64(5) FMM_M2L_F64(6)
-        FMM_M2L_BF(1) FMM_M2L_BF(2) FMM_M2L_BF(3) FMM_M2L_BF(4)
-        FMM_M2L_BF(5) FMM_M2L_BF(6) FMM_M2L_BF(7) FMM_M2L_BF(8)
-        default: break;
+            FMM_M2L_BF(1) FMM_M2L_BF(2) FMM_M2L_BF(3) FMM_M2L_BF(4)
+            FMM_M2L_BF(5) FMM_M2L_BF(6) FMM_M2L_BF(7) FMM_M2L_BF(8)
+            default: break;
+        }
     }
-    if (rs_fused) {
+    if (sum_down) {
         *fused = true;
         return g.periodic;
     }
-    if (mg.nchunk > 1) {
+    if (nchunk > 1) {
         const int64_t tot = mg.nt_all * g.Kp;
-        const unsigned nb = (unsigned)std::min<int64_t>(4096, (tot + 255) / 256);
+        M2LGeom mg = P->mg;
+        mg.nchunk = nchunk;
+        // four threads per entry while that is at most a block or two per CU
+        const int quad = tot <= 512 * kReduceEntries;
+        const unsigned nb = quad ? (unsigned)((tot + kReduceEntries - 1) / kReduceEntries)
+                                 : (unsigned)std::min<int64_t>(4096, (tot + 255) / 256);
         // periodic trees with a downward pass: the extra block forms the root
         k_m2l_reduce<T><<<dim3(nb + (want_root ? 1u : 0u), (unsigned)R), kTreeThreads, 0, st>>>(
             g, mg, part, loc, want_root ? 1 : 0, mult, (const T*)P->m2mT, (const T*)P->m2m_seg,
             P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l, P->ws.dom,
-            g.depth >= 2 ? P->ws.root_part : nullptr);
+            g.depth >= 2 ? P->ws.root_part : nullptr, quad);
         return want_root;
     }
     return false;
@@ -598,7 +703,7 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     mark(P, 2);
     // periodic trees whose M2L ends in a reduction launch form the root there;
     // the level-1 M2M blocks then also leave their shares of the root multipole
-    const bool root_in_reduce = g.periodic && g.depth >= 1 && P->m2l_mode != 0 && P->mg.nchunk > 1;
+    const bool root_in_reduce = g.periodic && g.depth >= 1 && P->m2l_mode != 0 && P->ws.nchunk > 1;
     // folded: the leaf kernel left each leaf's term of level d - 1, and the
     // first launch (level d - 2) forms level d - 1 from them first
     const int top = folded ? g.depth - 2 : g.depth - 1;
@@ -629,7 +734,7 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     if (g.periodic && !root_ready && !fused && g.depth >= 1 && (1u << (3 * (g.depth - 1))) > 256) {
         k_m2l_reduce<T><<<dim3(1, R), kTreeThreads, 0, st>>>(
             g, P->mg, (const T*)P->ws.m2l_part, loc, 1, mult, (const T*)P->m2mT, (const T*)P->m2m_seg,
-            P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l, P->ws.dom, nullptr);
+            P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l, P->ws.dom, nullptr, 0);
         root_ready = true;
     }
     // downward pass: ancestors' local expansions and the L2L into the leaves
@@ -663,7 +768,7 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
             g, l0, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, mult, (const T*)P->m2mT,
             (const T*)P->m2m_seg, P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l,
             P->ws.dom, P->ws.leaf_start, order, root_ready ? 1 : 0, fused ? (const T*)P->ws.m2l_part : nullptr,
-            P->mg.nchunk, P->mg.nt_all, l_start);
+            P->ws.nchunk, P->mg.nt_all, l_start);
     }
     return order;
 }
@@ -954,7 +1059,6 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         P->leaf_cap = cap;
     }
     bool ok = true;
-    ok &= dev_alloc(P, &P->bankT, 343 * K * K * ts);
     ok &= dev_alloc(P, &P->m2mT, K * K * ts);  // octant 0; the others are its reflections
     ok &= dev_alloc(P, &P->l2lT, K * K * ts);
     ok &= dev_alloc(P, (void**)&P->latT, K * K * 8);
@@ -984,19 +1088,15 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         if (e == hipSuccess) e = hipMemcpy(dst, src, bytes, hipMemcpyHostToDevice);
     };
     if (P->fp64) {
-        auto b = transpose_blocks<double>(bank, 343, K);
         auto a = transpose_blocks<double>(m2m, 1, K);
         auto c = transpose_blocks<double>(l2l, 1, K);
-        up(P->bankT, b.data(), b.size() * 8);
         up(P->m2mT, a.data(), K * K * 8);
         up(P->l2lT, c.data(), K * K * 8);
         up(P->gcoef, gc.data(), gc.size() * 8);
     } else {
-        auto b = transpose_blocks<float>(bank, 343, K);
         auto a = transpose_blocks<float>(m2m, 1, K);
         auto c = transpose_blocks<float>(l2l, 1, K);
         std::vector<float> gf(gc.begin(), gc.end());
-        up(P->bankT, b.data(), b.size() * 4);
         up(P->m2mT, a.data(), K * K * 4);
         up(P->l2lT, c.data(), K * K * 4);
         up(P->gcoef, gf.data(), gf.size() * 4);
@@ -1022,17 +1122,31 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
     // matrix-core M2L: mode, tile geometry, offset lists, task list, banks
     {
         const int lmin = prm->boundary == FMM_PERIODIC ? 1 : 2;
-        const bool mma_ok = (int)K <= 16 * fmmk::kM2LMaxRT && (!P->fp64 || K <= 96);
+        // FP64 at every order; FP32 and bf16x3 up to order 10 (above it FP32
+        // truncation errors are below the rounding of the type)
+        const bool mma_ok = P->fp64 || (int)K <= 16 * fmmk::kM2LMaxRT;
         if (d >= lmin && mma_ok && prm->m2l_kernel != 1)
             P->m2l_mode = P->fp64 ? 2 : (prm->precision == FMM_MIXED_BF16X3 ? 3 : 1);
+        if (d >= lmin && P->m2l_mode == 0) {
+            // plain M2L: every offset's operator, transposed
+            if (!dev_alloc(P, &P->bankT, 343 * K * K * ts)) {
+                fmm_plan_destroy(P);
+                return FMM_E_OOM;
+            }
+            if (P->fp64) {
+                auto b = transpose_blocks<double>(bank, 343, K);
+                up(P->bankT, b.data(), b.size() * 8);
+            } else {
+                auto b = transpose_blocks<float>(bank, 343, K);
+                up(P->bankT, b.data(), b.size() * 4);
+            }
+        }
     }
     if (P->m2l_mode && e == hipSuccess) {
         fmmk::M2LGeom& mg = P->mg;
         const int lmin = prm->boundary == FMM_PERIODIC ? 1 : 2;
         mg.RP = round_up((int)K, 16);
         mg.KP = round_up((int)K, P->m2l_mode == 3 ? 32 : 4);
-        mg.SA = lds_stride(P->m2l_mode, mg.KP);
-        mg.SB = mg.SA;
         P->m2l_rt = mg.RP / 16;
         // target columns of one class: its boxes at every level >= lmin
         int64_t ncol = 0, nt_all = 0;
@@ -1057,7 +1171,21 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             return n;
         };
         int csize = prm->m2l_chunk;
-        if (csize == 0 && P->m2l_rs) {
+        if (P->m2l_mode != 3) P->mma = P->fp64 ? mma_shape<double>(p) : mma_shape<float>(p);
+        if (csize == 0 && P->m2l_mode == 2) {
+            // FP64: the cheapest number of chunks (up to order 8 at most 27, which
+            // bounds the partials)
+            double bc = 0.0;
+            for (int nc = 1; nc <= (K <= 96 ? 27 : 63); ++nc) {
+                double t = 0.0;
+                (void)mma_launch(P->mma, true, mg.KP, ncol, (int64_t)nc * P->mma.npart, (int64_t)RT, nc,
+                                 nc > 1 ? (double)nc * RT * nt_all * P->Kp * 8.0 : 0.0, &t);
+                if (csize == 0 || t < bc) {
+                    bc = t;
+                    csize = (189 + nc - 1) / nc;
+                }
+            }
+        } else if (csize == 0 && P->m2l_rs) {
             // about one work-group per CU over all replicas: the smallest chunk
             // size with at most 256 work-groups (7 for one replica: 31 chunks
             // per class, 248 work-groups), at least one chunk per group
@@ -1065,7 +1193,7 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             while (csize < 26 && 8 * (int64_t)RT * rs_chunks(csize) > 256) ++csize;
         } else if (csize == 0) {
             // bf16x3 runs one double-buffered work-group per CU: about one task per CU;
-            // the others overlap two single-buffered work-groups per CU
+            // FP32 takes up to 27 chunks per class (216 work-groups for one tile)
             const int64_t target = P->m2l_mode == 3 ? 256 : 2048, cap = P->m2l_mode == 3 ? 63 : 27;
             const int64_t want = std::max<int64_t>(1, std::min<int64_t>(cap, (target + items - 1) / items));
             csize = (int)((189 + want - 1) / want);
@@ -1110,7 +1238,7 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             cstart.assign(8 * (mg.nchunk + 1), 0);
             for (int c = 0; c < 8; ++c)
                 for (int k = 0; k <= mg.nchunk; ++k) cstart[c * (mg.nchunk + 1) + k] = (int16_t)rs_bound[k];
-        } else if (P->m2l_mode == 3) {
+        } else if (P->m2l_mode != 1) {
             // every class runs on class 0's (canonical) offsets, mirrored by
             // the class's reflection; chunks are equal slices of that list
             std::sort(cls_off.begin(), cls_off.begin() + 189);
@@ -1138,17 +1266,49 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         // i mod 8), each with its own L2.  Tasks are ordered so that slot i holds
         // a task of an offset chunk assigned to XCD i mod 8: every XCD then reads
         // only its share of the operator bank, which stays in its L2.
+        // FP32 and FP64 work items have a row part in place of a column tile, and
+        // FP64 ones no class (-1: the columns of all classes).
         const int kXcd = 8;
+        const int ncls = P->m2l_mode == 2 ? 1 : 8, nsub = P->m2l_mode == 3 ? ntile : P->mma.npart;
         std::vector<std::vector<fmmk::M2LTask>> byx(kXcd);
+        // FP32: chunks to XCDs by their total offsets, largest first (26 to 84
+        // at 27 chunks: in chunk order the fullest XCD had 236 of 1512)
+        std::vector<int> xcd_of(mg.nchunk);
+        for (int ch = 0; ch < mg.nchunk; ++ch) xcd_of[ch] = ch % kXcd;
+        if (P->m2l_mode == 1 && mg.nchunk >= kXcd) {
+            std::vector<std::pair<int, int>> w(mg.nchunk);
+            for (int ch = 0; ch < mg.nchunk; ++ch) {
+                w[ch] = {0, ch};
+                for (int c = 0; c < 8; ++c)
+                    w[ch].first -= cstart[c * (mg.nchunk + 1) + ch + 1] - cstart[c * (mg.nchunk + 1) + ch];
+            }
+            std::sort(w.begin(), w.end());
+            int load[kXcd] = {};
+            for (const auto& wc : w) {
+                const int x = (int)(std::min_element(load, load + kXcd) - load);
+                load[x] -= wc.first;
+                xcd_of[wc.second] = x;
+            }
+        }
         for (int ch = 0; ch < mg.nchunk; ++ch)
-            for (int c = 0; c < 8; ++c)
-                for (int t = 0; t < ntile; ++t) {
+            for (int c = 0; c < ncls; ++c)
+                for (int t = 0; t < nsub; ++t) {
                     int x;
-                    if (mg.nchunk >= kXcd) x = ch % kXcd;
-                    else x = ch + mg.nchunk * ((c * ntile + t) % (kXcd / mg.nchunk));
+                    if (mg.nchunk >= kXcd) x = xcd_of[ch];
+                    else x = ch + mg.nchunk * ((c * nsub + t) % (kXcd / mg.nchunk));
                     const int o0 = cstart[c * (mg.nchunk + 1) + ch], o1 = cstart[c * (mg.nchunk + 1) + ch + 1];
-                    byx[x].push_back({c, t, ch, o0, o1, {0, 0, 0}});
+                    byx[x].push_back({P->m2l_mode == 2 ? -1 : c, t, ch, o0, o1, {0, 0, 0}});
                 }
+        // FP32: a class has 0 to 11 offsets in a chunk, so an XCD's 32 CUs take
+        // its items longest first, every second round in reverse
+        if (P->m2l_mode == 1)
+            for (auto& v : byx) {
+                std::stable_sort(v.begin(), v.end(), [](const fmmk::M2LTask& a, const fmmk::M2LTask& b) {
+                    return a.o1 - a.o0 > b.o1 - b.o0;
+                });
+                for (size_t i = 32; i < v.size(); i += 64)
+                    std::reverse(v.begin() + i, v.begin() + std::min(v.size(), i + 32));
+            }
         std::vector<fmmk::M2LTask> tl;
         size_t longest = 0;
         for (auto& v : byx) longest = std::max(longest, v.size());
@@ -1156,14 +1316,26 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             for (int x = 0; x < kXcd; ++x)
                 if (j < byx[x].size()) tl.push_back(byx[x][j]);
         P->n_tasks = (int64_t)tl.size();
-        const size_t esz = P->m2l_mode == 2 ? 8 : (P->m2l_mode == 1 ? 4 : 2);
-        P->m2l_lds = esz * ((size_t)mg.RP * mg.SA + (size_t)fmmk::kM2LTile * mg.SB);
+        // what fmm_eval_noalloc counts its scratch with, so that its size limit
+        // does not follow the chunk rule above: up to order 8 the partials of
+        // the chunk count for 2048 work items per class tiling, in FP64 above
+        // it none (it then runs one chunk where the plan's do not fit)
+        P->scratch_nchunk = mg.nchunk;
+        if (P->m2l_mode == 2 && K > 96) {
+            P->scratch_nchunk = 1;
+        } else if (P->m2l_mode == 2 && prm->m2l_chunk == 0) {
+            const int64_t want = std::max<int64_t>(1, std::min<int64_t>(27, (2048 + items - 1) / items));
+            const int cs = (int)((189 + want - 1) / want);
+            P->scratch_nchunk = (189 + cs - 1) / cs;
+        }
         const int KC = mg.KP / 8;
-        if (P->m2l_mode == 3 && P->m2l_rs) {
+        if (P->m2l_mode != 3) {
+            P->m2l_lds = (size_t)2 * 16 * P->mma.a_chunks;  // two operator buffers: static LDS
+        } else if (P->m2l_rs) {
             // resident source rows and two operator buffers: static LDS
             P->m2l_nbuf = 2;
             P->m2l_lds = 0;
-        } else if (P->m2l_mode == 3) {
+        } else {
             // one staging buffer: operator (2 KC RP chunks) + sources ((2 KC + 1) 80 chunks)
             const size_t one = (size_t)16 * (2 * KC * mg.RP + (2 * KC + 1) * fmmk::kM2LTile);
             P->m2l_nbuf = 2 * one <= fmmk::kLdsBytes ? 2 : 1;
@@ -1174,9 +1346,17 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         ok2 &= dev_alloc(P, (void**)&P->tasks, tl.size() * sizeof(fmmk::M2LTask));
         ok2 &= dev_alloc(P, (void**)&P->olist, ol.size() * sizeof(int16_t));
         ok2 &= dev_alloc(P, (void**)&P->cstart, cstart.size() * sizeof(int16_t));
-        const size_t nb = (size_t)343 * mg.RP * mg.KP;
-        ok2 &= dev_alloc(P, &P->bank_mma, nb * esz * (P->m2l_mode == 3 ? 2 : 1));
-        if (P->m2l_mode == 3) ok2 &= dev_alloc(P, &P->sign_tab, 8 * 4 * fmmk::kM2LMaxKs * 16);
+        const size_t nb = (size_t)189 * mg.RP * mg.KP;
+        const size_t nb1 = (size_t)189 * P->mma.npart * P->mma.a_chunks * 16;
+        ok2 &= dev_alloc(P, &P->bank_mma, P->m2l_mode == 3 ? nb * 4 : nb1);
+        if (P->m2l_mode == 3) {
+            ok2 &= dev_alloc(P, &P->sign_tab, 8 * 4 * fmmk::kM2LMaxKs * 16);
+        } else {
+            ok2 &= dev_alloc(P, (void**)&P->tasks1, P->mma.npart * sizeof(fmmk::M2LTask));
+            ok2 &= dev_alloc(P, (void**)&P->mlist, ol.size() * 4);
+            ok2 &= dev_alloc(P, &P->zrow, fmmk::kKMax * 8);
+            ok2 &= dev_alloc(P, &P->mma_masks, 8 * 4 * 3 * 8);
+        }
         if (!ok2) {
             fmm_plan_destroy(P);
             return FMM_E_OOM;
@@ -1184,20 +1364,55 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         up(P->tasks, tl.data(), tl.size() * sizeof(fmmk::M2LTask));
         up(P->olist, ol.data(), ol.size() * sizeof(int16_t));
         up(P->cstart, cstart.data(), cstart.size() * sizeof(int16_t));
-        if (P->m2l_mode == 2) {
-            std::vector<double> bm(nb, 0.0);
-            for (int o = 0; o < 343; ++o)
-                for (size_t r = 0; r < K; ++r)
-                    for (size_t k = 0; k < K; ++k)
-                        bm[((size_t)o * mg.RP + r) * mg.KP + k] = bank[((size_t)o * K + r) * K + k];
-            up(P->bank_mma, bm.data(), nb * 8);
-        } else if (P->m2l_mode == 1) {
-            std::vector<float> bm(nb, 0.f);
-            for (int o = 0; o < 343; ++o)
-                for (size_t r = 0; r < K; ++r)
-                    for (size_t k = 0; k < K; ++k)
-                        bm[((size_t)o * mg.RP + r) * mg.KP + k] = (float)bank[((size_t)o * K + r) * K + k];
-            up(P->bank_mma, bm.data(), nb * 4);
+        if (P->m2l_mode != 3) {
+            // operator slots: class 0's offsets in ascending order; a class's
+            // offset o runs on the slot of its mirror image P o
+            std::vector<int16_t> c0(cls_off.begin(), cls_off.begin() + 189);
+            std::sort(c0.begin(), c0.end());
+            std::vector<int> slot_of(343, -1);
+            for (int i = 0; i < 189; ++i) slot_of[c0[i]] = i;
+            std::vector<int32_t> ml(ol.size());
+            for (int c = 0; c < 8; ++c)
+                for (int i = 0; i < 189; ++i) {
+                    const int o = ol[189 * c + i];
+                    int v[3] = {o / 49 - 3, (o / 7) % 7 - 3, o % 7 - 3};
+                    if (P->m2l_mode == 1)  // FP32: the class's own offset list
+                        for (int a = 0; a < 3; ++a)
+                            if ((c >> (2 - a)) & 1) v[a] = -v[a];
+                    const int co = ((v[0] + 3) * 7 + (v[1] + 3)) * 7 + (v[2] + 3);
+                    ml[189 * c + i] = (slot_of[co] << 16) | co;
+                }
+            up(P->mlist, ml.data(), ml.size() * 4);
+            std::vector<fmmk::M2LTask> t1;
+            for (int t = 0; t < P->mma.npart; ++t) t1.push_back({-1, t, 0, 0, 189, {0, 0, 0}});
+            P->n_tasks1 = (int)t1.size();
+            up(P->tasks1, t1.data(), t1.size() * sizeof(fmmk::M2LTask));
+            if (e == hipSuccess) e = hipMemset(P->zrow, 0, fmmk::kKMax * 8);
+            // the operators as LDS images, [slot][row part]
+            const int rpb = 16 * P->mma.rtb, nf = P->mma.nf;
+            std::vector<unsigned char> img(nb1, 0);
+            for (int o = 0; o < 189; ++o)
+                for (int r = 0; r < (int)K; ++r) {
+                    unsigned char* base = img.data() + ((size_t)o * P->mma.npart + r / rpb) * P->mma.a_chunks * 16;
+                    const double* src = bank.data() + ((size_t)c0[o] * K + r) * K;
+                    for (int k = 0; k < (int)K; ++k)
+                        if (P->fp64) ((double*)base)[fmmk::mma_image_index<double>(rpb, nf, r % rpb, k)] = src[k];
+                        else ((float*)base)[fmmk::mma_image_index<float>(rpb, nf, r % rpb, k)] = (float)src[k];
+                }
+            up(P->bank_mma, img.data(), img.size());
+            // reflection signs per class and lane group (see k_m2l_mma)
+            std::vector<uint64_t> mk(8 * 4 * 3, 0);
+            for (int c = 0; c < 8; ++c)
+                for (int q = 0; q < 4; ++q)
+                    for (int b = 0; b < 64; ++b) {
+                        const int row = 16 * (b / 4) + 4 * q + b % 4;
+                        const int src = P->fp64 ? 16 * (b / 4) + 8 * ((b / 2) % 2) + 2 * q + b % 2 : row;
+                        const int k[3] = {src, b < 4 ? 16 * nf + 4 * b + q : (int)K, row};
+                        for (int m = 0; m < 3; ++m)
+                            if (k[m] < (int)K && (__builtin_popcount((unsigned)(c & refl_bits_host(k[m]))) & 1))
+                                mk[(4 * c + q) * 3 + m] |= (uint64_t)1 << b;
+                    }
+            up(P->mma_masks, mk.data(), mk.size() * 8);
         } else {
             // slot j = canonical offset j: [part hi/lo][KC][RP][8], the LDS image
             // of the operator
@@ -1229,19 +1444,13 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             if (ea == hipSuccess)
                 ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P->m2l_lds);
         };
-        switch (P->m2l_mode * 16 + P->m2l_rt) {
-#define FMM_LDS_CASE(MODE, RTV, KER) \
-    case MODE * 16 + RTV: setlds((const void*)&KER<RTV>); break;
-#define FMM_LDS_ALL(MODE, KER) \
-    FMM_LDS_CASE(MODE, 1, KER) FMM_LDS_CASE(MODE, 2, KER) FMM_LDS_CASE(MODE, 3, KER) \
-    FMM_LDS_CASE(MODE, 4, KER) FMM_LDS_CASE(MODE, 5, KER) FMM_LDS_CASE(MODE, 6, KER) \
-    FMM_LDS_CASE(MODE, 7, KER) FMM_LDS_CASE(MODE, 8, KER)
-            FMM_LDS_ALL(1, fmmk::k_m2l_f32)
-            FMM_LDS_ALL(2, fmmk::k_m2l_f64)
-            FMM_LDS_ALL(3, fmmk::k_m2l_bf16x3)
+        if (P->m2l_mode == 3) switch (P->m2l_rt) {
+#define FMM_LDS_CASE(RTV) \
+    case RTV: setlds((const void*)&fmmk::k_m2l_bf16x3<RTV>); break;
+            FMM_LDS_CASE(1) FMM_LDS_CASE(2) FMM_LDS_CASE(3) FMM_LDS_CASE(4)
+            FMM_LDS_CASE(5) FMM_LDS_CASE(6) FMM_LDS_CASE(7) FMM_LDS_CASE(8)
             default: break;
         }
-
         if (ea != hipSuccess) e = ea;
     }
     for (int fold = 0; fold < 2 && e == hipSuccess; ++fold) {
@@ -1266,12 +1475,12 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
     // re-zeroes the ones it used; the bf16 split rows' zero row and padding
     // past K are never written)
     if (e == hipSuccess) {
-        const size_t bytes = ws_layout(P, N, S, RM, true, nullptr, nullptr);
+        const size_t bytes = ws_layout(P, N, S, RM, true, nullptr, nullptr, P->mg.nchunk);
         if (!dev_alloc(P, &P->ws_arena, bytes)) {
             fmm_plan_destroy(P);
             return FMM_E_OOM;
         }
-        ws_layout(P, N, S, RM, true, (char*)P->ws_arena, &P->ws);
+        ws_layout(P, N, S, RM, true, (char*)P->ws_arena, &P->ws, P->mg.nchunk);
         e = hipMemset(P->ws_arena, 0, bytes);
     }
     if (prm->hamiltonian) {
@@ -1397,7 +1606,7 @@ fmm_status fmm_eval_noalloc(fmm_plan_t P, int64_t n, const void* x, const void* 
     if ((s = check_box(P, box, &L)) != FMM_OK) return s;
     void* base = scratch_address(P->device);
     if (!base) return fail(P, FMM_E_HIP, "no static scratch address for this device");
-    const size_t need = ws_layout(P, n, S, 1, false, nullptr, nullptr);
+    const size_t need = ws_layout(P, n, S, 1, false, nullptr, nullptr, P->scratch_nchunk);
     if (need > kScratchBytes) {
         char msg[160];
         std::snprintf(msg, sizeof msg, "fmm_eval_noalloc: %zu bytes of scratch needed, the static "
@@ -1406,7 +1615,9 @@ fmm_status fmm_eval_noalloc(fmm_plan_t P, int64_t n, const void* x, const void* 
     }
     P->err.clear();
     Workspace sw;
-    ws_layout(P, n, S, 1, false, (char*)base, &sw);
+    // the plan's offset chunks where their partials fit, else one
+    const bool fits = ws_layout(P, n, S, 1, false, nullptr, nullptr, P->mg.nchunk) <= kScratchBytes;
+    ws_layout(P, n, S, 1, false, (char*)base, &sw, fits ? P->mg.nchunk : 1);
     const fmmk::RepDesc rd{0, n, 0, S, L, 0};
     // what must start at zero: the leaf and site counters, the cube record
     // and the bf16 split rows (the zero row and the padding past K); fill
