@@ -105,6 +105,7 @@ struct fmm_plan_s {
     // matrix-core M2L
     int p2p_waves = 8;  // wavefronts per near-field block (4, 8 or 16)
     int p2p_split = 1;  // near-field blocks per leaf (1 to 4)
+    int p2p_blocks = 1;  // blocks that share a leaf's rounds (trees of few, full leaves; 1 to 4)
     int m2l_mode = 0;  // 0 plain, 1 f32, 2 f64, 3 bf16x3
     fmmk::M2LGeom mg{};
     int m2l_rt = 0;
@@ -809,19 +810,13 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
     const V4* pos = (const V4*)P->ws.pos;
     const T* loc = (const T*)P->ws.loc;
     mark(P, 6);
-    switch (P->p2p_waves) {
-#define FMM_NEAR(NWV)                                                                            \
-    case NWV:                                                                                    \
-        k_near_far<T, NWV><<<dim3(g.nleaf * P->p2p_split, R), 64 * NWV, 0, st>>>(               \
-            g, P->p2p_split, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx,              \
-            (const T*)P->gcoef, qA, qB, site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr,   \
-            order, P->status);                                                                     \
-        break;
-        FMM_NEAR(4)
-        FMM_NEAR(8)
-        FMM_NEAR(16)
-        default: break;
-    }
+    auto near = P->p2p_blocks > 1    ? k_near_far<T, 8, true>
+                : P->p2p_waves == 4  ? k_near_far<T, 4, false>
+                : P->p2p_waves == 16 ? k_near_far<T, 16, false>
+                                     : k_near_far<T, 8, false>;
+    near<<<dim3(g.nleaf * P->p2p_split * P->p2p_blocks, R), 64 * P->p2p_waves, 0, st>>>(
+        g, P->p2p_split, P->p2p_blocks, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx,
+        (const T*)P->gcoef, qA, qB, site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status);
     if (P->excl_n > 0)
         k_excl<T><<<dim3(ab, R), 256, 0, st>>>(g, reps, x, qA, qB, site, lam, fa, P->ws.dom, P->excl_start,
                                                P->excl_idx, phi, F, P->ws.cphi, fa.qC != nullptr,
@@ -832,7 +827,7 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
         k_hcorr<T><<<(unsigned)S_tot, kHcorrThreads, 0, st>>>(g, R, reps, P->ws.site_start, P->ws.site_members, x, qA,
                                                     qB, lam, P->green, F, P->ws.hc_e, P->ws.hc_dl,
                                                     P->status);
-    k_reduce<T><<<(unsigned)(R + S_tot), 256, 0, st>>>(g, R, g.nleaf * P->p2p_split, P->ws.leaf_energy,
+    k_reduce<T><<<(unsigned)(R + S_tot), 256, 0, st>>>(g, R, g.nleaf * P->p2p_split * P->p2p_blocks, P->ws.leaf_energy,
                                                        P->ws.site_start, P->ws.site_members, P->ws.cphi, E,
                                                        dVdl, P->status, qA, qB, lam, fa, dVdl_t, reps,
                                                        ham && S_tot > 0 ? P->ws.hc_e : nullptr,
@@ -1029,6 +1024,16 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         P->p2p_waves = per_leaf <= 32.0 ? 4 : 8;
     }
     P->p2p_split = prm->p2p_split ? prm->p2p_split : 1;
+    // Few, full leaves (up to 128 over all replicas, more than 256 atoms each on
+    // average): two blocks per round of 512 targets, at most four, so that the
+    // wavefronts of a leaf do not pile up on one CU.  From the plan's maxima
+    // alone, so every call of a plan sums in one order.  (With 384 leaves of 86
+    // atoms the half-empty blocks cost more than they spread: 130 -> 202 us.)
+    if (P->p2p_waves == 8 && P->p2p_split == 1) {
+        const double leaves = (double)std::max(prm->max_replicas, 1) * std::ldexp(1.0, 3 * prm->depth);
+        const double per_leaf = (double)prm->max_atoms / leaves;
+        if (leaves <= 128 && per_leaf > 256.0) P->p2p_blocks = per_leaf <= 512.0 ? 2 : 4;
+    }
     P->tsz = P->fp64 ? 8 : 4;
     const int p = prm->order_p, d = prm->depth;
     P->K = (p + 1) * (p + 1);

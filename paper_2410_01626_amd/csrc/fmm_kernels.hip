@@ -2140,6 +2140,8 @@ template <typename T> __device__ __forceinline__ T inv_sqrt(T v);
 // far from the denormal range, so no range scaling is needed
 template <> __device__ __forceinline__ float inv_sqrt<float>(float v) { return __builtin_amdgcn_rsqf(v); }
 template <> __device__ __forceinline__ double inv_sqrt<double>(double v) { return rsqrt(v); }
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 
 // Per target leaf (kNW wavefronts, one lane per target): the sources of the 27
@@ -2149,9 +2151,19 @@ template <> __device__ __forceinline__ double inv_sqrt<double>(double v) { retur
 // between the wavefronts by order m.  Wavefront 0 adds the per-wave partials in
 // a fixed order, applies the periodic background term and writes potential,
 // force, the per-leaf energy partial and (qB - qA) phi for the site sums.
-template <typename T, int kNW>
+//
+// kBig: nblk blocks share a leaf (trees of few, full leaves, which would leave
+// most CUs idle).  The work is cut along the split of wavefronts between target
+// chunks that one block would use, so every sum keeps its order: unit 2 r + h is
+// the first or second half of round r's wavefronts (whole chunks), and block b
+// takes units b, b + nblk, ...  The wavefronts past its half only help staging;
+// the others then have a SIMD each, so the pair loop reads its next four
+// sources ahead.  51,200 atoms at depth 2 (64 leaves of 800): 2,103 -> 792 us
+// (the longest wavefront sums 64 targets over 24,000 sources: 68 issue cycles
+// per source, 680 us at 2.4 GHz).
+template <typename T, int kNW, bool kBig>
 __global__ __launch_bounds__(64 * kNW) void k_near_far(
-    Geo g, int nsplit, const RepDesc* __restrict__ reps, const vec4_t<T>* __restrict__ pos,
+    Geo g, int nsplit, int nblk, const RepDesc* __restrict__ reps, const vec4_t<T>* __restrict__ pos,
     const int32_t* __restrict__ leaf_start_all, const int32_t* __restrict__ perm,
     const double* __restrict__ dom_all, const T* __restrict__ loc_all,
     const int32_t* __restrict__ gidx, const T* __restrict__ gcoef,
@@ -2166,8 +2178,8 @@ __global__ __launch_bounds__(64 * kNW) void k_near_far(
     const int32_t* leaf_start = leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1);
     const double* dom = dom_all + 8 * blockIdx.y;
     const T* loc = loc_all + (size_t)blockIdx.y * g.nbox * g.Kp;
-    double* leaf_energy = leaf_energy_all + (size_t)blockIdx.y * g.nleaf * nsplit;
-    __shared__ vec4_t<T> tile[CAP];
+    double* leaf_energy = leaf_energy_all + (size_t)blockIdx.y * gridDim.x;
+    __shared__ vec4_t<T> tile[CAP + (kBig ? 16 : 0)];
     __shared__ int nb_start[28], nb_cnt[28], nb_pre[29];
     __shared__ T nb_off[27][3];
     __shared__ T lam[kKMax];
@@ -2181,13 +2193,15 @@ __global__ __launch_bounds__(64 * kNW) void k_near_far(
     // block `sub` of the leaf takes targets 32 sub .. 32 sub + 31 (the last
     // block of the leaf all the rest); one block per leaf takes them all
     // leaves in the order given by leaf_work_order (largest first), if any
-    const int lslot = blockIdx.x / nsplit, sub = blockIdx.x - lslot * nsplit;
+    // (kBig: slot-major over the nblk blocks of every leaf)
+    const int lslot = kBig ? blockIdx.x % g.nleaf : blockIdx.x / nsplit;
+    const int sub = kBig ? 0 : blockIdx.x - lslot * nsplit, unit0 = kBig ? blockIdx.x / g.nleaf : 0;
     const int leaf = leaf_order_all ? leaf_order_all[(size_t)blockIdx.y * g.nleaf + lslot] : lslot;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int lb = leaf_start[leaf], ln = leaf_start[leaf + 1] - lb;
     const int ta = 32 * sub;
-    const int tb = lb + ta, tn = sub + 1 == nsplit ? ln - ta : min(32, ln - ta);
-    if (tn <= 0) {
+    const int tb = lb + ta, tn = kBig || sub + 1 == nsplit ? ln - ta : min(32, ln - ta);
+    if (tn <= 0 || (kBig && 64 * kNW * (unit0 >> 1) >= tn)) {
         if (tid == 0) leaf_energy[blockIdx.x] = 0.0;
         return;
     }
@@ -2279,7 +2293,10 @@ __global__ __launch_bounds__(64 * kNW) void k_near_far(
     // work (sources x gsz); each wavefront of a chunk takes a contiguous slice
     // of every source tile.
     __shared__ int w_first[kNW + 1];
-    for (int t0 = 0; t0 < tn; t0 += 64 * kNW) {
+    bool again = false;  // the tile holds an earlier pass
+    for (int unit = unit0;; unit += kBig ? nblk : 1) {
+        const int t0 = 64 * kNW * (kBig ? unit >> 1 : unit);
+        if (t0 >= tn) break;
         const int nch = min(kNW, (tn - t0 + 63) / 64);
         // every thread derives the same split (no barrier): w[c] wavefronts
         // for chunk c, each extra one to the largest gs / w (ties: lower c);
@@ -2308,34 +2325,56 @@ __global__ __launch_bounds__(64 * kNW) void k_near_far(
         wf[0] = 0;
 #pragma unroll
         for (int c = 0; c < kNW; ++c) wf[c + 1] = wf[c] + w[c];
+        // kBig: chunks [cb, ce) and their wavefronts [vb, ve) of this half
+        int cb = 0, ce = nch, vb = 0, ve = kNW;
+        if constexpr (kBig) {
+            int mid = 0, vm = 0;
+#pragma unroll
+            for (int c = 1; c < kNW; ++c)
+                if (c < nch && wf[c] <= kNW / 2) {
+                    mid = c;
+                    vm = wf[c];
+                }
+            if (unit & 1) {
+                cb = mid;
+                vb = vm;
+            } else {
+                ce = mid;
+                ve = vm;
+            }
+            if (cb >= ce) continue;
+        }
+        const int vw = wave + vb;  // this wavefront's place in the round's split
+        const bool busy = vw < ve;
         int chunk = 0, wc0 = 0, wc1 = wf[1];
 #pragma unroll
         for (int c = 1; c < kNW; ++c)
-            if (c < nch && wf[c] <= wave) {
+            if (c < nch && wf[c] <= vw) {
                 chunk = c;
                 wc0 = wf[c];
                 wc1 = wf[c + 1];
             }
-        const int wpc = wc1 - wc0, slice = wave - wc0;
+        const int wpc = wc1 - wc0, slice = busy ? vw - wc0 : -1;
         // kept for the energy sum at the end of the round (read after barriers)
         if (tid <= kNW) {
 #pragma unroll
             for (int c = 0; c <= kNW; ++c)
-                if (c == tid) w_first[c] = wf[c];
+                if (c == tid) w_first[c] = wf[c] - vb;
         }
         const int tc = min(64, tn - t0 - 64 * chunk);
         int gsz = 1;
         while (gsz < tc) gsz <<= 1;
         const int ngrp = 64 / gsz, grp = lane / gsz, tl = lane & (gsz - 1);
         const int tj = t0 + 64 * chunk + tl;
-        const bool tv = tl < tc;
+        const bool tv = busy && tl < tc;
         vec4_t<T> me;
         if (tv) me = pos[tb + tj];
         else { me.x = me.y = me.z = me.w = T(0); }
         T ph = T(0), fx = T(0), fy = T(0), fz = T(0);
         for (int s0 = 0; s0 < total; s0 += CAP) {
             const int cnt = min(CAP, total - s0);
-            if (t0 > 0 || s0 > 0) __syncthreads();  // the tile's previous readers are done
+            if (again) __syncthreads();  // the tile's previous readers are done
+            again = true;
             if (total <= CAP) {
                 // the whole neighbourhood in one pass: wavefront w copies
                 // neighbours w, w + kNW, ..., lane j their atom j (all loads
@@ -2408,22 +2447,55 @@ __global__ __launch_bounds__(64 * kNW) void k_near_far(
             const int own_b = nb_pre[13] - s0, own_e = nb_pre[14] - s0;
             auto sweep = [&](int j0, int j1, auto guard) {
                 const int first = j0 + ((grp - (j0 - jb)) & (ngrp - 1));
-#pragma unroll 4
-                for (int j = first; j < j1; j += ngrp) {
-                    const vec4_t<T> s = tile[j];
+                // (multiply-adds spelled out: every form of the loop rounds alike)
+                auto pair = [&](const vec4_t<T>& s) {
                     const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
-                    const T r2 = dx * dx + dy * dy + dz * dz;
+                    const T r2 = fma_(dz, dz, fma_(dx, dx, dy * dy));
                     T ri;
                     if constexpr (decltype(guard)::value) ri = r2 > T(0) ? inv_sqrt<T>(r2) : T(0);
                     else ri = inv_sqrt<T>(r2);
-                    const T qr = s.w * ri;
-                    const T qr3 = qr * (ri * ri);
-                    ph += qr;
-                    fx += qr3 * dx;
-                    fy += qr3 * dy;
-                    fz += qr3 * dz;
+                    const T qr3 = (s.w * ri) * (ri * ri);
+                    ph = fma_(s.w, ri, ph);
+                    fx = fma_(qr3, dx, fx);
+                    fy = fma_(qr3, dy, fy);
+                    fz = fma_(qr3, dz, fz);
+                };
+                int j = first;
+                if constexpr (kBig) {
+                    // full chunks (one lane group: the range is the same for
+                    // every lane): four sources at a time, the next four read
+                    // while they are summed (reads run at most 8 entries past
+                    // the range, into the tile's padding; never used)
+                    const int js = __builtin_amdgcn_readfirstlane(j), je_ = __builtin_amdgcn_readfirstlane(j1);
+                    if (__builtin_amdgcn_readfirstlane(ngrp) == 1 && js < je_) {
+                        vec4_t<T> s0[4], s1[4];
+                        int i = js;
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) s0[k] = tile[i + k];
+                        for (; i + 7 < je_; i += 8) {
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) s1[k] = tile[i + 4 + k];
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) pair(s0[k]);
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) s0[k] = tile[i + 8 + k];
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int k = 0; k < 4; ++k) pair(s1[k]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        for (; i < je_; ++i) pair(tile[i]);
+                        return;
+                    }
+                    for (; j < j1; j += ngrp) pair(tile[j]);
+                } else {
+#pragma unroll 4
+                    for (; j < j1; j += ngrp) pair(tile[j]);
                 }
             };
+            if (kBig && !busy) continue;  // (uniform per wavefront; the barriers are above)
             sweep(jb, min(je, own_b), std::false_type{});
             sweep(max(jb, own_b), min(je, own_e), std::true_type{});
             sweep(max(jb, own_e), je, std::false_type{});
@@ -2539,7 +2611,7 @@ __global__ __launch_bounds__(64 * kNW) void k_near_far(
         // energy partial of this round, in target order
         if (wave == 0) {
             double v = 0.0;
-            for (int c = 0; c < nch; ++c) v += esum_part[w_first[c]][lane];
+            for (int c = cb; c < ce; ++c) v += esum_part[w_first[c]][lane];
             esum += v;
         }
     }
