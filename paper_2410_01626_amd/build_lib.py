@@ -11,7 +11,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libfmmcph.so")
 SOURCES = [os.path.join(CSRC, "fmm_api.hip"), os.path.join(CSRC, "lambda_dynamics.hip"),
            os.path.join(CSRC, "operators.cpp")]
-HEADERS = [os.path.join(CSRC, f) for f in ("fmm_kernels.hip", "m2l_mma.hip", "adjoint.hip", "exclusions.hip", "fmm_internal.h",
+HEADERS = [os.path.join(CSRC, f) for f in ("fmm_kernels.hip", "m2l_mma.hip", "m2l_bf16x3.hip", "adjoint.hip", "exclusions.hip", "fmm_internal.h",
                                            "operators.h")] + [
     os.path.join(ROOT, "include", "fmmcph.h")]
 

@@ -181,7 +181,7 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_src2(
         mult_all[((size_t)g.nbox + gb) * g.Kp + tid] = acc;
         if constexpr (sizeof(T) == 4)
             if (msplit_all)
-                store_split(msplit_all + ((size_t)g.nbox + 1) * 2 * split_kp, split_kp, gb, tid, acc);
+                store_split(split_of(msplit_all, g.nbox, split_kp, 1), split_kp, g.depth, leaf, tid, acc);
     }
     if (g.periodic && tid == 0) {
         double a2 = 0.0, aq = 0.0;

@@ -14,6 +14,7 @@
 
 #include "fmm_kernels.hip"
 #include "m2l_mma.hip"
+#include "m2l_bf16x3.hip"
 #include "exclusions.hip"
 #include "adjoint.hip"
 #include "fmmcph.h"
@@ -122,11 +123,13 @@ struct fmm_plan_s {
     fmmk::M2LTask* tasks1 = nullptr;
     int n_tasks1 = 0;
     int32_t* mlist = nullptr;
-    void *zrow = nullptr, *mma_masks = nullptr;
+    void *zrow = nullptr;  // zeros read for absent sources
+    void* mma_masks = nullptr;
     MmaShape mma;
     int scratch_nchunk = 0;
     void* sign_tab = nullptr;  // bf16x3: reflection sign-bit masks [class][k chunk of 8]
-    int m2l_nbuf = 1;        // bf16x3: LDS staging buffers (2: copy of the next offset overlaps)
+    int split_kp = 0;        // bf16x3: KP of the split source rows, negative when interleaved
+    int m2l_cg = 0;          // bf16x3 without resident sources: column groups per wavefront
     bool m2l_rs = false;     // bf16x3 with resident sources (one tile per class, parity-group chunks)
     std::vector<void*> allocs;
     size_t ws_bytes = 0;
@@ -152,6 +155,9 @@ static __device__ __align__(256) unsigned char scratch[kScratchBytes];
 namespace {
 
 constexpr int kBboxBlocks = 256;
+// zeros that absent M2L sources read: an expansion row (FP32 / FP64) or eight
+// interleaved split rows of 2 KP bf16 (KP <= 128)
+constexpr size_t kZrowBytes = 8 * 2 * 128 * 2;
 
 // Device address of each GPU's copy of `scratch`, looked up once per device
 // with that device current (plan creation); host code uses only these
@@ -523,6 +529,16 @@ void launch_m2l_rs(fmm_plan_t P, const Geo& g, const fmmk::M2LGeom& mg, dim3 nt,
     }
 }
 
+template <int RTV>
+void launch_m2l_bf(fmm_plan_t P, const Geo& g, const fmmk::M2LGeom& mg, dim3 nt, float* loc, float* part) {
+    auto kern = P->m2l_cg == 5 ? fmmk::k_m2l_bf16x3<RTV, 5>
+                : P->m2l_cg == 4 ? fmmk::k_m2l_bf16x3<RTV, 4>
+                                 : fmmk::k_m2l_bf16x3<RTV, 2>;
+    kern<<<nt, fmmk::kBfThreads, 0, P->stream>>>(g, mg, P->tasks, P->olist, (const uint4*)P->ws.msplit,
+                                                 (const uint4*)P->bank_mma, (const uint4*)P->sign_tab,
+                                                 (const uint4*)P->zrow, loc, part);
+}
+
 // Matrix-core M2L launch: the kernel instance for the plan's precision and row
 // tile count, then the fixed-order chunk reduction.  Returns whether the
 // periodic root was formed (by the reduction launch or, with resident sources,
@@ -535,7 +551,6 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
     hipStream_t st = P->stream;
     const M2LGeom mg = P->mg;
     const dim3 nt((unsigned)P->n_tasks, (unsigned)R);
-    const size_t lds = P->m2l_lds;
     T* loc = (T*)P->ws.loc;
     T* part = (T*)P->ws.m2l_part;
     const T* mult = (const T*)P->ws.mult;
@@ -582,11 +597,7 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
         if (P->m2l_rs)                                                                          \
             launch_m2l_rs<RTV>(P, g, mg, nt, (float*)loc, (float*)part, sum_down && want_root);  \
         else                                                                                    \
-            k_m2l_bf16x3<RTV><<<nt, kM2LThreads, lds, st>>>(g, mg, P->tasks, P->olist, P->cstart, \
-                                                (const uint4*)P->ws.msplit,                        \
-                                                (const uint4*)P->bank_mma, P->m2l_nbuf,         \
-                                                (const uint4*)P->sign_tab, (float*)loc,         \
-                                                (float*)part);                                  \
+            launch_m2l_bf<RTV>(P, g, mg, nt, (float*)loc, (float*)part);                        \
         break;
             FMM_M2L_BF(1) FMM_M2L_BF(2) FMM_M2L_BF(3) FMM_M2L_BF(4)
             FMM_M2L_BF(5) FMM_M2L_BF(6) FMM_M2L_BF(7) FMM_M2L_BF(8)
@@ -683,7 +694,7 @@ void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
     auto leaf = fold ? k_leaf_p2m<T, true> : k_leaf_p2m<T, false>;
     leaf<<<dim3(g.nleaf, R), kLeafThreads, lds, st>>>(
         g, reps, x, qA, qB, site, lam, fa, P->ws.dom, P->ws.leaf_start, P->ws.perm, (V4*)P->ws.pos, P->status,
-        (T*)P->ws.mult, P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->mg.KP, bins, lb, (const T*)P->m2mT,
+        (T*)P->ws.mult, P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp, bins, lb, (const T*)P->m2mT,
         (const T*)P->m2m_seg, fold ? P->ws.m2m_part : nullptr);
 }
 
@@ -711,7 +722,7 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     for (int lev = top; lev >= g.lmin; --lev)
         k_m2m<T><<<dim3(1u << (3 * lev), R), kTreeThreads, 0, st>>>(
             g, lev, mult, (const T*)P->m2mT, (const T*)P->m2m_seg, P->ws.leaf_part, P->ws.box_part,
-            (uint16_t*)P->ws.msplit, P->mg.KP, root_in_reduce && lev == 1 ? P->ws.root_part : nullptr,
+            (uint16_t*)P->ws.msplit, P->split_kp, root_in_reduce && lev == 1 ? P->ws.root_part : nullptr,
             folded && lev == top ? P->ws.m2m_part : nullptr);
     mark(P, 3);
     if (g.periodic && g.depth == 0)
@@ -883,7 +894,7 @@ fmm_status enqueue_adjoint_full(fmm_plan_t P, const fmmk::RepDesc& r0, const T* 
     using V4 = vec4_t<T>;
     k_leaf_src2<T><<<g.nleaf, kLeafThreads, src2_lds_bytes<T>(g.K), st>>>(
         g, (const V4*)P->ws.pos, P->ws.perm, P->ws.leaf_start, gphi, gF, P->ws.dom, (V4*)P->ws.adj_src2, (T*)P->ws.mult,
-        P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->mg.KP);
+        P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp);
     enqueue_tree<T>(P, g, 2, false, false);
     mark(P, 6);
     k_near_adj<T, kAdjWaves><<<g.nleaf, 64 * kAdjWaves, 0, st>>>(g, (const V4*)P->ws.pos, (const V4*)P->ws.adj_src2,
@@ -1167,6 +1178,7 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         // canonical offsets' parity groups
         P->m2l_rs = P->m2l_mode == 3 && ntile == 1 && prm->m2l_kernel != 3 && P->m2l_rt <= fmmk::kM2LRsMaxRT &&
                     mg.KP / 8 == fmmk::m2l_rs_kc(P->m2l_rt);
+        P->split_kp = P->m2l_rs ? mg.KP : -mg.KP;
         // chunks of the parity groups (sizes of class 0's list: 26, 3 x 25,
         // 3 x 23, 19) for a chunk size
         auto rs_chunks = [](int cs) {
@@ -1274,7 +1286,27 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         // FP32 and FP64 work items have a row part in place of a column tile, and
         // FP64 ones no class (-1: the columns of all classes).
         const int kXcd = 8;
-        const int ncls = P->m2l_mode == 2 ? 1 : 8, nsub = P->m2l_mode == 3 ? ntile : P->mma.npart;
+        // bf16x3 without resident sources: the column groups per wavefront (2, 4
+        // or 5) with the least time in rounds of 256 work-groups, an offset
+        // taking the products (48 cycles per tile and k-step) or the L1 lookups
+        // (one per 64 bytes: the operator, every wavefront's rows)
+        int btile = ntile;
+        if (P->m2l_mode == 3 && !P->m2l_rs) {
+            double bc = 0.0;
+            for (int cg : {5, 4, 2}) {
+                const int tiles = (int)((ncol + fmmk::m2l_bf_cols(P->m2l_rt, cg) - 1) / fmmk::m2l_bf_cols(P->m2l_rt, cg));
+                const int rtw = P->m2l_rt > 1 ? (P->m2l_rt + 1) / 2 : 1, nks = mg.KP / 32;
+                const double prod = 48.0 * rtw * cg * nks, look = mg.RP * mg.KP / 16.0 + 4 * 2 * nks * cg * 16.0;
+                const int64_t blocks = 8 * (int64_t)tiles * mg.nchunk * (int64_t)RT;
+                const double t = (double)((blocks + 255) / 256) * (std::max(prod, look) + 400.0);
+                if (P->m2l_cg == 0 || t < bc) {
+                    bc = t;
+                    P->m2l_cg = cg;
+                    btile = tiles;
+                }
+            }
+        }
+        const int ncls = P->m2l_mode == 2 ? 1 : 8, nsub = P->m2l_mode == 3 ? btile : P->mma.npart;
         std::vector<std::vector<fmmk::M2LTask>> byx(kXcd);
         // FP32: chunks to XCDs by their total offsets, largest first (26 to 84
         // at 27 chunks: in chunk order the fullest XCD had 236 of 1512)
@@ -1300,6 +1332,7 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
                 for (int t = 0; t < nsub; ++t) {
                     int x;
                     if (mg.nchunk >= kXcd) x = xcd_of[ch];
+                    else if (P->m2l_mode == 3) x = c;  // a class's operators and rows in one L2
                     else x = ch + mg.nchunk * ((c * nsub + t) % (kXcd / mg.nchunk));
                     const int o0 = cstart[c * (mg.nchunk + 1) + ch], o1 = cstart[c * (mg.nchunk + 1) + ch + 1];
                     byx[x].push_back({P->m2l_mode == 2 ? -1 : c, t, ch, o0, o1, {0, 0, 0}});
@@ -1336,15 +1369,8 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         const int KC = mg.KP / 8;
         if (P->m2l_mode != 3) {
             P->m2l_lds = (size_t)2 * 16 * P->mma.a_chunks;  // two operator buffers: static LDS
-        } else if (P->m2l_rs) {
-            // resident source rows and two operator buffers: static LDS
-            P->m2l_nbuf = 2;
-            P->m2l_lds = 0;
         } else {
-            // one staging buffer: operator (2 KC RP chunks) + sources ((2 KC + 1) 80 chunks)
-            const size_t one = (size_t)16 * (2 * KC * mg.RP + (2 * KC + 1) * fmmk::kM2LTile);
-            P->m2l_nbuf = 2 * one <= fmmk::kLdsBytes ? 2 : 1;
-            P->m2l_lds = P->m2l_nbuf * one;
+            P->m2l_lds = 0;  // static
         }
         const std::vector<int16_t>& ol = cls_off;
         bool ok2 = !ol.empty();
@@ -1353,13 +1379,14 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         ok2 &= dev_alloc(P, (void**)&P->cstart, cstart.size() * sizeof(int16_t));
         const size_t nb = (size_t)189 * mg.RP * mg.KP;
         const size_t nb1 = (size_t)189 * P->mma.npart * P->mma.a_chunks * 16;
-        ok2 &= dev_alloc(P, &P->bank_mma, P->m2l_mode == 3 ? nb * 4 : nb1);
+        ok2 &= dev_alloc(P, &P->bank_mma, P->m2l_mode == 3 ? nb * 4 * (P->m2l_rs ? 1 : 8) : nb1);
         if (P->m2l_mode == 3) {
             ok2 &= dev_alloc(P, &P->sign_tab, 8 * 4 * fmmk::kM2LMaxKs * 16);
+            ok2 &= dev_alloc(P, &P->zrow, kZrowBytes);
         } else {
             ok2 &= dev_alloc(P, (void**)&P->tasks1, P->mma.npart * sizeof(fmmk::M2LTask));
             ok2 &= dev_alloc(P, (void**)&P->mlist, ol.size() * 4);
-            ok2 &= dev_alloc(P, &P->zrow, fmmk::kKMax * 8);
+            ok2 &= dev_alloc(P, &P->zrow, kZrowBytes);
             ok2 &= dev_alloc(P, &P->mma_masks, 8 * 4 * 3 * 8);
         }
         if (!ok2) {
@@ -1367,6 +1394,7 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             return FMM_E_OOM;
         }
         up(P->tasks, tl.data(), tl.size() * sizeof(fmmk::M2LTask));
+        if (e == hipSuccess) e = hipMemset(P->zrow, 0, kZrowBytes);
         up(P->olist, ol.data(), ol.size() * sizeof(int16_t));
         up(P->cstart, cstart.data(), cstart.size() * sizeof(int16_t));
         if (P->m2l_mode != 3) {
@@ -1392,7 +1420,6 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             for (int t = 0; t < P->mma.npart; ++t) t1.push_back({-1, t, 0, 0, 189, {0, 0, 0}});
             P->n_tasks1 = (int)t1.size();
             up(P->tasks1, t1.data(), t1.size() * sizeof(fmmk::M2LTask));
-            if (e == hipSuccess) e = hipMemset(P->zrow, 0, fmmk::kKMax * 8);
             // the operators as LDS images, [slot][row part]
             const int rpb = 16 * P->mma.rtb, nf = P->mma.nf;
             std::vector<unsigned char> img(nb1, 0);
@@ -1443,20 +1470,15 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
                         sg[((size_t)c * 4 * fmmk::kM2LMaxKs + k / 8) * 4 + (k % 8) / 2] |=
                             (k & 1) ? 0x80000000u : 0x8000u;
             up(P->sign_tab, sg.data(), sg.size() * 4);
+            if (!P->m2l_rs && e == hipSuccess) {
+                // the other classes' copies, signed on the device
+                const int64_t copy = 189 * (int64_t)2 * KC * mg.RP;
+                fmmk::k_sign_bank<<<dim3((unsigned)((copy + 255) / 256), 7), 256>>>((uint4*)P->bank_mma, (const uint4*)P->sign_tab,
+                                                                                  copy, KC, mg.RP);
+                e = hipGetLastError();
+                if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
+            }
         }
-        hipError_t ea = hipSuccess;
-        auto setlds = [&](const void* fn) {
-            if (ea == hipSuccess)
-                ea = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, (int)P->m2l_lds);
-        };
-        if (P->m2l_mode == 3) switch (P->m2l_rt) {
-#define FMM_LDS_CASE(RTV) \
-    case RTV: setlds((const void*)&fmmk::k_m2l_bf16x3<RTV>); break;
-            FMM_LDS_CASE(1) FMM_LDS_CASE(2) FMM_LDS_CASE(3) FMM_LDS_CASE(4)
-            FMM_LDS_CASE(5) FMM_LDS_CASE(6) FMM_LDS_CASE(7) FMM_LDS_CASE(8)
-            default: break;
-        }
-        if (ea != hipSuccess) e = ea;
     }
     for (int fold = 0; fold < 2 && e == hipSuccess; ++fold) {
         const void* f = P->fp64 ? (fold ? (const void*)&fmmk::k_leaf_p2m<double, true>

@@ -207,15 +207,44 @@ __device__ __forceinline__ T wave_sum(T v) {
 
 __device__ __forceinline__ bool finite_d(double v) { return isfinite(v); }
 
-// Split FP32 expansion coefficients into bf16 hi + lo parts (the source
-// layout of the bf16x3 M2L): row `box` of the replica's split array.
-__device__ __forceinline__ void store_split(uint16_t* __restrict__ msplit_rep, int KP, int64_t box, int k,
+// First box of level l in the level-major box order: (8^l - 1) / 7.
+__device__ __forceinline__ int64_t lev_offset(int l) { return (((int64_t)1 << (3 * l)) - 1) / 7; }
+
+// Row of box m (Morton index) of level lev >= 1 in the interleaved split
+// array: per level, the boxes of one parity class (the low bit of each
+// coordinate) together, in raster order of the halved coordinates.  The
+// sources of a class's neighbouring target columns are then neighbouring rows
+// for every offset.
+__device__ __forceinline__ uint32_t split_row(int lev, uint32_t m) {
+    int ux, uy, uz;
+    unmorton(m >> 3, ux, uy, uz);
+    const int sh = lev - 1;
+    return (uint32_t)(lev_offset(lev) - 1) + ((m & 7) << (3 * sh)) + (((ux << sh) + uy) << sh) + uz;
+}
+
+// Split an FP32 expansion coefficient into bf16 hi + lo parts (the source
+// layout of the bf16x3 M2L) and store it for box m of level lev in the
+// replica's split array.  split_kp = KP: rows [box][hi/lo][KP]; split_kp =
+// -KP: eight rows interleaved in 16-byte chunks, [row / 8][hi/lo][KP / 8][row % 8][8].
+__device__ __forceinline__ void store_split(uint16_t* __restrict__ msplit_rep, int split_kp, int lev, int64_t m, int k,
                                             float v) {
     const __bf16 h = (__bf16)v;
     const __bf16 l = (__bf16)(v - (float)h);
-    uint16_t* row = msplit_rep + (size_t)box * 2 * KP;
-    row[k] = __builtin_bit_cast(uint16_t, h);
-    row[KP + k] = __builtin_bit_cast(uint16_t, l);
+    if (split_kp > 0) {
+        uint16_t* row = msplit_rep + (size_t)(lev_offset(lev) + m) * 2 * split_kp;
+        row[k] = __builtin_bit_cast(uint16_t, h);
+        row[split_kp + k] = __builtin_bit_cast(uint16_t, l);
+    } else {
+        const uint32_t r = split_row(lev, (uint32_t)m);
+        uint16_t* at = msplit_rep + (size_t)(r >> 3) * 16 * -split_kp + (k >> 3) * 64 + (r & 7) * 8 + (k & 7);
+        at[0] = __builtin_bit_cast(uint16_t, h);
+        at[8 * -split_kp] = __builtin_bit_cast(uint16_t, l);
+    }
+}
+
+// A replica's split array.
+__device__ __forceinline__ uint16_t* split_of(uint16_t* msplit_all, int64_t nbox, int split_kp, int rep) {
+    return msplit_all ? msplit_all + (size_t)rep * (nbox + 1) * 2 * abs(split_kp) : nullptr;
 }
 
 // ------------------------------------------------------------------ fills
@@ -974,7 +1003,7 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
         mult[(size_t)gb * g.Kp + tid] = acc;
         if constexpr (sizeof(T) == 4)
             if (msplit_all)
-                store_split(msplit_all + (size_t)blockIdx.y * (g.nbox + 1) * 2 * split_kp, split_kp, gb, tid, acc);
+                store_split(split_of(msplit_all, g.nbox, split_kp, blockIdx.y), split_kp, g.depth, leaf, tid, acc);
     }
     if (g.periodic && tid == 0) {
         double a2 = 0.0, aq = 0.0;
@@ -1009,9 +1038,6 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
 }
 
 // ------------------------------------------------------------------ tree passes
-
-// First box of level l in the level-major box order: (8^l - 1) / 7.
-__device__ __forceinline__ int64_t lev_offset(int l) { return (((int64_t)1 << (3 * l)) - 1) / 7; }
 
 constexpr int kGatherPer = 8 * kKMax / kTreeThreads;  // child coefficients per thread
 
@@ -1090,7 +1116,7 @@ __device__ __forceinline__ void gather_children_parts(const Geo& g, int64_t box,
             const T tv = (T)v[m];
             mult[(size_t)(cb + c) * g.Kp + k] = tv;
             if constexpr (sizeof(T) == 4)
-                if (msplit) store_split(msplit, split_kp, cb + c, k, (float)tv);
+                if (msplit) store_split(msplit, split_kp, clev, 8 * box + c, k, (float)tv);
             xs[i] = refl_sign(c, refl_bits(k)) * (double)tv;
         }
     }
@@ -1132,7 +1158,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2m(Geo g, int lev, T* __restr
         // lev = d - 2: the children's multipoles from the leaves' M2M terms
         gather_children_parts<T>(g, box, m2m_part_all + (size_t)rp * g.nleaf * K, mult,
                                  leaf_part_all + (size_t)rp * g.nleaf * 2, box_part,
-                                 msplit_all ? msplit_all + (size_t)rp * (g.nbox + 1) * 2 * split_kp : nullptr,
+                                 split_of(msplit_all, g.nbox, split_kp, rp),
                                  split_kp, xs, ps);
     else
         gather_children<T>(g, lev + 1, 8 * (int64_t)box, mult, leaf_part_all + (size_t)rp * g.nleaf * 2,
@@ -1148,7 +1174,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2m(Geo g, int lev, T* __restr
         if (root_part_all) xs[r] = refl_sign(box, refl_bits(r)) * v;
         if constexpr (sizeof(T) == 4)
             if (msplit_all)
-                store_split(msplit_all + (size_t)rp * (g.nbox + 1) * 2 * split_kp, split_kp, gb, r, (float)v);
+                store_split(split_of(msplit_all, g.nbox, split_kp, rp), split_kp, lev, box, r, (float)v);
     }
     if (g.periodic && threadIdx.x < 2) {
         double v = 0.0;
@@ -1627,7 +1653,8 @@ __global__ __launch_bounds__(256) void k_m2l_plain(Geo g, const T* __restrict__ 
 // The targets that share a child class (position inside their parent) share
 // the same 189 translation offsets, so for every offset o the class does
 // lambda~[:, T] += T(o) mu~[:, T - o]: a dense (K x K) x (K x columns) product.
-// bf16x3 plans run it here, FP32 and FP64 plans in m2l_mma.hip.  Chunks of
+// bf16x3 plans run it here (resident sources) and in m2l_bf16x3.hip, FP32 and
+// FP64 plans in m2l_mma.hip.  Chunks of
 // offsets write partial sums that are added in a fixed order.
 //   BF16X3 v_mfma_f32_16x16x32_bf16 A lane l: A[l%16][8(l/16)+e], B: B[8(l/16)+e][l%16],
 //          output: lane l holds D[4(l/16) + v][l%16];
@@ -1666,200 +1693,13 @@ __device__ __forceinline__ bool m2l_column(const Geo& g, int cls, int tile, int 
     return false;
 }
 
-// bf16x3 matrix-core M2L with direct global-to-LDS staging (gfx950
-// global_load_lds_dwordx4: each lane's 16 bytes land at the wavefront's LDS
-// base + 16 lane).  The operator bank and the source expansions are stored
-// pre-split into bf16 hi/lo parts in layouts that are their own LDS images:
-//   operator o: [part][KC][RP] chunks of 8 bf16 (chunk kc of row r holds
-//               k = 8 kc .. 8 kc + 7), 2 KC RP chunks, zero padded;
-//   box b:      [part][KC] chunks, row nbox of each replica all zero.
-// A step (one offset) copies the operator contiguously and, per target
-// column, the source box's 2 KC chunks plus one pad chunk, consecutive lanes
-// on consecutive chunks of one source row (a few cache lines per copy
-// instruction instead of one per lane); the source box of every column for
-// the offset two steps ahead is tabulated in LDS by the column's thread.  The
-// odd row stride 2 KC + 1 puts the 16 columns of a fragment read in distinct
-// LDS banks, and the operator fragments are 16 consecutive 16-byte chunks per
-// quarter wavefront.  With two buffers the copy of offset
-// i + 1 is in flight while offset i is multiplied: one wait and one barrier
-// per offset.  Products Th mh + Th ml + Tl mh accumulate in FP32.
-//
-// Every class works from the 189 operators of class 0 (the bank holds those
-// only, in list order): reflecting the axes whose bit is set in the class
-// maps class 0's offsets onto the class's own, and T(P o) = S T(o) S with S
-// the diagonal +-1 reflection signs.  So a column of class c applies T(o') of
-// the canonical offset o' to S mu of the source at offset P o' (signs flipped
-// on the B fragments) and its result is S times the accumulator (at the
-// store).  Offset chunks are then equal for all classes.
 constexpr int kM2LThreads = 64 * kM2LWaves;
-// source copy slots per lane: kM2LTile columns of up to 2 KC + 1 = 33 chunks
-constexpr int kM2LSlots = (kM2LTile * (8 * kM2LMaxKs + 1) + kM2LThreads - 1) / kM2LThreads;
 
+// Direct global-to-LDS copy (gfx950 global_load_lds_dwordx4): each lane's 16
+// bytes land at the wavefront's LDS base + 16 lane.
 __device__ __forceinline__ void lds_dma16(const uint4* gsrc, uint4* lds_wave_base) {
     __builtin_amdgcn_global_load_lds((const void*)gsrc,
                                      (__attribute__((address_space(3))) void*)lds_wave_base, 16, 0, 0);
-}
-
-template <int RT>
-__global__ __launch_bounds__(kM2LThreads) void k_m2l_bf16x3(Geo g, M2LGeom mg,
-                                                           const M2LTask* __restrict__ tasks,
-                                                           const int16_t* __restrict__ olist,
-                                                           const int16_t* __restrict__ cstart,
-                                                           const uint4* __restrict__ msplit,
-                                                           const uint4* __restrict__ bank, int nbuf,
-                                                           const uint4* __restrict__ sign_tab,
-                                                           float* __restrict__ loc, float* __restrict__ part) {
-    extern __shared__ __align__(16) uint4 lds_q[];
-    __shared__ int col_box[kM2LTile];
-    __shared__ int src_box[2][kM2LTile];  // source box per column, two offsets ahead
-    const int KC = mg.KP / 8;
-    // sources: per target column its 2 KC chunks and one pad chunk (odd row
-    // stride: the 16 columns of a fragment read fall in distinct LDS banks)
-    const int SBc = 2 * KC + 1;
-    const int a_chunks = 2 * KC * mg.RP, b_chunks = SBc * kM2LTile;
-    const M2LTask tk = tasks[blockIdx.x];
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    msplit += (size_t)blockIdx.y * (g.nbox + 1) * 2 * KC;
-    loc += (size_t)blockIdx.y * g.nbox * g.Kp;
-    if (part) part += (size_t)blockIdx.y * mg.nchunk * mg.nt_all * g.Kp;
-    const bool active = tk.tile * kM2LTile + 16 * wave < mg.ncol;
-    // threads < kM2LTile: their target column and its place in the tree
-    int clev = 0, ctx = 0, cty = 0, ctz = 0;
-    const bool col_ok = tid < kM2LTile && m2l_column(g, tk.cls, tk.tile, tid, clev, ctx, cty, ctz);
-    const int cn = 1 << clev;
-    const int64_t clo = lev_offset(clev);
-    if (tid < kM2LTile) col_box[tid] = col_ok ? (int)(clo + morton(ctx, cty, ctz)) : -1;
-    const int o0 = tk.o0, o1 = tk.o1;
-    // the chunk's offsets, 64 at a time in a register (lane i: offset o0 + i)
-    const int16_t* ol = olist + tk.cls * 189;
-    int ol_reg = lane < o1 - o0 ? ol[o0 + lane] : 0;
-    const int fx = (tk.cls & 4) ? -1 : 1, fy = (tk.cls & 2) ? -1 : 1, fz = (tk.cls & 1) ? -1 : 1;
-    // source copy: buffer chunk e = t kM2LThreads + tid is chunk sc[t] of column
-    // sj[t], so consecutive lanes read consecutive chunks of one source row
-    int sj[kM2LSlots], sc[kM2LSlots];
-#pragma unroll
-    for (int t = 0; t < kM2LSlots; ++t) {
-        const int e = t * kM2LThreads + tid;
-        sj[t] = min(e / SBc, kM2LTile - 1);
-        const int c = e - (e / SBc) * SBc;
-        sc[t] = e < b_chunks ? (c == 2 * KC ? 0 : c) : -1;  // pad chunk: any in-bounds source
-    }
-    // the source boxes of offset slot oc for the block's columns (threads < kM2LTile)
-    auto sources = [&](int oc, int* dst) {
-        const int st = oc - o0;
-        if (st > 0 && (st & 63) == 0) ol_reg = ol[min(oc + lane, o1 - 1)];
-        const int oi = __builtin_amdgcn_readlane(ol_reg, st & 63);  // canonical offset
-        if (tid < kM2LTile) {
-            const int ox = fx * (oi / 49 - 3), oy = fy * ((oi / 7) % 7 - 3), oz = fz * (oi % 7 - 3);
-            int sx = ctx - ox, sy = cty - oy, sz = ctz - oz;
-            bool ok = col_ok;
-            if (g.periodic) {
-                sx &= cn - 1;
-                sy &= cn - 1;
-                sz &= cn - 1;
-            } else {
-                ok = ok && sx >= 0 && sy >= 0 && sz >= 0 && sx < cn && sy < cn && sz < cn;
-            }
-            dst[tid] = ok ? (int)(clo + morton(sx, sy, sz)) : (int)g.nbox;
-        }
-    };
-    auto issue = [&](int oc, uint4* dst) {
-        const uint4* src = bank + (size_t)oc * a_chunks;
-        for (int c0 = 0; c0 < a_chunks; c0 += kM2LThreads)
-            if (c0 + tid < a_chunks) lds_dma16(src + c0 + tid, dst + c0 + 64 * wave);
-        const int* sb = src_box[(oc - o0) & 1];
-        uint4* d = dst + a_chunks;
-#pragma unroll
-        for (int t = 0; t < kM2LSlots; ++t)
-            if (sc[t] >= 0) lds_dma16(msplit + (size_t)sb[sj[t]] * 2 * KC + sc[t], d + t * kM2LThreads + 64 * wave);
-    };
-
-    mf4 acc[RT];
-#pragma unroll
-    for (int r = 0; r < RT; ++r) acc[r] = mf4{0.f, 0.f, 0.f, 0.f};
-    const int col = 16 * wave + (lane & 15), kq = lane >> 4, row = lane & 15;
-    // sign bits of S for the lane's B fragments (k = 8 kc + e, kc = 4 si + kq),
-    // from the table sign_tab[class][kc] (bf16 sign-bit masks of 8 entries)
-    uint4 bsg[kM2LMaxKs];
-#pragma unroll
-    for (int si = 0; si < kM2LMaxKs; ++si) bsg[si] = sign_tab[tk.cls * 4 * kM2LMaxKs + 4 * si + kq];
-    if (o0 < o1) sources(o0, src_box[0]);
-    if (o0 + 1 < o1) sources(o0 + 1, src_box[1]);
-    __syncthreads();
-    if (o0 < o1) issue(o0, lds_q);
-    for (int oc = o0; oc < o1; ++oc) {
-        const int st = oc - o0;
-        uint4* cur = lds_q + (size_t)(st & (nbuf - 1)) * (a_chunks + b_chunks);
-        __builtin_amdgcn_s_waitcnt(0);  // this lane's copies of offset oc have landed
-        __syncthreads();                // everyone's have; the other buffer is free
-        if (nbuf == 2 && oc + 1 < o1) issue(oc + 1, lds_q + (size_t)((st + 1) & 1) * (a_chunks + b_chunks));
-        // the table slot of offset oc was last read by issue(oc) (before the
-        // barrier): it now takes offset oc + 2
-        if (oc + 2 < o1) sources(oc + 2, src_box[st & 1]);
-        if (active) {
-            const uint4* A = cur;
-            const uint4* B = cur + a_chunks;
-#pragma unroll
-            for (int si = 0; si < kM2LMaxKs; ++si) {
-                if (4 * si >= KC) break;
-                const int kc = 4 * si + kq;
-                uint4 uh = B[col * SBc + kc], ul = B[col * SBc + KC + kc];
-                uh.x ^= bsg[si].x;
-                uh.y ^= bsg[si].y;
-                uh.z ^= bsg[si].z;
-                uh.w ^= bsg[si].w;
-                ul.x ^= bsg[si].x;
-                ul.y ^= bsg[si].y;
-                ul.z ^= bsg[si].z;
-                ul.w ^= bsg[si].w;
-                const mbf8 bh = __builtin_bit_cast(mbf8, uh);
-                const mbf8 bl = __builtin_bit_cast(mbf8, ul);
-#pragma unroll
-                for (int r = 0; r < RT; ++r) {
-                    const mbf8 ah = __builtin_bit_cast(mbf8, A[kc * mg.RP + 16 * r + row]);
-                    const mbf8 al = __builtin_bit_cast(mbf8, A[(KC + kc) * mg.RP + 16 * r + row]);
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(al, bh, acc[r], 0, 0, 0);
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bl, acc[r], 0, 0, 0);
-                    acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ah, bh, acc[r], 0, 0, 0);
-                }
-            }
-        }
-        if (nbuf == 1 && oc + 1 < o1) {
-            __syncthreads();
-            issue(oc + 1, lds_q);
-        }
-    }
-    // Output rows get the class's signs S; the block's results are transposed
-    // through LDS (the staging buffers are free now) so that each box row is
-    // written as contiguous 16-byte chunks, padding rows (zero) included.
-    __syncthreads();
-    float* tt = (float*)lds_q;
-    const int ts = mg.RP + 4;
-    if (active) {
-#pragma unroll
-        for (int r = 0; r < RT; ++r) {
-            // row 16 r + 4 kq + v is entry 4 (kq & 1) + v of sign chunk 2 r + kq / 2
-            const uint4 m = sign_tab[tk.cls * 4 * kM2LMaxKs + 2 * r + (kq >> 1)];
-            const uint32_t lo = (kq & 1) ? m.z : m.x, hi = (kq & 1) ? m.w : m.y;
-#pragma unroll
-            for (int v = 0; v < 4; ++v) {
-                const uint32_t wd = v < 2 ? lo : hi;
-                const bool neg = (wd >> ((v & 1) ? 31 : 15)) & 1u;
-                tt[col * ts + 16 * r + 4 * kq + v] = neg ? -acc[r][v] : acc[r][v];
-            }
-        }
-    }
-    __syncthreads();
-    const int cpb = g.Kp / 4;
-    for (int c = tid; c < kM2LTile * cpb; c += kM2LThreads) {
-        const int j = c / cpb, q4 = c - j * cpb;
-        const int box = col_box[j];
-        if (box < 0) continue;
-        float* dst = mg.nchunk == 1
-                         ? loc + (size_t)box * g.Kp
-                         : part + ((size_t)tk.chunk * mg.nt_all + (box - lev_offset(g.lmin))) * g.Kp;
-        *(float4*)(dst + 4 * q4) = *(const float4*)(tt + j * ts + 4 * q4);
-    }
 }
 
 // bf16x3 M2L with resident sources, for trees whose classes have at most
@@ -1872,9 +1712,9 @@ __global__ __launch_bounds__(kM2LThreads) void k_m2l_bf16x3(Geo g, M2LGeom mg,
 // class's source rows once (2 KC chunks each, the rows in column order, plus
 // the zero row for open-boundary sources outside the domain) and per offset
 // only the operator; a column reads its source at the row of the source's
-// own column index (the rows are a permutation of the columns).  Staging,
-// fragments and signs are those of k_m2l_bf16x3; results go to memory
-// straight from the accumulators.
+// own column index (the rows are a permutation of the columns).  Operand
+// layouts and signs are those of k_m2l_bf16x3 (m2l_bf16x3.hip); results go to
+// memory straight from the accumulators.
 constexpr int kM2LRsMaxRT = 7;  // row tiles whose resident-source staging fits the LDS
 
 // What the periodic root needs (root_l == null: no root work-group): the
