@@ -659,9 +659,15 @@ void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
     const RepDesc* reps = P->ws.reps;
     const unsigned ab = nblocks(maxn, 256);
     if (!g.periodic) {
-        const int nb = (int)std::min<int64_t>(kBboxBlocks, ab);
-        k_bbox<T><<<dim3(nb, R), 256, 0, st>>>(x, set0, P->ws.reps, P->ws.bbox_part);
-        k_bbox_final<<<R, 64, 0, st>>>(P->ws.bbox_part, nb, P->ws.dom);
+        // up to 16,384 atoms one block of 1,024 threads per replica forms the
+        // cube itself (16 atoms a thread; the second launch costs as much)
+        if (maxn <= 16384) {
+            k_bbox<T, 1024><<<dim3(1, R), 1024, 0, st>>>(x, set0, P->ws.reps, P->ws.bbox_part, P->ws.dom);
+        } else {
+            const int nb = (int)std::min<int64_t>(kBboxBlocks, nblocks(maxn, 1024));
+            k_bbox<T, 256><<<dim3(nb, R), 256, 0, st>>>(x, set0, P->ws.reps, P->ws.bbox_part, nullptr);
+            k_bbox_final<<<R, 64, 0, st>>>(P->ws.bbox_part, nb, P->ws.dom);
+        }
         set0.count = 0;  // stored by k_bbox
     }
     // bucket binning: the leaf kernel finds each leaf's atoms in its bucket and
@@ -825,6 +831,9 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
                 : P->p2p_waves == 4  ? k_near_far<T, 4, false>
                 : P->p2p_waves == 16 ? k_near_far<T, 16, false>
                                      : k_near_far<T, 8, false>;
+    if constexpr (sizeof(T) == 8)
+        if (P->p2p_blocks == 1 && P->p2p_waves == 8 && (int64_t)g.nleaf * P->p2p_split * R > 256)
+            near = k_near_far<T, 8, false, 4>;
     near<<<dim3(g.nleaf * P->p2p_split * P->p2p_blocks, R), 64 * P->p2p_waves, 0, st>>>(
         g, P->p2p_split, P->p2p_blocks, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx,
         (const T*)P->gcoef, qA, qB, site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status);
@@ -1035,6 +1044,15 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         P->p2p_waves = per_leaf <= 32.0 ? 4 : 8;
     }
     P->p2p_split = prm->p2p_split ? prm->p2p_split : 1;
+    // FP64 trees of few leaves (up to 128 over all replicas): a block per 32
+    // targets, so that the leaves spread over more CUs (64 leaves of 78 atoms:
+    // 47 -> 27 us)
+    if (P->fp64 && prm->p2p_split == 0 && P->p2p_waves == 8) {
+        const double leaves = (double)std::max(prm->max_replicas, 1) * std::ldexp(1.0, 3 * prm->depth);
+        const double per_leaf = (double)prm->max_atoms / leaves;
+        if (leaves <= 128 && per_leaf > 24.0 && per_leaf <= 256.0)
+            P->p2p_split = (int)std::min<double>(fmmk::kMaxSplit, std::ceil(1.25 * per_leaf / 32.0));
+    }
     // Few, full leaves (up to 128 over all replicas, more than 256 atoms each on
     // average): two blocks per round of 512 targets, at most four, so that the
     // wavefronts of a leaf do not pile up on one CU.  From the plan's maxima

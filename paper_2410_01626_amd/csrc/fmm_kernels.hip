@@ -280,56 +280,10 @@ __device__ __forceinline__ void store_reps(const RepSet& set, RepDesc* reps) {
 
 // ------------------------------------------------------------------ domain
 
-// Per-block min/max of the coordinates (open boundaries): part[b] = {min xyz, max xyz}.
-template <typename T>
-__global__ __launch_bounds__(256) void k_bbox(const T* __restrict__ x, RepSet set,
-                                              RepDesc* __restrict__ reps,
-                                              double* __restrict__ part) {
-    __shared__ double smin[3][256], smax[3][256];
-    store_reps(set, reps);
-    const RepDesc rd = first_rep(set, reps, blockIdx.y);
-    double mn[3] = {1e300, 1e300, 1e300}, mx[3] = {-1e300, -1e300, -1e300};
-    for (int64_t i = rd.a0 + blockIdx.x * 256 + threadIdx.x; i < rd.a0 + rd.n;
-         i += (int64_t)gridDim.x * 256)
-        for (int a = 0; a < 3; ++a) {
-            double v = (double)x[3 * i + a];
-            mn[a] = fmin(mn[a], v);
-            mx[a] = fmax(mx[a], v);
-        }
-    for (int a = 0; a < 3; ++a) {
-        smin[a][threadIdx.x] = mn[a];
-        smax[a][threadIdx.x] = mx[a];
-    }
-    __syncthreads();
-    for (int s = 128; s > 0; s >>= 1) {
-        if ((int)threadIdx.x < s)
-            for (int a = 0; a < 3; ++a) {
-                smin[a][threadIdx.x] = fmin(smin[a][threadIdx.x], smin[a][threadIdx.x + s]);
-                smax[a][threadIdx.x] = fmax(smax[a][threadIdx.x], smax[a][threadIdx.x + s]);
-            }
-        __syncthreads();
-    }
-    const size_t pb = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
-    if (threadIdx.x == 0)
-        for (int a = 0; a < 3; ++a) {
-            part[6 * pb + a] = smin[a][0];
-            part[6 * pb + 3 + a] = smax[a][0];
-        }
-}
-
-// Root cube of an open system: dom = {lo_x, lo_y, lo_z, edge}.  The edge is the
-// largest extent, enlarged by a relative 2^-20 so no atom sits on the far face.
-// One block per replica; dom + 8 r receives that replica's cube.
-__global__ void k_bbox_final(const double* __restrict__ part, int nblk, double* __restrict__ dom_all) {
-    if (threadIdx.x != 0) return;
-    double* dom = dom_all + 8 * blockIdx.x;
-    part += (size_t)6 * nblk * blockIdx.x;
-    double mn[3] = {1e300, 1e300, 1e300}, mx[3] = {-1e300, -1e300, -1e300};
-    for (int b = 0; b < nblk; ++b)
-        for (int a = 0; a < 3; ++a) {
-            mn[a] = fmin(mn[a], part[6 * b + a]);
-            mx[a] = fmax(mx[a], part[6 * b + 3 + a]);
-        }
+// Root cube of an open system from its extent: dom = {lo_x, lo_y, lo_z, edge}.
+// The edge is the largest extent, enlarged by a relative 2^-20 so no atom sits
+// on the far face.
+__device__ __forceinline__ void root_cube(double (&mn)[3], const double (&mx)[3], double* __restrict__ dom) {
     double e = fmax(mx[0] - mn[0], fmax(mx[1] - mn[1], mx[2] - mn[2]));
     if (!(e > 0) || !(e < 1e300)) {  // no atoms, or all atoms at one point
         e = 1.0;
@@ -338,6 +292,104 @@ __global__ void k_bbox_final(const double* __restrict__ part, int nblk, double* 
     e *= 1.0 + 0x1p-20;
     for (int a = 0; a < 3; ++a) dom[a] = mn[a] - 0x1p-21 * e;
     dom[3] = e;
+}
+
+// Minima mn and maxima mx over the NT threads of a block, left in thread 0:
+// by lane exchange within each wavefront, then of the wavefronts' values
+// within the first.
+template <int NT, typename V>
+__device__ __forceinline__ void block_minmax(V (&mn)[3], V (&mx)[3]) {
+    constexpr int NW = NT / 64;
+    __shared__ V wmm[6][NW];
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    auto lanes = [&](int n) {
+        for (int off = n >> 1; off > 0; off >>= 1)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                mn[a] = min(mn[a], __shfl_xor(mn[a], off, 64));
+                mx[a] = max(mx[a], __shfl_xor(mx[a], off, 64));
+            }
+    };
+    lanes(64);
+    if (NW == 1) return;
+    if (lane == 0)
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            wmm[a][wave] = mn[a];
+            wmm[3 + a][wave] = mx[a];
+        }
+    __syncthreads();
+    if (wave == 0) {
+#pragma unroll
+        for (int a = 0; a < 3; ++a) {
+            mn[a] = wmm[a][lane & (NW - 1)];
+            mx[a] = wmm[3 + a][lane & (NW - 1)];
+        }
+        lanes(NW);
+    }
+}
+
+// Min/max of the coordinates (open boundaries).  Per block: part[b] = {min xyz,
+// max xyz}; with dom (one block per replica) the root cube itself.  Four atoms
+// per thread and round keep twelve loads in flight.
+template <typename T, int NT>
+__global__ __launch_bounds__(NT) void k_bbox(const T* __restrict__ x, RepSet set, RepDesc* __restrict__ reps,
+                                             double* __restrict__ part, double* __restrict__ dom_all) {
+    store_reps(set, reps);
+    const RepDesc rd = first_rep(set, reps, blockIdx.y);
+    // in the input's type (exact); +-infinity stands for no atom
+    T tn[3], tx[3];
+    for (int a = 0; a < 3; ++a) {
+        tn[a] = (T)INFINITY;
+        tx[a] = (T)-INFINITY;
+    }
+    const int64_t stride = (int64_t)gridDim.x * NT;
+    for (int64_t i0 = blockIdx.x * (int64_t)NT + threadIdx.x; i0 < rd.n; i0 += 4 * stride) {
+        T v[4][3];
+#pragma unroll
+        for (int m = 0; m < 4; ++m) {
+            // past the end: the thread's first atom again
+            const int64_t i = rd.a0 + (i0 + m * stride < rd.n ? i0 + m * stride : i0);
+            for (int a = 0; a < 3; ++a) v[m][a] = x[3 * i + a];
+        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m)
+            for (int a = 0; a < 3; ++a) {
+                tn[a] = min(tn[a], v[m][a]);
+                tx[a] = max(tx[a], v[m][a]);
+            }
+    }
+    block_minmax<NT>(tn, tx);
+    if (threadIdx.x != 0) return;
+    double mn[3], mx[3];
+    for (int a = 0; a < 3; ++a) {
+        mn[a] = fmin(1e300, (double)tn[a]);
+        mx[a] = fmax(-1e300, (double)tx[a]);
+    }
+    if (dom_all) {
+        root_cube(mn, mx, dom_all + 8 * blockIdx.y);
+        return;
+    }
+    const size_t pb = (size_t)blockIdx.y * gridDim.x + blockIdx.x;
+    for (int a = 0; a < 3; ++a) {
+        part[6 * pb + a] = mn[a];
+        part[6 * pb + 3 + a] = mx[a];
+    }
+}
+
+// The root cube of every replica (one wavefront each) from its blocks'
+// extents.  (One thread reading 256 partials in turn took 55 us.)
+__global__ __launch_bounds__(64) void k_bbox_final(const double* __restrict__ part, int nblk, double* __restrict__ dom_all) {
+    part += (size_t)6 * nblk * blockIdx.x;
+    double mn[3] = {1e300, 1e300, 1e300}, mx[3] = {-1e300, -1e300, -1e300};
+#pragma unroll 4
+    for (int b = threadIdx.x; b < nblk; b += 64)
+        for (int a = 0; a < 3; ++a) {
+            mn[a] = fmin(mn[a], part[6 * b + a]);
+            mx[a] = fmax(mx[a], part[6 * b + 3 + a]);
+        }
+    block_minmax<64>(mn, mx);
+    if (threadIdx.x == 0) root_cube(mn, mx, dom_all + 8 * blockIdx.x);
 }
 
 // ------------------------------------------------------------------ binning
@@ -508,26 +560,50 @@ __global__ __launch_bounds__(1024) void k_scan2(const RepDesc* __restrict__ reps
     int32_t* st = leaves ? leaf_start + (size_t)blockIdx.x * (nleaf + 1) : s1;
     const int64_t n = leaves ? nleaf : n1;
     const int32_t base = leaves ? (int32_t)reps[blockIdx.x].a0 : 0;
-    __shared__ int32_t part[1024];
-    const int t = threadIdx.x;
-    const int64_t chunk = (n + 1023) / 1024;
-    const int64_t b = t * chunk, e = (b + chunk < n) ? b + chunk : n;
-    int32_t sum = 0;
-    for (int64_t i = b; i < e; ++i) sum += cnt[i];
-    part[t] = sum;
-    __syncthreads();
-    for (int off = 1; off < 1024; off <<= 1) {
-        int32_t v = (t >= off) ? part[t - off] : 0;
+    // Tiles of 32,768 counts: a wavefront takes 2,048 in a row, eight loads of
+    // four counts per lane in flight; lane sums, DPP scans and the wavefronts'
+    // totals give every count its start.  (A chunk per thread, read twice one
+    // count at a time, took 57 us for the 32,768 leaves of depth 5.)
+    constexpr int E = 8, kTile = 1024 * 4 * E;
+    __shared__ int32_t wtot[16];
+    const int t = threadIdx.x, wave = t >> 6, lane = t & 63;
+    int32_t run = base;
+    for (int64_t b0 = 0; b0 < n || b0 == 0; b0 += kTile) {
+        int32_t v[E][4];
+        const int64_t w0 = b0 + (int64_t)wave * (256 * E) + 4 * lane;
+#pragma unroll
+        for (int j = 0; j < E; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) v[j][q] = w0 + 256 * j + q < n ? cnt[w0 + 256 * j + q] : 0;
+        int32_t off[E], tot = 0;
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            const int32_t s4 = (v[j][0] + v[j][1]) + (v[j][2] + v[j][3]);
+            const int32_t inc = wave_scan<int32_t>(s4);
+            off[j] = tot + inc - s4;
+            tot += lane_value<int32_t>(inc, 63);
+        }
+        if (lane == 0) wtot[wave] = tot;
         __syncthreads();
-        part[t] += v;
+        int32_t wbase = run, all = 0;
+#pragma unroll
+        for (int w = 0; w < 16; ++w) {
+            wbase += w < wave ? wtot[w] : 0;
+            all += wtot[w];
+        }
+#pragma unroll
+        for (int j = 0; j < E; ++j) {
+            int32_t r = wbase + off[j];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                if (w0 + 256 * j + q < n) st[w0 + 256 * j + q] = r;
+                r += v[j][q];
+            }
+        }
+        run += all;
         __syncthreads();
     }
-    int32_t run = base + part[t] - sum;
-    for (int64_t i = b; i < e; ++i) {
-        st[i] = run;
-        run += cnt[i];
-    }
-    if (t == 1023) st[n] = base + part[1023];
+    if (t == 0) st[n] = run;
 }
 
 __global__ __launch_bounds__(256) void k_scatter(Geo g, const RepDesc* __restrict__ reps,
@@ -1979,7 +2055,15 @@ template <typename T> __device__ __forceinline__ T inv_sqrt(T v);
 // hardware reciprocal square root (about 1 ulp); pair distances squared are
 // far from the denormal range, so no range scaling is needed
 template <> __device__ __forceinline__ float inv_sqrt<float>(float v) { return __builtin_amdgcn_rsqf(v); }
-template <> __device__ __forceinline__ double inv_sqrt<double>(double v) { return rsqrt(v); }
+// FP64: the hardware estimate and one third-order step (the library function's
+// own refinement, without its test for zero and infinity: a zero distance is
+// handled by the caller, and infinite ones do not occur)
+__device__ __forceinline__ double inv_sqrt_est(double v) { return __builtin_amdgcn_rsq(v); }
+template <> __device__ __forceinline__ double inv_sqrt<double>(double v) {
+    const double y = inv_sqrt_est(v);
+    const double e = __builtin_fma(-(y * v), y, 1.0);
+    return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
+}
 __device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
 __device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
@@ -2001,8 +2085,12 @@ __device__ __forceinline__ double fma_(double a, double b, double c) { return __
 // sources ahead.  51,200 atoms at depth 2 (64 leaves of 800): 2,103 -> 792 us
 // (the longest wavefront sums 64 targets over 24,000 sources: 68 issue cycles
 // per source, 680 us at 2.4 GHz).
-template <typename T, int kNW, bool kBig>
-__global__ __launch_bounds__(64 * kNW) void k_near_far(
+//
+// kOcc: wavefronts per SIMD the registers are capped for.  FP64 with more
+// blocks than CUs takes 4 (two blocks per CU at the price of some spills: 30k
+// box 89 -> 79 us), with fewer 1 (64 leaves: 26 us against 31).
+template <typename T, int kNW, bool kBig, int kOcc = 1>
+__global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     Geo g, int nsplit, int nblk, const RepDesc* __restrict__ reps, const vec4_t<T>* __restrict__ pos,
     const int32_t* __restrict__ leaf_start_all, const int32_t* __restrict__ perm,
     const double* __restrict__ dom_all, const T* __restrict__ loc_all,
@@ -2328,6 +2416,70 @@ __global__ __launch_bounds__(64 * kNW) void k_near_far(
                         }
                         for (; i < je_; ++i) pair(tile[i]);
                         return;
+                    }
+                    for (; j < j1; j += ngrp) pair(tile[j]);
+                } else if constexpr (sizeof(T) == 8) {
+                    // four sources side by side, stage by stage (the scheduling
+                    // barriers keep the compiler from running them one after the
+                    // other): the FP64 chain of a pair is long and only two
+                    // wavefronts share a SIMD (30k box: 99 -> 89 us)
+                    for (; j + 3 * ngrp < j1; j += 4 * ngrp) {
+                        vec4_t<T> s4[4];
+                        T dx[4], dy[4], dz[4], r2[4], ri[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) s4[k] = tile[j + k * ngrp];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            dx[k] = me.x - s4[k].x;
+                            dy[k] = me.y - s4[k].y;
+                            dz[k] = me.z - s4[k].z;
+                        }
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) r2[k] = dy[k] * dy[k];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) r2[k] = fma_(dx[k], dx[k], r2[k]);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) r2[k] = fma_(dz[k], dz[k], r2[k]);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) ri[k] = inv_sqrt_est(r2[k]);
+                        __builtin_amdgcn_sched_barrier(0);
+                        T e[4], g3[4];
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) e[k] = -(ri[k] * r2[k]);
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) e[k] = fma_(e[k], ri[k], T(1));
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            g3[k] = fma_(e[k], T(0.375), T(0.5));
+                            e[k] = ri[k] * e[k];
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            ri[k] = fma_(e[k], g3[k], ri[k]);
+                            if constexpr (decltype(guard)::value) ri[k] = r2[k] > T(0) ? ri[k] : T(0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            e[k] = s4[k].w * ri[k];
+                            g3[k] = ri[k] * ri[k];
+                            ph = fma_(s4[k].w, ri[k], ph);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) e[k] *= g3[k];
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int k = 0; k < 4; ++k) {
+                            fx = fma_(e[k], dx[k], fx);
+                            fy = fma_(e[k], dy[k], fy);
+                            fz = fma_(e[k], dz[k], fz);
+                        }
                     }
                     for (; j < j1; j += ngrp) pair(tile[j]);
                 } else {
@@ -2742,7 +2894,13 @@ __global__ __launch_bounds__(256) void k_reduce(Geo g, int R, int64_t nparts,
         vt += cphi[i] * ((1.0 - lp) * (b0 - a0) + lp * (d0 - c0));
     };
     if (b < R) {
-        for (int64_t i = t; i < nparts; i += 256) v += leaf_energy[(size_t)b * nparts + i];
+        // (eight loads in flight: 32,768 leaf partials one at a time took 36 us)
+        const double* le = leaf_energy + (size_t)b * nparts;
+        double v8[8] = {0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0, 0.0};
+        for (int64_t i = t; i < nparts; i += 8 * 256)
+#pragma unroll
+            for (int j = 0; j < 8; ++j) v8[j] += i + 256 * j < nparts ? le[i + 256 * j] : 0.0;
+        v = ((v8[0] + v8[1]) + (v8[2] + v8[3])) + ((v8[4] + v8[5]) + (v8[6] + v8[7]));
         // bonded exclusions: the removed pair energies, same units
         if (excl_e)
             for (int i = t; i < excl_parts; i += 256) v += excl_e[(size_t)b * excl_parts + i];
