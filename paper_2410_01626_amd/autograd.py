@@ -7,13 +7,27 @@ non-differentiable output.  For an upstream weight w on E alone,
 fmm_eval_adjoint returns
     dE/dx = -w F,  dE/dqA = w (1 - lambda_s) phi,  dE/dqB = w lambda_s phi,
     dE/dlambda = w dV/dlambda
-(sites -1: dE/dqA = w phi, dE/dqB = 0); with weights on phi or F as well,
+(sites -1: dE/dqA = w phi, dE/dqB = 0); with weights on phi or F (whatever their
+values: none is looked at, backward never waits for the device),
 fmm_eval_adjoint_full returns the gradient of w E + gphi . phi + gF . F in one
 tree pass (charges and, as second sources, charges gphi with dipoles -q gF).
 """
 from __future__ import annotations
 
 import torch
+
+
+def _order_streams(plan, device, weights):
+    """A plan on another stream than autograd's reads the upstream weights (and
+    takes the memory of its outputs) after the work queued here so far."""
+    here = torch.cuda.current_stream(device)
+    if here.cuda_stream == plan.stream.cuda_stream:
+        return
+    there = torch.cuda.ExternalStream(plan.stream.cuda_stream, device=device)
+    there.wait_stream(here)
+    for t in weights:
+        if t is not None:
+            t.record_stream(there)
 
 
 class FmmCoulomb(torch.autograd.Function):
@@ -24,6 +38,9 @@ class FmmCoulomb(torch.autograd.Function):
         ctx.plan = plan
         ctx.box = box
         ctx.mark_non_differentiable(out["dVdl"])
+        # outputs the loss does not use arrive as None in backward, not as zeros
+        # that only a wait for the device could tell from weights
+        ctx.set_materialize_grads(False)
         return out["E"], out["F"], out["phi"], out["dVdl"]
 
     @staticmethod
@@ -31,15 +48,14 @@ class FmmCoulomb(torch.autograd.Function):
         if gdVdl is not None and bool(torch.any(gdVdl != 0)):
             raise NotImplementedError("dV/dlambda is not differentiable; got a gradient on it")
         x, qA, qB, lam, site = ctx.saved_tensors
-        w = (gE if gE is not None else torch.zeros(1, device=x.device)).to(torch.float64)
-        w = w.reshape(1).contiguous()
-        use_phi = gphi is not None and bool(torch.any(gphi != 0))
-        use_F = gF is not None and bool(torch.any(gF != 0))
-        if use_phi or use_F:
-            adj = ctx.plan.eval_adjoint_full(
-                x, qA, qB, site, lam, gE=w,
-                gphi=gphi.to(x.dtype).contiguous() if use_phi else None,
-                gF=gF.to(x.dtype).contiguous() if use_F else None, box=ctx.box)
+        w = None if gE is None else gE.to(torch.float64).reshape(1).contiguous()
+        gphi = None if gphi is None else gphi.to(x.dtype).contiguous()
+        gF = None if gF is None else gF.to(x.dtype).contiguous()
+        if w is None and gphi is None and gF is None:
+            w = torch.zeros(1, dtype=torch.float64, device=x.device)
+        _order_streams(ctx.plan, x.device, (w, gphi, gF))
+        if gphi is not None or gF is not None:
+            adj = ctx.plan.eval_adjoint_full(x, qA, qB, site, lam, gE=w, gphi=gphi, gF=gF, box=ctx.box)
         else:
             adj = ctx.plan.eval_adjoint(x, qA, qB, site, lam, w, box=ctx.box)
         return (adj["grad_x"] if ctx.needs_input_grad[0] else None,
