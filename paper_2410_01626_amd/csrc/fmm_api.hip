@@ -791,6 +791,15 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     return order;
 }
 
+// FP32 near field with a wavefront per leaf (the same sums as the block per
+// leaf with 4 wavefronts): from kSmallLeaves leaves on, which give every SIMD
+// four wavefronts (4,096 leaves of 15: 76 -> 41 us, of 29: 108 -> 90 us; 512
+// leaves of 10: 15 against 25 us), with at most kSmallFill atoms each.  The same
+// with eight slices, for p2p_waves = 8, would gain with 4,096 leaves of 37 and 49
+// atoms (153 -> 123, 199 -> 173 us) and lose with fuller ones (98 atoms: 520
+// against 557 us; 16 systems of 512 leaves of 68: 559 against 667 us).
+constexpr int64_t kSmallLeaves = 4096, kSmallFill = 48;
+
 // Enqueue one evaluation of R replicas (arguments already validated; rd holds
 // the host copy of the replica descriptors).  Every phase is one launch over
 // all replicas (grid y = replica).
@@ -834,9 +843,21 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
     if constexpr (sizeof(T) == 8)
         if (P->p2p_blocks == 1 && P->p2p_waves == 8 && (int64_t)g.nleaf * P->p2p_split * R > 256)
             near = k_near_far<T, 8, false, 4>;
-    near<<<dim3(g.nleaf * P->p2p_split * P->p2p_blocks, R), 64 * P->p2p_waves, 0, st>>>(
-        g, P->p2p_split, P->p2p_blocks, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx,
-        (const T*)P->gcoef, qA, qB, site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status);
+    bool small = false;
+    if constexpr (sizeof(T) == 4) {
+        small = P->p2p_waves == kSmallWaves && P->p2p_split == 1 && P->p2p_blocks == 1 &&
+                g.nleaf % (8 * kSmallWaves) == 0 && (int64_t)g.nleaf * R >= kSmallLeaves &&
+                maxn <= kSmallFill * g.nleaf;
+        if (small)
+            k_near_small<T><<<dim3(g.nleaf / kSmallWaves, R), 64 * kSmallWaves, near_small_lds<T>(g.K), st>>>(
+                g, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx, (const T*)P->gcoef, qA, qB,
+                site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status);
+    }
+    if (!small)
+        near<<<dim3(g.nleaf * P->p2p_split * P->p2p_blocks, R), 64 * P->p2p_waves, 0, st>>>(
+            g, P->p2p_split, P->p2p_blocks, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx,
+            (const T*)P->gcoef, qA, qB, site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order,
+            P->status);
     if (P->excl_n > 0)
         k_excl<T><<<dim3(ab, R), 256, 0, st>>>(g, reps, x, qA, qB, site, lam, fa, P->ws.dom, P->excl_start,
                                                P->excl_idx, phi, F, P->ws.cphi, fa.qC != nullptr,

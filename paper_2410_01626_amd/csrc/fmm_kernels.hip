@@ -167,6 +167,45 @@ __device__ __forceinline__ void for_rho_orders(int p, const RhoLds<T>& rc, int m
     }
 }
 
+// The same with lanes that differ in m0: every lane walks its own orders side
+// by side (for_rho_orders visits the orders one after the other, each with the
+// lanes of the other orders idle).
+template <typename T, typename Fn>
+__device__ __forceinline__ void for_rho_lane_orders(int p, const RhoLds<T>& rc, int m0, int dm, T x, T y, T z,
+                                                    Fn&& fn) {
+    const T r2 = x * x + y * y + z * z;
+    T cre = T(1), cim = T(0);
+    int mc = 0;
+    for (int m = m0; m <= p; m += dm) {
+        while (mc < m) {
+            ++mc;
+            const T fm = rc.f[mc];
+            const T nre = fm * (x * cre - y * cim);
+            const T nim = fm * (x * cim + y * cre);
+            cre = nre;
+            cim = nim;
+        }
+        const int k0 = (m == 0) ? 0 : 2 * m - 1;
+        fn(m * m + k0, m > 0, cre, cim);
+        if (m + 1 > p) continue;
+        T p0re = cre, p0im = cim;
+        T p1re = rc.a[(m + 1) * (kPMax + 1) + m] * z * cre;
+        T p1im = rc.a[(m + 1) * (kPMax + 1) + m] * z * cim;
+        fn((m + 1) * (m + 1) + k0, m > 0, p1re, p1im);
+        for (int l = m + 2; l <= p; ++l) {
+            const T al = rc.a[l * (kPMax + 1) + m];
+            const T bl = rc.b[l * (kPMax + 1) + m];
+            const T nre = al * z * p1re - bl * r2 * p0re;
+            const T nim = al * z * p1im - bl * r2 * p0im;
+            p0re = p1re;
+            p0im = p1im;
+            p1re = nre;
+            p1im = nim;
+            fn(l * l + k0, m > 0, p1re, p1im);
+        }
+    }
+}
+
 // Inclusive scan across the 64 lanes by DPP moves (register to register, no
 // LDS crossbar): shifts by 1, 2, 4 and 8 lanes within each row of 16 (a lane
 // shifted in from outside the row reads 0), then the last lane of row 0 added
@@ -2610,6 +2649,453 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     if (wave == 0) {
         esum = wave_sum<double>(esum);
         if (lane == 0) leaf_energy[blockIdx.x] = esum;
+    }
+}
+
+// LDS that one wavefront writes and reads back: its own accesses complete in
+// order, the compiler only has to keep them so.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Trees of many small leaves: one wavefront per leaf, four leaves per block.
+// Every sum of k_near_far<T, 4> keeps its order: the four slices of a source
+// pass, there one wavefront each, run one after the other here, each with its
+// far-field orders and its lane-group butterfly, and are added in the same
+// order.  A block per leaf mostly waits there (50 KB of LDS, three blocks per
+// CU, each a chain of set-up, staging, some 35 sources per lane, far field and
+// barriers) and repeats its set-up in every wavefront; here the wavefronts are
+// independent, sources pass through a window of kSmallWin each, the next four
+// are read while four are summed, and the lane groups of a far field take their
+// orders side by side.  Leaves of more than kSmallSolo atoms are done by the
+// whole block afterwards, in k_near_far's own split.  500,000 atoms at depth 5
+// (15 per leaf): 625 -> 290 us (the pair loop's issue cycles: about 140 us).
+// LDS: a window and the K gradient-table rows per wavefront, dynamic.
+constexpr int kSmallWaves = 4;
+constexpr int kSmallWin = 256;   // sources of a wavefront's window
+constexpr int kSmallSolo = 128;  // atoms of a leaf that one wavefront takes alone
+template <typename T>
+__host__ __device__ inline size_t near_small_lds(int K) {
+    return (size_t)kSmallWaves * (kSmallWin + K) * sizeof(vec4_t<T>);
+}
+template <typename T>
+__global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
+    Geo g, const RepDesc* __restrict__ reps, const vec4_t<T>* __restrict__ pos,
+    const int32_t* __restrict__ leaf_start_all, const int32_t* __restrict__ perm,
+    const double* __restrict__ dom_all, const T* __restrict__ loc_all,
+    const int32_t* __restrict__ gidx, const T* __restrict__ gcoef,
+    const T* __restrict__ qA, const T* __restrict__ qB, const int32_t* __restrict__ site,
+    T* __restrict__ phi_out, T* __restrict__ F_out,
+    double* __restrict__ leaf_energy_all, double* __restrict__ cphi, int unit_dq,
+    const int32_t* __restrict__ leaf_order_all, int32_t* __restrict__ status) {
+    using V4 = vec4_t<T>;
+    constexpr int kNW = kSmallWaves;
+    constexpr int CAP = 2048;  // sources of a pass: what k_near_far stages at a time
+    extern __shared__ char near_lds[];
+    __shared__ int nb_start[kNW][28], nb_pre[kNW][32];
+    __shared__ T nb_off[kNW][27][3];
+    __shared__ RhoLds<T> rho;
+    load_rho_lds<T, 64 * kNW>(rho, g.p);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    V4* tile = (V4*)near_lds + (size_t)wave * (kSmallWin + g.K);
+    V4* coef = tile + kSmallWin;  // (local coefficient, its three gradient rows)
+    const int64_t n_sites = reps[blockIdx.y].S;
+    const int32_t* leaf_start = leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1);
+    const double* dom = dom_all + 8 * blockIdx.y;
+    const T* loc = loc_all + (size_t)blockIdx.y * g.nbox * g.Kp;
+    double* leaf_energy = leaf_energy_all + (size_t)blockIdx.y * g.nleaf;
+    const int32_t* order = leaf_order_all ? leaf_order_all + (size_t)blockIdx.y * g.nleaf : nullptr;
+    const int nblk = gridDim.x;  // nleaf / kNW, a multiple of 8
+    // a block takes one leaf of each quarter of the order (leaves sorted by
+    // work, or neighbours of one cluster, do not meet in a block); without an
+    // order of work each XCD (blocks b, b + 8, ...) walks runs of up to 64
+    // neighbouring leaves, whose sources its L2 then holds
+    const int run = min(64, nblk >> 3);
+    const int bx = blockIdx.x % (8 * run);
+    const int b0 = order ? (int)blockIdx.x : (int)blockIdx.x - bx + (bx & 7) * run + (bx >> 3);
+    auto slot_of = [&](int w) -> int { return b0 + w * nblk; };
+    auto leaf_of = [&](int slot) { return order ? order[slot] : slot; };
+    const bool far = g.has_far;
+    const double edge = dom[3];
+    const double h = edge / g.nb;
+    const T ih = (T)(1.0 / h);
+    int cx = 0, cy = 0, cz = 0, lb = 0, total = 0, own_b = 0, own_e = 0;
+    int wb = 0, we = 0;  // sources [wb, we) are in the window
+
+    // neighbours, source ranges and far-field rows of a leaf, for this wavefront
+    auto setup = [&](int leaf) {
+        wave_lds_fence();
+        unmorton((uint32_t)leaf, cx, cy, cz);
+        lb = leaf_start[leaf];
+        if (far) {
+            const T* lsrc = loc + (size_t)(g.lev_off[g.depth] + leaf) * g.Kp;
+            for (int k = lane; k < g.K; k += 64) coef[k].x = lsrc[k];
+        }
+        int my_cnt = 0;
+        if (lane < 27) {
+            const int dx = lane / 9 - 1, dy = (lane / 3) % 3 - 1, dz = lane % 3 - 1;
+            int nx = cx + dx, ny = cy + dy, nz = cz + dz;
+            bool ok = true;
+            if (g.periodic) {
+                nx = (nx % g.nb + g.nb) % g.nb;
+                ny = (ny % g.nb + g.nb) % g.nb;
+                nz = (nz % g.nb + g.nb) % g.nb;
+            } else {
+                ok = nx >= 0 && ny >= 0 && nz >= 0 && nx < g.nb && ny < g.nb && nz < g.nb;
+            }
+            int s = 0;
+            if (ok) {
+                const uint32_t m = morton(nx, ny, nz);
+                s = leaf_start[m];
+                my_cnt = leaf_start[m + 1] - s;
+            }
+            nb_start[wave][lane] = s;
+            nb_off[wave][lane][0] = (T)(dx * h);
+            nb_off[wave][lane][1] = (T)(dy * h);
+            nb_off[wave][lane][2] = (T)(dz * h);
+        }
+        const int v = wave_scan<int>(my_cnt);
+        // nb_pre[i]: first source of neighbour i; 27: their number
+        if (lane < 27) nb_pre[wave][lane + 1] = v;
+        if (lane == 27) nb_pre[wave][0] = 0;
+        if (lane >= 28 && lane < 32) nb_pre[wave][lane] = 0x7fffffff;
+        wave_lds_fence();
+        total = __builtin_amdgcn_readlane(v, 26);
+        own_b = __builtin_amdgcn_readlane(v, 12);
+        own_e = __builtin_amdgcn_readlane(v, 13);
+        if (far) {
+            for (int e = lane; e < 3 * g.Kg; e += 64) {
+                const int a = e / g.Kg, r = e - a * g.Kg;
+                T gv = T(0);
+#pragma unroll
+                for (int t = 0; t < 4; ++t) {
+                    const int kk = gidx[(size_t)e * 4 + t];
+                    const T gc = gcoef[(size_t)e * 4 + t];
+                    if (kk >= 0) gv += gc * coef[kk].x;
+                }
+                ((T*)(coef + r))[1 + a] = gv;
+            }
+        }
+        wb = we = 0;
+        wave_lds_fence();
+    };
+    // sources [s, min(s + kSmallWin, total)) into the window
+    auto stage = [&](int s) {
+        constexpr int G = kSmallWin / 64;
+        wave_lds_fence();
+        const int cnt = min(kSmallWin, total - s);
+        V4 a[G];
+        int lo_[G];
+#pragma unroll
+        for (int m = 0; m < G; ++m) {
+            const int gsrc = s + min(lane + 64 * m, cnt - 1);
+            int lo = 0;  // largest i with nb_pre[i] <= gsrc (i < 27: gsrc < nb_pre[27])
+#pragma unroll
+            for (int b = 16; b >= 1; b >>= 1)
+                if (nb_pre[wave][lo + b] <= gsrc) lo += b;
+            lo_[m] = lo;
+            a[m] = pos[nb_start[wave][lo] + (gsrc - nb_pre[wave][lo])];
+        }
+#pragma unroll
+        for (int m = 0; m < G; ++m)
+            if (lane + 64 * m < cnt) {
+                V4 v = a[m];
+                v.x += nb_off[wave][lo_[m]][0];
+                v.y += nb_off[wave][lo_[m]][1];
+                v.z += nb_off[wave][lo_[m]][2];
+                tile[lane + 64 * m] = v;
+            }
+        wb = s;
+        we = s + cnt;
+        wave_lds_fence();
+    };
+    // slice `slice` of `wpc` of a chunk of targets (lane groups of gsz lanes;
+    // tj: this lane's target in the leaf), summed over the lane groups
+    auto run_slice = [&](const V4& me, bool tv, int tj, int slice, int wpc, int gsz, T& ph, T& fx, T& fy, T& fz) {
+        const int ngrp = 64 / gsz, grp = lane / gsz, lg = 6 - (31 - __builtin_clz(gsz));  // ngrp = 1 << lg
+        ph = fx = fy = fz = T(0);
+        for (int s0 = 0; s0 < total; s0 += CAP) {
+            const int cnt = min(CAP, total - s0);
+            const int sl = (cnt + wpc - 1) / wpc;
+            const int jb = s0 + slice * sl, je = s0 + min(slice * sl + sl, cnt);
+            // only the own leaf (neighbour 13, [own_b, own_e)) can hold a source at distance 0
+            for (int cur = jb; cur < je;) {
+                if (cur < wb || cur >= we) stage(cur);
+                const int end = min(je, we);
+                // lane group grp takes sources j0 + c, j0 + c + ngrp, ... of the
+                // slice's interleaving; nf of them in every group (a uniform
+                // count), one more in some.  Four at a time, the next four read
+                // while they are summed.
+                auto sweep = [&](int j0, int j1, auto guard) {
+                    if (j0 >= j1) return;
+                    const int first = j0 + ((grp - (j0 - jb)) & (ngrp - 1));
+                    const V4* src = tile + (first - wb);
+                    const int nf = (j1 - j0) >> lg, n4 = nf >> 2;
+                    auto pair = [&](const V4& s) {
+                        const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
+                        const T r2 = fma_(dz, dz, fma_(dx, dx, dy * dy));
+                        T ri;
+                        if constexpr (decltype(guard)::value) ri = r2 > T(0) ? inv_sqrt<T>(r2) : T(0);
+                        else ri = inv_sqrt<T>(r2);
+                        const T qr3 = (s.w * ri) * (ri * ri);
+                        ph = fma_(s.w, ri, ph);
+                        fx = fma_(qr3, dx, fx);
+                        fy = fma_(qr3, dy, fy);
+                        fz = fma_(qr3, dz, fz);
+                    };
+                    V4 sa[4], sb[4];
+                    if (n4 > 0) {
+                        auto load = [&](int blk, V4(&v)[4]) {
+                            const V4* q = src + (min(blk, n4 - 1) << (lg + 2));
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) v[t] = q[t << lg];
+                        };
+                        load(0, sa);
+                        for (int blk = 0; blk + 1 < n4; blk += 2) {
+                            load(blk + 1, sb);
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) pair(sa[t]);
+                            __builtin_amdgcn_sched_barrier(0);
+                            load(blk + 2, sa);
+                            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) pair(sb[t]);
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                        if (n4 & 1) {
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) pair(sa[t]);
+                        }
+                    }
+                    const int last = j1 - wb - 1;  // the last entry of the range
+                    V4 sr[4];
+#pragma unroll
+                    for (int t = 0; t < 3; ++t) sr[t] = tile[min(first - wb + ((4 * n4 + t) << lg), last)];
+                    sr[3] = tile[min(first - wb + (nf << lg), last)];
+#pragma unroll
+                    for (int t = 0; t < 3; ++t)
+                        if (4 * n4 + t < nf) pair(sr[t]);
+                    if (first + (nf << lg) < j1) pair(sr[3]);
+                };
+                sweep(cur, min(end, own_b), std::false_type{});
+                sweep(max(cur, own_b), min(end, own_e), std::true_type{});
+                sweep(max(cur, own_e), end, std::false_type{});
+                if (g.check && tv) {
+                    const int self_j = own_b + tj;
+                    const int j0 = max(cur, own_b), j1 = min(end, own_e);
+                    bool bad = false;
+                    for (int j = j0 + ((grp - (j0 - jb)) & (ngrp - 1)); j < j1; j += ngrp) {
+                        const V4 s = tile[j - wb];
+                        const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
+                        bad |= j != self_j && !(dx * dx + dy * dy + dz * dz > T(0));
+                    }
+                    if (bad) atomicOr(&status[0], kStatusCoincident);
+                }
+                cur = end;
+            }
+        }
+        if (far && tv) {
+            T fp = T(0), gx = T(0), gy = T(0), gz = T(0);
+            const int Kg = g.Kg;
+            for_rho_lane_orders<T>(g.p, rho, slice + wpc * grp, wpc * ngrp, me.x * ih, me.y * ih, me.z * ih,
+                                   [&](int kc, bool has_s, T re, T im) {
+                                       const V4 c = coef[kc];
+                                       V4 s;
+                                       if (has_s) s = coef[kc + 1];
+                                       fp += c.x * re;
+                                       if (has_s) fp += s.x * im;
+                                       if (kc < Kg) {
+                                           gx += c.y * re;
+                                           gy += c.z * re;
+                                           gz += c.w * re;
+                                           if (has_s) {
+                                               gx += s.y * im;
+                                               gy += s.z * im;
+                                               gz += s.w * im;
+                                           }
+                                       }
+                                   });
+            ph += fp * ih;
+            fx -= gx * ih * ih;
+            fy -= gy * ih * ih;
+            fz -= gz * ih * ih;
+        }
+        for (int off = gsz; off < 64; off <<= 1) {
+            ph += __shfl_xor(ph, off, 64);
+            fx += __shfl_xor(fx, off, 64);
+            fy += __shfl_xor(fy, off, 64);
+            fz += __shfl_xor(fz, off, 64);
+        }
+    };
+    // a target's outputs; returns charge times potential
+    auto finish = [&](const V4& me, int32_t i, int32_t st, double dq, T p, T ex, T ey, T ez) -> double {
+        if (g.periodic) {
+            // background: phi += (2 pi / 3) Q |t|^2 / V, field -= (4 pi / 3) Q t / V
+            const double Q = dom[4];
+            const double V = edge * edge * edge;
+            const double t0v = (double)me.x + (cx + 0.5) * h - 0.5 * edge;
+            const double t1v = (double)me.y + (cy + 0.5) * h - 0.5 * edge;
+            const double t2v = (double)me.z + (cz + 0.5) * h - 0.5 * edge;
+            p += (T)(2.0 * kPi / 3.0 * Q * (t0v * t0v + t1v * t1v + t2v * t2v) / V);
+            ex -= (T)(4.0 * kPi / 3.0 * Q * t0v / V);
+            ey -= (T)(4.0 * kPi / 3.0 * Q * t1v / V);
+            ez -= (T)(4.0 * kPi / 3.0 * Q * t2v / V);
+        }
+        const T q = me.w;
+        const T ke = (T)g.coulomb_k;
+        if (phi_out) phi_out[i] = ke * p;
+        if (F_out) {
+            F_out[3 * (size_t)i] = ke * q * ex;
+            F_out[3 * (size_t)i + 1] = ke * q * ey;
+            F_out[3 * (size_t)i + 2] = ke * q * ez;
+        }
+        if (st >= 0 && st < n_sites) cphi[i] = g.coulomb_k * dq * (double)p;
+        return (double)q * (double)p;
+    };
+    auto pow2_lanes = [](int tc) {
+        int z = 1;
+        while (z < tc) z <<= 1;
+        return z;
+    };
+    __syncthreads();  // rho
+
+    // k_near_far's split of its kNW wavefronts between the chunks of 64 of the
+    // tn targets from t0 on
+    auto split = [&](int left, int nch, int (&w)[kNW]) {
+        int gs[kNW];
+#pragma unroll
+        for (int c = 0; c < kNW; ++c) {
+            gs[c] = pow2_lanes(min(64, left - 64 * c));
+            w[c] = c < nch ? 1 : 0;
+        }
+        for (int e = nch; e < kNW; ++e) {
+            int best = 0, wbst = w[0], gb = gs[0];
+#pragma unroll
+            for (int c = 1; c < kNW; ++c)
+                if (c < nch && gs[c] * wbst > gb * w[c]) {
+                    best = c;
+                    wbst = w[c];
+                    gb = gs[c];
+                }
+#pragma unroll
+            for (int c = 0; c < kNW; ++c) w[c] += c == best ? 1 : 0;
+        }
+    };
+
+    const int slot = __builtin_amdgcn_readfirstlane(slot_of(wave));
+    const int leaf = __builtin_amdgcn_readfirstlane(leaf_of(slot));
+    const int ln = __builtin_amdgcn_readfirstlane(leaf_start[leaf + 1] - leaf_start[leaf]);
+    if (ln == 0 && lane == 0) leaf_energy[slot] = 0.0;
+    if (ln > 0 && ln <= kSmallSolo) {
+        static_assert(kSmallSolo == 128, "two chunks");
+        setup(leaf);
+        const int nch = ln > 64 ? 2 : 1;
+        int w[kNW];
+        split(ln, nch, w);
+        double esum = 0.0;
+        for (int c = 0; c < nch; ++c) {
+            const int tc = min(64, ln - 64 * c), gsz = pow2_lanes(tc);
+            const int grp = lane / gsz, tl = lane & (gsz - 1), wpc = c ? w[1] : w[0];
+            const bool tv = tl < tc;
+            const int tj = 64 * c + tl;
+            V4 me;
+            me.x = me.y = me.z = me.w = T(0);
+            int32_t i = 0, st = -1;
+            double dq = 0.0;
+            if (tv) {
+                me = pos[lb + tj];
+                i = perm[lb + tj];
+                st = site[i];
+                dq = unit_dq ? 1.0 : (double)qB[i] - (double)qA[i];
+            }
+            T p = T(0), ex = T(0), ey = T(0), ez = T(0);
+            for (int slice = 0; slice < wpc; ++slice) {
+                T ph, fx, fy, fz;
+                run_slice(me, tv, tj, slice, wpc, gsz, ph, fx, fy, fz);
+                p += ph;
+                ex += fx;
+                ey += fy;
+                ez += fz;
+            }
+            double e = 0.0;
+            if (tv && grp == 0) e = finish(me, i, st, dq, p, ex, ey, ez);
+            esum += e;
+        }
+        esum = wave_sum<double>(esum);
+        if (lane == 0) leaf_energy[slot] = esum;
+    }
+
+    // fuller leaves, by the whole block (uniform conditions); a slice's sums
+    // and a chunk's energies pass through the wavefronts' own windows
+    auto part = [&](int w, int a) { return (T*)((V4*)near_lds + (size_t)w * (kSmallWin + g.K)) + 64 * a; };
+    for (int b = 0; b < kNW; ++b) {
+        const int bslot = slot_of(b), bleaf = leaf_of(bslot);
+        const int tn = leaf_start[bleaf + 1] - leaf_start[bleaf];
+        if (tn <= kSmallSolo) continue;
+        setup(bleaf);
+        double esum = 0.0;
+        for (int t0 = 0; t0 < tn; t0 += 64 * kNW) {
+            const int nch = min(kNW, (tn - t0 + 63) / 64);
+            int w[kNW], wf[kNW + 1];
+            split(tn - t0, nch, w);
+            wf[0] = 0;
+#pragma unroll
+            for (int c = 0; c < kNW; ++c) wf[c + 1] = wf[c] + w[c];
+            int chunk = 0, wc0 = 0, wc1 = wf[1];
+#pragma unroll
+            for (int c = 1; c < kNW; ++c)
+                if (c < nch && wf[c] <= wave) {
+                    chunk = c;
+                    wc0 = wf[c];
+                    wc1 = wf[c + 1];
+                }
+            const int wpc = wc1 - wc0, slice = wave - wc0;
+            const int tc = min(64, tn - t0 - 64 * chunk), gsz = pow2_lanes(tc);
+            const int grp = lane / gsz, tl = lane & (gsz - 1);
+            const int tj = t0 + 64 * chunk + tl;
+            const bool tv = tl < tc;
+            V4 me;
+            me.x = me.y = me.z = me.w = T(0);
+            if (tv) me = pos[lb + tj];
+            T ph, fx, fy, fz;
+            run_slice(me, tv, tj, slice, wpc, gsz, ph, fx, fy, fz);
+            wave_lds_fence();
+            if (grp == 0) {
+                part(wave, 0)[tl] = ph;
+                part(wave, 1)[tl] = fx;
+                part(wave, 2)[tl] = fy;
+                part(wave, 3)[tl] = fz;
+            }
+            wb = we = 0;
+            __syncthreads();
+            double e = 0.0;
+            if (slice == 0 && grp == 0 && tv) {
+                T p = T(0), ex = T(0), ey = T(0), ez = T(0);
+                for (int v = wave; v < wave + wpc; ++v) {
+                    p += part(v, 0)[tl];
+                    ex += part(v, 1)[tl];
+                    ey += part(v, 2)[tl];
+                    ez += part(v, 3)[tl];
+                }
+                const int32_t i = perm[lb + tj];
+                e = finish(me, i, site[i], unit_dq ? 1.0 : (double)qB[i] - (double)qA[i], p, ex, ey, ez);
+            }
+            ((double*)part(wave, 4))[lane] = e;
+            __syncthreads();
+            if (wave == 0) {
+                double v = 0.0;
+                for (int c = 0; c < kNW; ++c) v += ((double*)part(c, 4))[lane];
+                esum += v;
+            }
+            __syncthreads();  // the windows are free again
+        }
+        if (wave == 0) {
+            esum = wave_sum<double>(esum);
+            if (lane == 0) leaf_energy[bslot] = esum;
+        }
     }
 }
 
