@@ -626,6 +626,15 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
     return false;
 }
 
+// FP32 near field with a wavefront per leaf (the same sums as the block per
+// leaf with 4 wavefronts): from kSmallLeaves leaves on, which give every SIMD
+// four wavefronts (4,096 leaves of 15: 76 -> 41 us, of 29: 108 -> 90 us; 512
+// leaves of 10: 15 against 25 us), with at most kSmallFill atoms each.  The same
+// with eight slices, for p2p_waves = 8, would gain with 4,096 leaves of 37 and 49
+// atoms (153 -> 123, 199 -> 173 us) and lose with fuller ones (98 atoms: 520
+// against 557 us; 16 systems of 512 leaves of 68: 559 against 667 us).
+constexpr int64_t kSmallLeaves = 4096, kSmallFill = 48;
+
 // Binning and leaf multipoles of R replicas (grid y = replica): replica
 // descriptors, the open bounding cube, leaf keys, the counting sort and the
 // leaf kernel (sort in leaf, gather with the interpolated charges, P2M).
@@ -695,6 +704,14 @@ void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
     const LeafBinArgs lb{P->ws.leaf_count, P->ws.key,          P->ws.rank,         P->ws.site_count,
                          P->ws.site_rank,  P->ws.site_start,   P->ws.site_members, (int)S_tot};
     const size_t lds = leaf_lds_bytes<T>(g.K) + (binned && S_tot > 0 ? (size_t)(256 + S_tot + 1) * 4 : 0);
+    if (!binned && !fold && g.nleaf % (kLeafThreads / 64) == 0 && (int64_t)g.nleaf * R >= kSmallLeaves &&
+        maxn <= kSmallFill * g.nleaf) {
+        // (leaves without bins: more than kScanFuseCap of them, or of sites)
+        k_leaf_p2m_small<T><<<dim3(g.nleaf / (kLeafThreads / 64), R), kLeafThreads, lds, st>>>(
+            g, reps, x, qA, qB, site, lam, fa, P->ws.dom, P->ws.leaf_start, P->ws.perm, (V4*)P->ws.pos, P->status,
+            (T*)P->ws.mult, P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp, lb);
+        return;
+    }
     // the folded first M2M step is its own instantiation (it needs more
     // registers, which would lower every other launch's occupancy)
     auto leaf = fold ? k_leaf_p2m<T, true> : k_leaf_p2m<T, false>;
@@ -790,15 +807,6 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     }
     return order;
 }
-
-// FP32 near field with a wavefront per leaf (the same sums as the block per
-// leaf with 4 wavefronts): from kSmallLeaves leaves on, which give every SIMD
-// four wavefronts (4,096 leaves of 15: 76 -> 41 us, of 29: 108 -> 90 us; 512
-// leaves of 10: 15 against 25 us), with at most kSmallFill atoms each.  The same
-// with eight slices, for p2p_waves = 8, would gain with 4,096 leaves of 37 and 49
-// atoms (153 -> 123, 199 -> 173 us) and lose with fuller ones (98 atoms: 520
-// against 557 us; 16 systems of 512 leaves of 68: 559 against 667 us).
-constexpr int64_t kSmallLeaves = 4096, kSmallFill = 48;
 
 // Enqueue one evaluation of R replicas (arguments already validated; rd holds
 // the host copy of the replica descriptors).  Every phase is one launch over
@@ -1519,11 +1527,12 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
             }
         }
     }
-    for (int fold = 0; fold < 2 && e == hipSuccess; ++fold) {
-        const void* f = P->fp64 ? (fold ? (const void*)&fmmk::k_leaf_p2m<double, true>
-                                        : (const void*)&fmmk::k_leaf_p2m<double, false>)
-                                : (fold ? (const void*)&fmmk::k_leaf_p2m<float, true>
-                                        : (const void*)&fmmk::k_leaf_p2m<float, false>);
+    const void* leaf_k[2][3] = {{(const void*)&fmmk::k_leaf_p2m<float, false>, (const void*)&fmmk::k_leaf_p2m<float, true>,
+                                 (const void*)&fmmk::k_leaf_p2m_small<float>},
+                                {(const void*)&fmmk::k_leaf_p2m<double, false>, (const void*)&fmmk::k_leaf_p2m<double, true>,
+                                 (const void*)&fmmk::k_leaf_p2m_small<double>}};
+    for (int v = 0; v < 3 && e == hipSuccess; ++v) {
+        const void* f = leaf_k[P->fp64 ? 1 : 0][v];
         e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize,
                                 P->fp64 ? (int)leaf_lds_bytes_max<double>((int)K)
                                         : (int)leaf_lds_bytes_max<float>((int)K));

@@ -167,21 +167,25 @@ __device__ __forceinline__ void for_rho_orders(int p, const RhoLds<T>& rc, int m
     }
 }
 
+__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
+__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
+
 // The same with lanes that differ in m0: every lane walks its own orders side
 // by side (for_rho_orders visits the orders one after the other, each with the
-// lanes of the other orders idle).
+// lanes of the other orders idle).  Multiply-adds are spelled out as the
+// compiler forms them there: the two give equal bits.
 template <typename T, typename Fn>
 __device__ __forceinline__ void for_rho_lane_orders(int p, const RhoLds<T>& rc, int m0, int dm, T x, T y, T z,
                                                     Fn&& fn) {
-    const T r2 = x * x + y * y + z * z;
+    const T r2 = fma_(z, z, fma_(y, y, x * x));
     T cre = T(1), cim = T(0);
     int mc = 0;
     for (int m = m0; m <= p; m += dm) {
         while (mc < m) {
             ++mc;
             const T fm = rc.f[mc];
-            const T nre = fm * (x * cre - y * cim);
-            const T nim = fm * (x * cim + y * cre);
+            const T nre = fm * fma_(x, cre, -(y * cim));
+            const T nim = fm * fma_(y, cre, x * cim);
             cre = nre;
             cim = nim;
         }
@@ -195,8 +199,9 @@ __device__ __forceinline__ void for_rho_lane_orders(int p, const RhoLds<T>& rc, 
         for (int l = m + 2; l <= p; ++l) {
             const T al = rc.a[l * (kPMax + 1) + m];
             const T bl = rc.b[l * (kPMax + 1) + m];
-            const T nre = al * z * p1re - bl * r2 * p0re;
-            const T nim = al * z * p1im - bl * r2 * p0im;
+            const T az = al * z, br = bl * r2;
+            const T nre = fma_(az, p1re, -(br * p0re));
+            const T nim = fma_(az, p1im, -(br * p0im));
             p0re = p1re;
             p0im = p1im;
             p1re = nre;
@@ -861,6 +866,35 @@ __device__ void tri_matvec(const TriPart<TO, kShape>& tp, int K, const TO* __res
     __syncthreads();
 }
 
+// LDS that one wavefront writes and reads back: its own accesses complete in
+// order, the compiler only has to keep them so.
+__device__ __forceinline__ void wave_lds_fence() {
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
+// Interpolated charge of atom i (site st, or none), in FP64.
+template <typename T>
+__device__ __forceinline__ double form_charge(const T* __restrict__ qA, const T* __restrict__ qB,
+                                              const double* __restrict__ lam, const FormArgs<T>& fa, int64_t s0,
+                                              int64_t n_sites, int32_t i, int32_t st) {
+    const double a0 = (double)qA[i], b0 = (double)qB[i];
+    const bool four = fa.qC != nullptr;
+    const double c0 = four ? (double)fa.qC[i] : 0.0, d0 = four ? (double)fa.qD[i] : 0.0;
+    double q = a0;
+    if (st >= 0 && st < n_sites) {
+        if (four) {
+            // four forms (Methods, eq 2): bilinear in (lambda_p, lambda_t)
+            const double lp = lam[st], lt = fa.lam_t[s0 + st];
+            q = (1.0 - lp) * ((1.0 - lt) * a0 + lt * b0) + lp * ((1.0 - lt) * c0 + lt * d0);
+        } else {
+            q += lam[st] * (b0 - a0);
+        }
+    }
+    return q;
+}
+
 // Per leaf, one block of 256 threads: sort the leaf's atoms by caller index
 // (stable binning; leaves of up to 256 atoms by counting ranks, larger ones by
 // a bitonic sort), gather (x - c_leaf, q) into the sorted particle array with
@@ -880,8 +914,8 @@ constexpr int kLeafThreads = 256;
 constexpr int kLeafTriCache = 16;
 constexpr int kLeafIdx = kSortCap / kLeafThreads;  // sorted indices per thread
 template <typename T, bool FOLD>
-__global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
-    Geo g, const RepDesc* __restrict__ reps, const T* __restrict__ x, const T* __restrict__ qA,
+__device__ __forceinline__ void leaf_block(
+    const int leaf, RhoLds<T>& rho, const Geo& g, const RepDesc* __restrict__ reps, const T* __restrict__ x, const T* __restrict__ qA,
     const T* __restrict__ qB, const int32_t* __restrict__ site, const double* __restrict__ lam,
     FormArgs<T> fa, const double* __restrict__ dom_all, int32_t* __restrict__ leaf_start_all,
     int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
@@ -890,7 +924,6 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
     double* __restrict__ m2m_part_all) {
     static_assert(2 * kLeafThreads == kTreeThreads, "two tree-operator shares per leaf thread");
     extern __shared__ __align__(16) unsigned char leaf_lds[];
-    __shared__ RhoLds<T> rho;
     __shared__ double ps[2][kLeafThreads / 64];
     __shared__ int32_t wpre[kLeafThreads / 64], wsite[kLeafThreads / 64];
     int32_t* sbuf = (int32_t*)leaf_lds;
@@ -902,7 +935,6 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
     int32_t* leaf_start = leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1);
     T* mult = mult_all + (size_t)blockIdx.y * g.nbox * g.Kp;
     double* leaf_part = leaf_part_all + (size_t)blockIdx.y * g.nleaf * 2;
-    const int leaf = blockIdx.x;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const bool binned = bins.bucket != nullptr;
     // bucket binning: the site starts are scanned into LDS past the sort / P2M
@@ -1017,7 +1049,7 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
         for (int m = 0; m < kLeafIdx; ++m) idx[m] = 0;
     }
     __syncthreads();  // sorted indices are in registers: the LDS is free for P2M rows
-    if (binned && blockIdx.x == 0 && blockIdx.y == 0)
+    if (binned && leaf == 0 && blockIdx.y == 0)
         for (int i = tid; i <= lb.S_tot; i += kLeafThreads) lb.site_start[i] = lb.S_tot > 0 ? site_st[i] : 0;
     const double h = edge / g.nb;
     const T ih = (T)(1.0 / h);
@@ -1036,25 +1068,13 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
         const double xv[3] = {(double)x[3 * i], (double)x[3 * i + 1], (double)x[3 * i + 2]};
         const int32_t st = site[i];
         if (binned && st >= 0 && st < n_sites) lb.site_members[site_st[rd.s0 + st] + lb.site_rank[i]] = i;
-        const double a0 = (double)qA[i], b0 = (double)qB[i];
-        const bool four = fa.qC != nullptr;
-        const double c0 = four ? (double)fa.qC[i] : 0.0, d0 = four ? (double)fa.qD[i] : 0.0;
         double sv[3];
         for (int d = 0; d < 3; ++d) {
             double v = xv[d];
             if (g.periodic) v -= edge * floor(v / edge);
             sv[d] = v - cc[d];
         }
-        double q = a0;
-        if (st >= 0 && st < n_sites) {
-            if (four) {
-                // four forms (Methods, eq 2): bilinear in (lambda_p, lambda_t)
-                const double lp = lam[st], lt = fa.lam_t[rd.s0 + st];
-                q = (1.0 - lp) * ((1.0 - lt) * a0 + lt * b0) + lp * ((1.0 - lt) * c0 + lt * d0);
-            } else {
-                q += lam[st] * (b0 - a0);
-            }
-        }
+        const double q = form_charge<T>(qA, qB, lam, fa, rd.s0, n_sites, i, st);
         vec4_t<T> o;
         o.x = (T)sv[0];
         o.y = (T)sv[1];
@@ -1149,6 +1169,157 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
             for (int sg = 0; sg < nseg; ++sg) v += pm[sg * g.K + tid];
             m2m_part_all[((size_t)blockIdx.y * g.nleaf + leaf) * g.K + tid] = refl_sign(c, refl_bits(tid)) * v;
         }
+    }
+}
+
+template <typename T, bool FOLD>
+__global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
+    Geo g, const RepDesc* __restrict__ reps, const T* __restrict__ x, const T* __restrict__ qA,
+    const T* __restrict__ qB, const int32_t* __restrict__ site, const double* __restrict__ lam,
+    FormArgs<T> fa, const double* __restrict__ dom_all, int32_t* __restrict__ leaf_start_all,
+    int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
+    T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
+    int split_kp, Bins bins, LeafBinArgs lb, const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
+    double* __restrict__ m2m_part_all) {
+    __shared__ RhoLds<T> rho;
+    leaf_block<T, FOLD>(blockIdx.x, rho, g, reps, x, qA, qB, site, lam, fa, dom_all, leaf_start_all, perm, pos, status,
+                        mult_all, leaf_part_all, msplit_all, split_kp, bins, lb, m2m0, m2m0_seg, m2m_part_all);
+}
+
+// The same for trees of many small leaves: one wavefront per leaf (up to 64
+// atoms; fuller ones by the whole block afterwards), four leaves per block.  A
+// block per leaf is a chain of barriers there with most lanes idle.  Lanes are
+// 16 atoms x 4 order groups; the LDS rows of 16 atoms at a time (together the
+// block form's 64) are summed in its order, coefficient lane, lane + 64, ... per
+// lane.  500,000 atoms at depth 5, order 10: 220 -> 98 us.
+template <typename T>
+__global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m_small(
+    Geo g, const RepDesc* __restrict__ reps, const T* __restrict__ x, const T* __restrict__ qA,
+    const T* __restrict__ qB, const int32_t* __restrict__ site, const double* __restrict__ lam,
+    FormArgs<T> fa, const double* __restrict__ dom_all, int32_t* __restrict__ leaf_start_all,
+    int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
+    T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
+    int split_kp, LeafBinArgs lb) {
+    extern __shared__ __align__(16) unsigned char leaf_lds[];
+    __shared__ RhoLds<T> rho;
+    constexpr int kW = kLeafThreads / 64;
+    const RepDesc rd = reps[blockIdx.y];
+    const int64_t n_sites = rd.S;
+    const T* const unused = nullptr;
+    const double* dom = dom_all + 8 * blockIdx.y;
+    const int32_t* leaf_start = leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1);
+    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    load_rho_lds<T, kLeafThreads>(rho, g.p);
+    const int leaf = __builtin_amdgcn_readfirstlane(blockIdx.x * kW + wave);
+    const int b = __builtin_amdgcn_readfirstlane(leaf_start[leaf]);
+    const int n = __builtin_amdgcn_readfirstlane(leaf_start[leaf + 1]) - b;
+    const bool solo = n <= 64;
+    const double edge = dom[3];
+    const double h = edge / g.nb;
+    const T ih = (T)(1.0 / h);
+    vec4_t<T> mine;
+    mine.x = mine.y = mine.z = mine.w = T(0);
+    if (solo) {
+        // caller order: a lane's place is the number of the leaf's (distinct)
+        // atom indices below its own
+        int32_t i = lane < n ? perm[b + lane] : 0;
+        int r = 0;
+        for (int k = 0; k < n; ++k) r += __builtin_amdgcn_readlane(i, k) < i ? 1 : 0;
+        i = __builtin_amdgcn_ds_permute(4 * (lane < n ? r : lane), i);
+        int cx, cy, cz;
+        unmorton((uint32_t)leaf, cx, cy, cz);
+        const double cc[3] = {dom[0] + (cx + 0.5) * h, dom[1] + (cy + 0.5) * h, dom[2] + (cz + 0.5) * h};
+        double s2 = 0.0, qs = 0.0;
+        if (lane < n) {
+            perm[b + lane] = i;
+            const double xv[3] = {(double)x[3 * (size_t)i], (double)x[3 * (size_t)i + 1], (double)x[3 * (size_t)i + 2]};
+            const int32_t st = site[i];
+            const double q = form_charge<T>(qA, qB, lam + rd.s0, fa, rd.s0, n_sites, i, st);
+            double sv[3];
+            for (int d = 0; d < 3; ++d) {
+                double v = xv[d];
+                if (g.periodic) v -= edge * floor(v / edge);
+                sv[d] = v - cc[d];
+            }
+            mine.x = (T)sv[0];
+            mine.y = (T)sv[1];
+            mine.z = (T)sv[2];
+            mine.w = (T)q;
+            pos[b + lane] = mine;
+            if (g.periodic) {
+                const double off[3] = {(cx + 0.5) * h - 0.5 * edge, (cy + 0.5) * h - 0.5 * edge,
+                                       (cz + 0.5) * h - 0.5 * edge};
+                const double t0 = (double)mine.x + off[0], t1 = (double)mine.y + off[1], t2 = (double)mine.z + off[2];
+                s2 = (double)mine.w * (t0 * t0 + t1 * t1 + t2 * t2) / (edge * edge);
+                qs = (double)mine.w;
+            }
+        }
+        if (g.periodic) {
+            s2 = wave_sum<double>(s2);
+            qs = wave_sum<double>(qs);
+            if (lane == 0) {
+                double* leaf_part = leaf_part_all + (size_t)blockIdx.y * g.nleaf * 2;
+                leaf_part[2 * leaf] = s2;
+                leaf_part[2 * leaf + 1] = qs;
+            }
+        }
+    }
+    __syncthreads();  // rho
+    if (solo) {
+        constexpr int kCols = kKMax / 64;
+        const int S = g.K | 1;  // odd: the rows of 16 atoms start in different banks
+        T* rows = (T*)leaf_lds + wave * 16 * (g.K + 1);
+        T v0[kCols], v1[kCols], v2[kCols], v3[kCols];
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) v0[c] = v1[c] = v2[c] = v3[c] = T(0);
+        for (int c0 = 0; c0 < n; c0 += 16) {
+            const int src = c0 + (lane & 15);  // lanes past the leaf hold zeros
+            const T ax = __shfl(mine.x, src), ay = __shfl(mine.y, src), az = __shfl(mine.z, src),
+                    q = __shfl(mine.w, src);
+            T* row = rows + (lane & 15) * S;
+            for_rho_lane_orders<T>(g.p, rho, lane >> 4, 4, ax * ih, ay * ih, az * ih,
+                                   [&](int kc, bool hs, T re, T im) {
+                                       row[kc] = q * re;
+                                       if (hs) row[kc + 1] = q * im;
+                                   });
+            wave_lds_fence();
+            const int nr = min(16, n - c0);
+#pragma unroll
+            for (int c = 0; c < kCols; ++c) {
+                const int k = lane + 64 * c;
+                if (64 * c < g.K && k < g.K) {
+                    int t = 0;
+                    for (; t + 4 <= nr; t += 4) {
+                        v0[c] += rows[t * S + k];
+                        v1[c] += rows[(t + 1) * S + k];
+                        v2[c] += rows[(t + 2) * S + k];
+                        v3[c] += rows[(t + 3) * S + k];
+                    }
+                    for (; t < nr; ++t) v0[c] += rows[t * S + k];
+                }
+            }
+            wave_lds_fence();
+        }
+        const int64_t gb = g.lev_off[g.depth] + leaf;
+        T* mult = mult_all + ((size_t)blockIdx.y * g.nbox + gb) * g.Kp;
+#pragma unroll
+        for (int c = 0; c < kCols; ++c) {
+            const int k = lane + 64 * c;
+            if (k < g.K) {
+                const T acc = (v0[c] + v1[c]) + (v2[c] + v3[c]);
+                mult[k] = acc;
+                if constexpr (sizeof(T) == 4)
+                    if (msplit_all)
+                        store_split(split_of(msplit_all, g.nbox, split_kp, blockIdx.y), split_kp, g.depth, leaf, k, acc);
+            }
+        }
+    }
+    for (int w = 0; w < kW; ++w) {
+        const int big = blockIdx.x * kW + w;
+        if (leaf_start[big + 1] - leaf_start[big] <= 64) continue;
+        __syncthreads();  // the rows are free
+        leaf_block<T, false>(big, rho, g, reps, x, qA, qB, site, lam, fa, dom_all, leaf_start_all, perm, pos, status,
+                             mult_all, leaf_part_all, msplit_all, split_kp, Bins{}, lb, unused, unused, nullptr);
     }
 }
 
@@ -2103,8 +2274,6 @@ template <> __device__ __forceinline__ double inv_sqrt<double>(double v) {
     const double e = __builtin_fma(-(y * v), y, 1.0);
     return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
 }
-__device__ __forceinline__ float fma_(float a, float b, float c) { return __builtin_fmaf(a, b, c); }
-__device__ __forceinline__ double fma_(double a, double b, double c) { return __builtin_fma(a, b, c); }
 
 
 // Per target leaf (kNW wavefronts, one lane per target): the sources of the 27
@@ -2650,14 +2819,6 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
         esum = wave_sum<double>(esum);
         if (lane == 0) leaf_energy[blockIdx.x] = esum;
     }
-}
-
-// LDS that one wavefront writes and reads back: its own accesses complete in
-// order, the compiler only has to keep them so.
-__device__ __forceinline__ void wave_lds_fence() {
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
 // Trees of many small leaves: one wavefront per leaf, four leaves per block.
