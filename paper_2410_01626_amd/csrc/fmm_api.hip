@@ -84,6 +84,8 @@ struct fmm_plan_s {
     // operator tables (device)
     void *bankT = nullptr, *m2mT = nullptr, *l2lT = nullptr, *gcoef = nullptr;
     void *m2m_seg = nullptr, *l2l_seg = nullptr;  // tree-pass register caches (thread order)
+    void* l2l_cls = nullptr;                      // the leaves' L2L by sign classes ...
+    int32_t* cls = nullptr;                       // ... and the classes' places and counts
     double* lat_seg = nullptr;
     double* latT = nullptr;
     int32_t* gidx = nullptr;
@@ -318,6 +320,33 @@ std::vector<T> pack_tri(const double* A, int K, int shape) {
         const int ke = std::min(std::min(K, (s + 1) * slen), shape == kTriLower ? (l + 1) * (l + 1) : K);
         for (int j = 0; j < kTriCache && kb + j < ke; ++j)
             out[(size_t)j * kTreeThreads + it] = (T)A[(size_t)r * K + kb + j];
+    }
+    return out;
+}
+
+// The leaf step of the downward pass by sign classes: the coefficients k of
+// class w = refl_bits(k), highest first, at places off[w] .. of the vector;
+// entry j of class sum (w, r) at j 8 K + w K + r, of which those of degree >=
+// l(r) count (cnt[w][l]).  Rows padded past the largest class so that reads
+// eight (or kClsCache) at a time stay in the table.
+constexpr int kClsRows = 48;
+template <typename T>
+std::vector<T> pack_classes(const double* A, int K, std::vector<int32_t>& cls) {
+    std::vector<T> out((size_t)kClsRows * 8 * K, T(0));
+    cls.assign(K + 128 + 8, 0);
+    int place = 0;
+    for (int w = 0; w < 8; ++w) {
+        cls[K + 128 + w] = place;
+        int j = 0;
+        for (int k = K - 1; k >= 0; --k) {
+            if (refl_bits_host(k) != w) continue;
+            const int lk = (int)std::floor(std::sqrt((double)k + 0.5));
+            cls[k] = place++;
+            for (int l = 0; l <= lk; ++l) ++cls[K + 16 * w + l];
+            for (int r = 0; r < K && r < (lk + 1) * (lk + 1); ++r)
+                out[((size_t)j * 8 + w) * K + r] = (T)A[(size_t)r * K + k];
+            ++j;
+        }
     }
     return out;
 }
@@ -798,12 +827,14 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
             l_start = g.depth - 2;
         }
         const unsigned nbx = nbox1 * (half ? 2u : 1u) + (order ? 1u : 0u);
-        auto down = half ? k_downward<T, 4> : k_downward<T, 8>;
+        const bool root = g.periodic && !root_ready && l_start == l0;
+        auto down = root ? (half ? k_downward<T, 4, true> : k_downward<T, 8, true>)
+                         : (half ? k_downward<T, 4, false> : k_downward<T, 8, false>);
         down<<<dim3(nbx, R), kTreeThreads, 0, st>>>(
             g, l0, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, mult, (const T*)P->m2mT,
             (const T*)P->m2m_seg, P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l,
-            P->ws.dom, P->ws.leaf_start, order, root_ready ? 1 : 0, fused ? (const T*)P->ws.m2l_part : nullptr,
-            P->ws.nchunk, P->mg.nt_all, l_start);
+            P->ws.dom, P->ws.leaf_start, order, fused ? (const T*)P->ws.m2l_part : nullptr,
+            P->ws.nchunk, P->mg.nt_all, l_start, (const T*)P->l2l_cls, P->cls);
     }
     return order;
 }
@@ -1128,6 +1159,8 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
     const size_t seg = (size_t)fmmk::kTriCache * fmmk::kTreeThreads;
     ok &= dev_alloc(P, &P->m2m_seg, seg * ts);
     ok &= dev_alloc(P, &P->l2l_seg, seg * ts);
+    ok &= dev_alloc(P, &P->l2l_cls, (size_t)kClsRows * 8 * K * ts);
+    ok &= dev_alloc(P, (void**)&P->cls, (K + 128 + 8) * 4);
     ok &= dev_alloc(P, (void**)&P->lat_seg, seg * 8);
     ok &= dev_alloc(P, (void**)&P->gidx, 3 * (size_t)P->Kg * 4 * 4);
     ok &= dev_alloc(P, &P->gcoef, 3 * (size_t)P->Kg * 4 * ts);
@@ -1169,17 +1202,23 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
     {
         auto ls = pack_tri<double>(lat.data(), (int)K, fmmk::kTriFull);
         up(P->lat_seg, ls.data(), ls.size() * 8);
+        std::vector<int32_t> cls;
         if (P->fp64) {
             auto a = pack_tri<double>(m2m.data(), (int)K, fmmk::kTriLower);
             auto c = pack_tri<double>(l2l.data(), (int)K, fmmk::kTriUpper);
             up(P->m2m_seg, a.data(), a.size() * 8);
             up(P->l2l_seg, c.data(), c.size() * 8);
+            auto d = pack_classes<double>(l2l.data(), (int)K, cls);
+            up(P->l2l_cls, d.data(), d.size() * 8);
         } else {
             auto a = pack_tri<float>(m2m.data(), (int)K, fmmk::kTriLower);
             auto c = pack_tri<float>(l2l.data(), (int)K, fmmk::kTriUpper);
             up(P->m2m_seg, a.data(), a.size() * 4);
             up(P->l2l_seg, c.data(), c.size() * 4);
+            auto d = pack_classes<float>(l2l.data(), (int)K, cls);
+            up(P->l2l_cls, d.data(), d.size() * 4);
         }
+        up(P->cls, cls.data(), cls.size() * 4);
     }
     up(P->gidx, gi.data(), gi.size() * 4);
     // matrix-core M2L: mode, tile geometry, offset lists, task list, banks

@@ -813,7 +813,7 @@ struct TriPart {
             ke = min(min(K, (s + 1) * slen), kShape == kTriLower ? (l + 1) * (l + 1) : K);
         }
 #pragma unroll
-        for (int j = 0; j < kCache; ++j) a[j] = packed[j * kTreeThreads + it];
+        for (int j = 0; j < kCache; ++j) a[j] = (packed + j * kTreeThreads)[(unsigned)it];
     }
 };
 
@@ -832,10 +832,11 @@ __device__ __forceinline__ void tri_dot(const TriPart<TO, kShape, kCache>& tp, i
     for (int c = 0; c < NC; ++c) acc[c] = 0.0;
     const int n = tp.ke - tp.kb;
 #pragma unroll
-    for (int j = 0; j < kCache; ++j)
+    for (int j = 0; j < kCache; ++j) {
         if (j < n)
 #pragma unroll
             for (int c = 0; c < NC; ++c) acc[c] += (double)tp.a[j] * xs[c * K + tp.kb + j];
+    }
     for (int k0 = tp.kb + kCache; k0 < tp.ke; k0 += 16) {
         TO a[16];
 #pragma unroll
@@ -1412,13 +1413,43 @@ __device__ __forceinline__ void gather_children_parts(const Geo& g, int64_t box,
     }
 }
 
-// parent[r] = sum_c s_c(r) (A_0 S_c mu_c)[r] from the products in ys.
-__device__ __forceinline__ double combine_octants(const double* ys, int K, int r) {
-    const int b = refl_bits(r);
-    double acc = 0.0;
+// The eight octants' products in one: with G_b[k] = sum_c s_c(b) (S_c mu_c)[k]
+// (the Walsh-Hadamard transform over the octants c, in place over the columns
+// S_c mu_c in xs), the parent is sum_c (S_c A_0 S_c mu_c)[r] = (A_0 G_b(r))[r]:
+// one product per row instead of eight, the column chosen by the row's signs.
+__device__ __forceinline__ void octant_transform(double* xs, int K) {
+    for (int k = threadIdx.x; k < K; k += kTreeThreads) {
+        double v[8];
 #pragma unroll
-    for (int c = 0; c < 8; ++c) acc += refl_sign(c, b) * ys[c * K + r];
-    return acc;
+        for (int c = 0; c < 8; ++c) v[c] = xs[c * K + k];
+#pragma unroll
+        for (int h = 1; h < 8; h <<= 1)
+#pragma unroll
+            for (int c = 0; c < 8; ++c)
+                if (!(c & h)) {
+                    const double a = v[c], b = v[c | h];
+                    v[c] = a + b;
+                    v[c | h] = a - b;
+                }
+#pragma unroll
+        for (int c = 0; c < 8; ++c) xs[c * K + k] = v[c];
+    }
+}
+// part <- the (segment, row) shares of that product, of the children's columns
+// S_c mu_c in xs (complete for all threads on entry)
+template <typename T>
+__device__ __forceinline__ void m2m_dot(const TriPart<T, kTriLower>& tp, int K, const T* __restrict__ op0, double* xs,
+                                        double* part) {
+    octant_transform(xs, K);
+    __syncthreads();
+    tri_dot<T, 1, kTriLower, kTriCache>(tp, K, op0, xs + refl_bits(max(tp.r, 0)) * K, part);
+    __syncthreads();
+}
+__device__ __forceinline__ double tri_row(const double* part, int K, int r) {
+    const int nseg = tri_nseg(K);
+    double v = 0.0;
+    for (int s = 0; s < nseg; ++s) v += part[s * K + r];
+    return v;
 }
 
 // M2M into the boxes of level lev (>= 2, or >= the coarsest interacting level
@@ -1434,7 +1465,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2m(Geo g, int lev, T* __restr
                                                       uint16_t* __restrict__ msplit_all, int split_kp,
                                                       double* __restrict__ root_part_all,
                                                       const double* __restrict__ m2m_part_all) {
-    __shared__ double xs[8 * kKMax], part[8 * kTreeThreads], ps[16];
+    __shared__ double xs[8 * kKMax], part[kTreeThreads], ps[16];
     TriPart<T, kTriLower> tp;
     tp.load(g.K, op0_seg);
     const int rp = blockIdx.y, K = g.K, box = blockIdx.x;
@@ -1450,13 +1481,12 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2m(Geo g, int lev, T* __restr
         gather_children<T>(g, lev + 1, 8 * (int64_t)box, mult, leaf_part_all + (size_t)rp * g.nleaf * 2,
                            box_part, xs, ps);
     __syncthreads();
-    tri_matvec<T, 8, kTriLower>(tp, K, op0, xs, part, xs);
+    m2m_dot<T>(tp, K, op0, xs, part);
     const int64_t gb = g.lev_off[lev] + box;
     for (int r = threadIdx.x; r < K; r += kTreeThreads) {
-        const double v = combine_octants(xs, K, r);
+        const double v = tri_row(part, K, r);
         mult[(size_t)gb * g.Kp + r] = (T)v;
-        // the root share's input S_c mu (octant c = box) over column 0 of xs:
-        // this thread alone reads row r of every column above
+        // the root share's input S_c mu (octant c = box) over column 0 of xs
         if (root_part_all) xs[r] = refl_sign(box, refl_bits(r)) * v;
         if constexpr (sizeof(T) == 4)
             if (msplit_all)
@@ -1635,8 +1665,8 @@ __device__ void periodic_root(const Geo& g, int rp, const T* __restrict__ mult_a
                        leaf_part_all + (size_t)rp * g.nleaf * 2, box_part_all + (size_t)rp * g.nbox * 2,
                        xs, ps);
     __syncthreads();
-    tri_matvec<T, 8, kTriLower>(tm, K, m2m0, xs, part, xs);
-    for (int r = threadIdx.x; r < K; r += kTreeThreads) v[r] = combine_octants(xs, K, r);
+    m2m_dot<T>(tm, K, m2m0, xs, part);
+    for (int r = threadIdx.x; r < K; r += kTreeThreads) v[r] = tri_row(part, K, r);
     __syncthreads();
     for (int k = threadIdx.x; k < K; k += kTreeThreads) xs[k] = v[k];
     __syncthreads();
@@ -1704,6 +1734,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_l2l_level(Geo g, int lev, int 
             (T)((double)own + refl_sign(c, refl_bits(threadIdx.x)) * xs[threadIdx.x]);
 }
 
+constexpr int kClsCache = 16;  // entries of a class sum loaded ahead (p = 8: all 15)
 // Downward pass in one launch: 8 / NC blocks per box b of level depth - 1,
 // each of which forms lambda~ of b and its ancestors from level l0 down (L2L
 // of the parent's total plus the box's own M2L sum, in FP64) and adds the L2L
@@ -1714,9 +1745,11 @@ __global__ __launch_bounds__(kTreeThreads) void k_l2l_level(Geo g, int lev, int 
 // (2 pi / 3) sum q |s/L|^2 e_0 itself (block 0 also stores mu~_0, lambda~_0 and
 // dom[4] = Q).  Ancestors shared by several blocks are recomputed by each;
 // only the leaf expansions are stored.  Open systems start at level l0 from
-// its M2L sum alone.  With root_ready the periodic root was already formed
-// (by the M2L reduction launch) and is read from root_l.
-template <typename T, int NC>
+// its M2L sum alone.  Only kRoot's blocks form the periodic root; otherwise it
+// was formed by an earlier launch and is read from root_l (an instantiation
+// of its own: the root's operators take half the registers).  500,000 atoms at
+// depth 5, p = 10: 154 -> 132 us with the leaves' products by sign classes.
+template <typename T, int NC, bool kRoot>
 __global__ __launch_bounds__(kTreeThreads) void k_downward(
     Geo g, int l0, T* __restrict__ loc_all, const T* __restrict__ l2l0, const T* __restrict__ l2l0_seg,
     const T* __restrict__ mult_all, const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
@@ -1724,8 +1757,11 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
     const double* __restrict__ latT, const double* __restrict__ lat_seg, double* __restrict__ root_m_all,
     double* __restrict__ root_l_all, double* __restrict__ dom_all,
     const int32_t* __restrict__ leaf_start_all, int32_t* __restrict__ leaf_order_all,
-    int root_ready, const T* __restrict__ m2l_part_all, int m2l_nchunk, int64_t m2l_nt_all, int l_start) {
-    __shared__ double xs[8 * kKMax], part[8 * kTreeThreads];
+    const T* __restrict__ m2l_part_all, int m2l_nchunk, int64_t m2l_nt_all, int l_start,
+    const T* __restrict__ l2l_cls, const int32_t* __restrict__ cls) {
+    // part: the class sums, the tree products' shares or the leaf order's keys
+    __shared__ double xs[8 * kKMax], part[8 * kKMax];
+    static_assert(kOrderCap * sizeof(int32_t) <= sizeof(part) && kTreeThreads <= 8 * kKMax, "scratch");
     if (leaf_order_all && blockIdx.x + 1 == gridDim.x) {
         // the extra last block: the near-field order of this replica's leaves
         leaf_work_order(g, leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1),
@@ -1795,18 +1831,27 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
         // expansion (k_l2l_level launches; no offset-chunk partials here)
         __syncthreads();
         for (int k = threadIdx.x; k < K; k += kTreeThreads) v[k] = (double)anc[(l_start - la) * K + k];
-    } else if (g.periodic && root_ready) {
-        // formed by the extra block of the M2L reduction launch, or by the
-        // resident-source M2L launch's extra work-group
-        __syncthreads();
-        for (int k = threadIdx.x; k < K; k += kTreeThreads) v[k] = root_l_all[(size_t)rp * K + k];
     } else if (g.periodic) {
-        periodic_root<T>(g, rp, mult_all, m2m0, m2m0_seg, leaf_part_all, box_part_all, latT, lat_seg,
-                         root_m_all, root_l_all, dom_all, xs, part, v, ps, blockIdx.x == 0);
+        if constexpr (kRoot) {
+            periodic_root<T>(g, rp, mult_all, m2m0, m2m0_seg, leaf_part_all, box_part_all, latT, lat_seg,
+                             root_m_all, root_l_all, dom_all, xs, part, v, ps, blockIdx.x == 0);
+        } else {
+            // formed by the extra block of the M2L reduction launch, or by the
+            // M2L launch's extra work-group
+            __syncthreads();
+            for (int k = threadIdx.x; k < K; k += kTreeThreads) v[k] = root_l_all[(size_t)rp * K + k];
+        }
     } else {
         __syncthreads();
         for (int k = threadIdx.x; k < K; k += kTreeThreads) v[k] = (double)anc[k];
     }
+    // the leaf step's operator entries (this thread's first two class sums)
+    T ca[2][kClsCache];
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+#pragma unroll
+        for (int j = 0; j < kClsCache; ++j)
+            ca[m][j] = (l2l_cls + j * 8 * K)[min(threadIdx.x + m * kTreeThreads, 8u * K - 1)];
     __syncthreads();
     for (int lev = l_start + 1; lev < D; ++lev) {
         const int a = b >> (3 * (D - 1 - lev)), c = a & 7;
@@ -1817,19 +1862,49 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
             v[r] = (double)anc[(lev - la) * K + r] + refl_sign(c, refl_bits(r)) * xs[r];
         __syncthreads();
     }
-    for (int i = threadIdx.x; i < NC * K; i += kTreeThreads) {
-        const int c = i / K, k = i - c * K;
-        xs[i] = refl_sign(c0 + c, refl_bits(k)) * v[k];
-    }
+    // the leaves' L2L, S_c A_0 S_c v for all octants c at once: the coefficients
+    // k fall into eight classes w of equal signs s_c(k) = s_c(w), so with the
+    // class sums P_w[r] = sum_{k in w} A_0[r][k] v[k] leaf c's row r is
+    // s_c(r) sum_w s_c(w) P_w[r] (an eighth of the products)
+    for (int k = threadIdx.x; k < K; k += kTreeThreads) xs[cls[k]] = v[k];
     __syncthreads();
-    tri_matvec<T, NC, kTriUpper>(tp, K, l2l0, xs, part, xs);
+    auto class_sum = [&](int it, const T(&c)[kClsCache], bool ahead) {
+        const int w = it / K, r = it - w * K, l = (int)sqrtf((float)r + 0.5f);
+        const int n = cls[K + 16 * w + l];
+        const double* x = xs + cls[K + 128 + w];
+        double acc = 0.0;
+        if (ahead) {
+#pragma unroll
+            for (int j = 0; j < kClsCache; ++j)
+                if (j < n) acc += (double)c[j] * x[j];
+        }
+#pragma unroll 1
+        for (int j0 = ahead ? kClsCache : 0; j0 < n; j0 += 8) {
+            T a[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a[j] = (l2l_cls + (j0 + j) * 8 * K)[(unsigned)it];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j0 + j < n) acc += (double)a[j] * x[j0 + j];
+        }
+        part[it] = acc;
+    };
+#pragma unroll
+    for (int m = 0; m < 2; ++m)
+        if ((int)threadIdx.x + m * kTreeThreads < 8 * K) class_sum(threadIdx.x + m * kTreeThreads, ca[m], true);
+#pragma unroll 1
+    for (int it = threadIdx.x + 2 * kTreeThreads; it < 8 * K; it += kTreeThreads) class_sum(it, ca[0], false);
+    __syncthreads();
 #pragma unroll
     for (int m = 0; m < kGatherPer; ++m) {
         const int i = threadIdx.x + m * kTreeThreads;
         if (i < NC * K) {
             const int c = i / K, r = i - c * K;
             const T own = m2l_part_all ? lsum[i] : lv[m];
-            dst[(size_t)c * g.Kp + r] = (T)((double)own + refl_sign(c0 + c, refl_bits(r)) * xs[i]);
+            double sum = 0.0;
+#pragma unroll
+            for (int w = 0; w < 8; ++w) sum += refl_sign(c0 + c, w) * part[w * K + r];
+            dst[(size_t)c * g.Kp + r] = (T)((double)own + refl_sign(c0 + c, refl_bits(r)) * sum);
         }
     }
 }
@@ -2214,7 +2289,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2l_reduce(
     int quad) {
     const int nred = (int)gridDim.x - (root_block ? 1 : 0);
     if ((int)blockIdx.x >= nred) {
-        __shared__ double xs[8 * kKMax], tp[8 * kTreeThreads], v[kKMax], ps[16];
+        __shared__ double xs[8 * kKMax], tp[kTreeThreads], v[kKMax], ps[16];
         if (root_part_all)
             periodic_root_from_shares(g, blockIdx.y, root_part_all, box_part_all, latT, lat_seg, root_m_all,
                                       root_l_all, dom_all, xs, tp, v);
