@@ -568,6 +568,14 @@ void launch_m2l_bf(fmm_plan_t P, const Geo& g, const fmmk::M2LGeom& mg, dim3 nt,
                                                  (const uint4*)P->zrow, loc, part);
 }
 
+// From 256 boxes above the leaves (over all replicas) on, the downward pass is a
+// matter of throughput: the M2L sums formed once by the reduction launch and
+// k_l2l_leaves, against k_downward with its inline sums and ancestor chains (16
+// systems of 512 leaves: 62 -> 38 us, 4 such: 34 -> 24 us in FP32, 25 -> 20 us
+// bf16x3 open; one such: 13 against 21 us).
+constexpr int64_t kManyBoxes = 256;
+bool many_boxes(const fmmk::Geo& g, int R) { return g.depth >= 1 && ((int64_t)R << (3 * (g.depth - 1))) >= kManyBoxes; }
+
 // Matrix-core M2L launch: the kernel instance for the plan's precision and row
 // tile count, then the fixed-order chunk reduction.  Returns whether the
 // periodic root was formed (by the reduction launch or, with resident sources,
@@ -595,7 +603,8 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
     // times.
     const int64_t down_blocks = g.depth < 1 ? 0 : (int64_t)R * (g.depth <= 3 ? 2 : 1) << (3 * (g.depth - 1));
     const bool sum_down = (P->m2l_mode == 3 ? P->m2l_rs : g.depth <= 3 && down_blocks >= 96) && nchunk > 1 &&
-                          (!g.periodic || (want_root && g.depth >= 2)) && g.depth - 1 >= (g.periodic ? 0 : g.lmin);
+                          (!g.periodic || (want_root && g.depth >= 2)) && g.depth - 1 >= (g.periodic ? 0 : g.lmin) &&
+                          !many_boxes(g, R);
     if (P->m2l_mode != 3) {
         // one chunk where the workspace holds no partials (static scratch)
         const bool own = nchunk == mg.nchunk;
@@ -642,7 +651,8 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
         M2LGeom mg = P->mg;
         mg.nchunk = nchunk;
         // four threads per entry while that is at most a block or two per CU
-        const int quad = tot <= 512 * kReduceEntries;
+        // over all replicas (16 systems of 584 boxes: 37 us, one thread each 15)
+        const int quad = R * tot <= 512 * kReduceEntries;
         const unsigned nb = quad ? (unsigned)((tot + kReduceEntries - 1) / kReduceEntries)
                                  : (unsigned)std::min<int64_t>(4096, (tot + 255) / 256);
         // periodic trees with a downward pass: the extra block forms the root
@@ -815,26 +825,30 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
         // order block without one)
         const unsigned nbox1 = 1u << (3 * (g.depth - 1));
         const bool half = nbox1 <= 64;
-        // deep trees whose M2L sums are all in loc and whose root is formed:
-        // the levels from l0 + 1 to d - 2 one launch each (every box once),
-        // the downward launch from there (its blocks would otherwise each
-        // redo the whole ancestor chain)
-        int l_start = l0;
-        if (!fused && (root_ready || !g.periodic) && g.depth - 1 - l0 >= 4) {
-            for (int lev = l0 + 1; lev <= g.depth - 2; ++lev)
-                k_l2l_level<T><<<dim3(1u << (3 * lev), R), kTreeThreads, 0, st>>>(
-                    g, lev, l0, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, P->ws.root_l);
-            l_start = g.depth - 2;
+        if (!fused && (root_ready || !g.periodic) && many_boxes(g, R)) {
+            // deep trees: the levels from l0 + 1 to d - 2 one launch each (every
+            // box once), the leaves' launch from there (its blocks would
+            // otherwise each redo the whole ancestor chain)
+            int l_start = l0;
+            if (g.depth - 1 - l0 >= 4) {
+                for (int lev = l0 + 1; lev <= g.depth - 2; ++lev)
+                    k_l2l_level<T><<<dim3(1u << (3 * lev), R), kTreeThreads, 0, st>>>(
+                        g, lev, l0, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, P->ws.root_l);
+                l_start = g.depth - 2;
+            }
+            k_l2l_leaves<T><<<dim3(nbox1 + (order ? 1u : 0u), R), kTreeThreads, 0, st>>>(
+                g, l_start, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, P->ws.root_l, (const T*)P->l2l_cls, P->cls, P->ws.leaf_start, order);
+            return order;
         }
         const unsigned nbx = nbox1 * (half ? 2u : 1u) + (order ? 1u : 0u);
-        const bool root = g.periodic && !root_ready && l_start == l0;
+        const bool root = g.periodic && !root_ready;
         auto down = root ? (half ? k_downward<T, 4, true> : k_downward<T, 8, true>)
                          : (half ? k_downward<T, 4, false> : k_downward<T, 8, false>);
         down<<<dim3(nbx, R), kTreeThreads, 0, st>>>(
             g, l0, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, mult, (const T*)P->m2mT,
             (const T*)P->m2m_seg, P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l,
             P->ws.dom, P->ws.leaf_start, order, fused ? (const T*)P->ws.m2l_part : nullptr,
-            P->ws.nchunk, P->mg.nt_all, l_start, (const T*)P->l2l_cls, P->cls);
+            P->ws.nchunk, P->mg.nt_all, (const T*)P->l2l_cls, P->cls);
     }
     return order;
 }

@@ -1519,9 +1519,11 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2m(Geo g, int lev, T* __restr
 // CUs as described below), and each XCD
 // reads one octant's neighbourhoods through its own L2; otherwise all leaves
 // go largest first.  Key: octant, count (capped at 2^16 - 1), leaf index
-// (ties: lower leaf first); needs nleaf <= kOrderCap.
+// (ties: lower leaf first).  Trees of more than kOrderCap leaves go unordered: their
+// tail is short and sorting 4,096 leaves in one block held the near field up by
+// 75 us (near field of 15 to 49 atoms a leaf: 43, 201 us ordered, 45, 204 not).
 // buf: kOrderCap ints of LDS.
-constexpr int kOrderCap = 4096;
+constexpr int kOrderCap = 512;
 __device__ void leaf_work_order(const Geo& g, const int32_t* __restrict__ leaf_start,
                                 int32_t* __restrict__ order, int32_t* key) {
     const int nl = g.nleaf;
@@ -1735,6 +1737,141 @@ __global__ __launch_bounds__(kTreeThreads) void k_l2l_level(Geo g, int lev, int 
 }
 
 constexpr int kClsCache = 16;  // entries of a class sum loaded ahead (p = 8: all 15)
+// A thread's first two class sums: operator entries, lengths, places in the
+// class-ordered vector, and the place of coefficient threadIdx.x in it.
+template <typename T>
+struct ClassShare {
+    T a[2][kClsCache];
+    int n[2], x[2], place;
+    __device__ __forceinline__ static void share(const int32_t* __restrict__ cls, int K, int it, int& n, int& x) {
+        const int w = it / K, l = (int)sqrtf((float)(it - w * K) + 0.5f);
+        n = cls[K + 16 * w + l];
+        x = cls[K + 128 + w];
+    }
+    __device__ __forceinline__ void load(const T* __restrict__ l2l_cls, const int32_t* __restrict__ cls, int K) {
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            const unsigned it = min(threadIdx.x + m * kTreeThreads, 8u * K - 1);
+#pragma unroll
+            for (int j = 0; j < kClsCache; ++j) a[m][j] = (l2l_cls + j * 8 * K)[it];
+            share(cls, K, it, n[m], x[m]);
+        }
+        place = cls[min((int)threadIdx.x, K - 1)];
+    }
+};
+// L2L into octant c is S_c A_0 S_c v, for all octants at once: the coefficients
+// k fall into eight classes w of equal signs s_c(k) = s_c(w), so with the class
+// sums P_w[r] = sum_{k in w} A_0[r][k] v[k] row r of octant c is
+// s_c(r) sum_w s_c(w) P_w[r] (an eighth of the products of eight octants).
+// part[w K + r] = P_w[r], v in class order in xs (kTreeThreads threads)
+template <typename T>
+__device__ __forceinline__ void class_sums(const ClassShare<T>& cs, const T* __restrict__ l2l_cls,
+                                           const int32_t* __restrict__ cls, int K, const double* xs, double* part) {
+    auto rest = [&](int it, int j0, int n, const double* x, double acc) {
+#pragma unroll 1
+        for (; j0 < n; j0 += 8) {
+            T a[8];
+#pragma unroll
+            for (int j = 0; j < 8; ++j) a[j] = (l2l_cls + (j0 + j) * 8 * K)[(unsigned)it];
+#pragma unroll
+            for (int j = 0; j < 8; ++j)
+                if (j0 + j < n) acc += (double)a[j] * x[j0 + j];
+        }
+        part[it] = acc;
+    };
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        const int it = threadIdx.x + m * kTreeThreads;
+        if (it < 8 * K) {
+            const double* x = xs + cs.x[m];
+            double acc = 0.0;
+            // reads without a branch each, so that they are in flight together
+            // (past the class they meet entries of 0)
+#pragma unroll
+            for (int j = 0; j < kClsCache; ++j) {
+                const double xv = x[j];
+                acc += (double)cs.a[m][j] * (j < cs.n[m] ? xv : 0.0);
+            }
+            rest(it, kClsCache, cs.n[m], x, acc);
+        }
+    }
+#pragma unroll 1
+    for (int it = threadIdx.x + 2 * kTreeThreads; it < 8 * K; it += kTreeThreads) {
+        int n, x;
+        cs.share(cls, K, it, n, x);
+        rest(it, 0, n, xs + x, 0.0);
+    }
+}
+// row r of octant c: s_c(r) sum_w s_c(w) P_w[r]
+__device__ __forceinline__ double class_row(const double* part, int K, int c, int r) {
+    double sum = 0.0;
+#pragma unroll
+    for (int w = 0; w < 8; ++w) sum += refl_sign(c, w) * part[w * K + r];
+    return refl_sign(c, refl_bits(r)) * sum;
+}
+
+// The downward pass of many boxes (throughput rather than latency): as
+// k_downward below from an expansion that level l_start already holds (the root
+// formed, all M2L sums in loc), one block per box of level depth - 1; two
+// blocks fit a CU where k_downward leaves room for one.  Same sums as there, bit
+// for bit (class sums for the ancestors too would save registers here, 75 -> 62
+// us, but cost k_downward's latency: 12.7 -> 15 us at 64 boxes).  4,096 boxes at
+// p = 10 (500,000 atoms, depth 5): 132 -> 75 us.
+template <typename T>
+__global__ __launch_bounds__(kTreeThreads, 4) void k_l2l_leaves(
+    Geo g, int l_start, T* __restrict__ loc_all, const T* __restrict__ l2l0, const T* __restrict__ l2l0_seg, const double* __restrict__ root_l_all,
+    const T* __restrict__ l2l_cls, const int32_t* __restrict__ cls,
+    const int32_t* __restrict__ leaf_start_all, int32_t* __restrict__ leaf_order_all) {
+    __shared__ double xs[kKMax + kClsCache], part[8 * kKMax];
+    if (leaf_order_all && blockIdx.x + 1 == gridDim.x) {
+        leaf_work_order(g, leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1),
+                        leaf_order_all + (size_t)blockIdx.y * g.nleaf, (int32_t*)part);
+        return;
+    }
+    const int rp = blockIdx.y, K = g.K, D = g.depth, b = blockIdx.x, r = threadIdx.x;
+    T* loc = loc_all + (size_t)rp * g.nbox * g.Kp;
+    double v = 0.0;  // coefficient r of the current box (threads below K)
+    if (r < K)
+        v = g.periodic && l_start == 0
+                ? root_l_all[(size_t)rp * K + r]
+                : (double)loc[(size_t)(lev_offset(l_start) + (b >> (3 * (D - 1 - l_start)))) * g.Kp + r];
+    if (l_start + 1 < D) {
+        // the box's ancestors by k_downward's products, in its order
+        TriPart<T, kTriUpper> tp;
+        tp.load(K, l2l0_seg);
+        for (int lev = l_start + 1; lev < D; ++lev) {
+            const int a = b >> (3 * (D - 1 - lev)), c = a & 7;
+            const T own = r < K ? loc[(size_t)(lev_offset(lev) + a) * g.Kp + r] : T(0);
+            if (r < K) xs[r] = refl_sign(c, refl_bits(r)) * v;
+            __syncthreads();
+            tri_matvec<T, 1, kTriUpper>(tp, K, l2l0, xs, part, xs);
+            if (r < K) v = (double)own + refl_sign(c, refl_bits(r)) * xs[r];
+            __syncthreads();
+        }
+    }
+    ClassShare<T> cs;
+    cs.load(l2l_cls, cls, K);
+    T* dst = loc + (size_t)(lev_offset(D) + 8 * (size_t)b) * g.Kp;
+    T lv[kGatherPer];
+#pragma unroll
+    for (int m = 0; m < kGatherPer; ++m) {
+        const int i = min((int)threadIdx.x + m * kTreeThreads, 8 * K - 1), c = i / K;
+        lv[m] = dst[(size_t)c * g.Kp + i - c * K];
+    }
+    if (r < K) xs[cs.place] = v;
+    __syncthreads();
+    class_sums<T>(cs, l2l_cls, cls, K, xs, part);
+    __syncthreads();
+#pragma unroll
+    for (int m = 0; m < kGatherPer; ++m) {
+        const int i = threadIdx.x + m * kTreeThreads;
+        if (i < 8 * K) {
+            const int c = i / K, k = i - c * K;
+            dst[(size_t)c * g.Kp + k] = (T)((double)lv[m] + class_row(part, K, c, k));
+        }
+    }
+}
+
 // Downward pass in one launch: 8 / NC blocks per box b of level depth - 1,
 // each of which forms lambda~ of b and its ancestors from level l0 down (L2L
 // of the parent's total plus the box's own M2L sum, in FP64) and adds the L2L
@@ -1757,7 +1894,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
     const double* __restrict__ latT, const double* __restrict__ lat_seg, double* __restrict__ root_m_all,
     double* __restrict__ root_l_all, double* __restrict__ dom_all,
     const int32_t* __restrict__ leaf_start_all, int32_t* __restrict__ leaf_order_all,
-    const T* __restrict__ m2l_part_all, int m2l_nchunk, int64_t m2l_nt_all, int l_start,
+    const T* __restrict__ m2l_part_all, int m2l_nchunk, int64_t m2l_nt_all,
     const T* __restrict__ l2l_cls, const int32_t* __restrict__ cls) {
     // part: the class sums, the tree products' shares or the leaf order's keys
     __shared__ double xs[8 * kKMax], part[8 * kKMax];
@@ -1826,12 +1963,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
             else lsum[i - nanc] = sv;
         }
     }
-    if (l_start > l0) {
-        // the ancestor at level l_start already holds its whole local
-        // expansion (k_l2l_level launches; no offset-chunk partials here)
-        __syncthreads();
-        for (int k = threadIdx.x; k < K; k += kTreeThreads) v[k] = (double)anc[(l_start - la) * K + k];
-    } else if (g.periodic) {
+    if (g.periodic) {
         if constexpr (kRoot) {
             periodic_root<T>(g, rp, mult_all, m2m0, m2m0_seg, leaf_part_all, box_part_all, latT, lat_seg,
                              root_m_all, root_l_all, dom_all, xs, part, v, ps, blockIdx.x == 0);
@@ -1845,16 +1977,12 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
         __syncthreads();
         for (int k = threadIdx.x; k < K; k += kTreeThreads) v[k] = (double)anc[k];
     }
-    // the leaf step's operator entries (this thread's first two class sums)
-    T ca[2][kClsCache];
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-#pragma unroll
-        for (int j = 0; j < kClsCache; ++j)
-            ca[m][j] = (l2l_cls + j * 8 * K)[min(threadIdx.x + m * kTreeThreads, 8u * K - 1)];
+    // the leaf step's operator entries, in flight during the ancestors' steps
+    ClassShare<T> cs;
+    cs.load(l2l_cls, cls, K);
     __syncthreads();
-    for (int lev = l_start + 1; lev < D; ++lev) {
-        const int a = b >> (3 * (D - 1 - lev)), c = a & 7;
+    for (int lev = l0 + 1; lev < D; ++lev) {
+        const int c = (b >> (3 * (D - 1 - lev))) & 7;
         for (int k = threadIdx.x; k < K; k += kTreeThreads) xs[k] = refl_sign(c, refl_bits(k)) * v[k];
         __syncthreads();
         tri_matvec<T, 1, kTriUpper>(tp, K, l2l0, xs, part, xs);
@@ -1862,38 +1990,9 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
             v[r] = (double)anc[(lev - la) * K + r] + refl_sign(c, refl_bits(r)) * xs[r];
         __syncthreads();
     }
-    // the leaves' L2L, S_c A_0 S_c v for all octants c at once: the coefficients
-    // k fall into eight classes w of equal signs s_c(k) = s_c(w), so with the
-    // class sums P_w[r] = sum_{k in w} A_0[r][k] v[k] leaf c's row r is
-    // s_c(r) sum_w s_c(w) P_w[r] (an eighth of the products)
-    for (int k = threadIdx.x; k < K; k += kTreeThreads) xs[cls[k]] = v[k];
+    if ((int)threadIdx.x < K) xs[cs.place] = v[threadIdx.x];
     __syncthreads();
-    auto class_sum = [&](int it, const T(&c)[kClsCache], bool ahead) {
-        const int w = it / K, r = it - w * K, l = (int)sqrtf((float)r + 0.5f);
-        const int n = cls[K + 16 * w + l];
-        const double* x = xs + cls[K + 128 + w];
-        double acc = 0.0;
-        if (ahead) {
-#pragma unroll
-            for (int j = 0; j < kClsCache; ++j)
-                if (j < n) acc += (double)c[j] * x[j];
-        }
-#pragma unroll 1
-        for (int j0 = ahead ? kClsCache : 0; j0 < n; j0 += 8) {
-            T a[8];
-#pragma unroll
-            for (int j = 0; j < 8; ++j) a[j] = (l2l_cls + (j0 + j) * 8 * K)[(unsigned)it];
-#pragma unroll
-            for (int j = 0; j < 8; ++j)
-                if (j0 + j < n) acc += (double)a[j] * x[j0 + j];
-        }
-        part[it] = acc;
-    };
-#pragma unroll
-    for (int m = 0; m < 2; ++m)
-        if ((int)threadIdx.x + m * kTreeThreads < 8 * K) class_sum(threadIdx.x + m * kTreeThreads, ca[m], true);
-#pragma unroll 1
-    for (int it = threadIdx.x + 2 * kTreeThreads; it < 8 * K; it += kTreeThreads) class_sum(it, ca[0], false);
+    class_sums<T>(cs, l2l_cls, cls, K, xs, part);
     __syncthreads();
 #pragma unroll
     for (int m = 0; m < kGatherPer; ++m) {
@@ -1901,10 +2000,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
         if (i < NC * K) {
             const int c = i / K, r = i - c * K;
             const T own = m2l_part_all ? lsum[i] : lv[m];
-            double sum = 0.0;
-#pragma unroll
-            for (int w = 0; w < 8; ++w) sum += refl_sign(c0 + c, w) * part[w * K + r];
-            dst[(size_t)c * g.Kp + r] = (T)((double)own + refl_sign(c0 + c, refl_bits(r)) * sum);
+            dst[(size_t)c * g.Kp + r] = (T)((double)own + class_row(part, K, c0 + c, r));
         }
     }
 }
