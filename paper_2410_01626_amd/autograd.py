@@ -14,26 +14,35 @@ tree pass (charges and, as second sources, charges gphi with dipoles -q gF).
 """
 from __future__ import annotations
 
+import contextlib
+
 import torch
 
 
-def _order_streams(plan, device, weights):
-    """A plan on another stream than autograd's reads the upstream weights (and
-    takes the memory of its outputs) after the work queued here so far."""
+@contextlib.contextmanager
+def _on_plan_stream(plan, device):
+    """A plan on another stream than autograd's: its kernels run after the work
+    queued here so far (their inputs, the memory of their outputs) and the work
+    queued here afterwards runs after them (readers of the outputs, whoever is
+    given the memory of a tensor freed here next).  Waits between the streams,
+    none on the host; under capture the plan's stream joins and leaves."""
     here = torch.cuda.current_stream(device)
     if here.cuda_stream == plan.stream.cuda_stream:
+        yield
         return
     there = torch.cuda.ExternalStream(plan.stream.cuda_stream, device=device)
     there.wait_stream(here)
-    for t in weights:
-        if t is not None:
-            t.record_stream(there)
+    try:
+        yield
+    finally:
+        here.wait_stream(there)
 
 
 class FmmCoulomb(torch.autograd.Function):
     @staticmethod
     def forward(ctx, x, qA, qB, lam, plan, site, box):
-        out = plan.eval(x, qA, qB, site, lam, box=box)
+        with _on_plan_stream(plan, x.device):
+            out = plan.eval(x, qA, qB, site, lam, box=box)
         ctx.save_for_backward(x, qA, qB, lam, site)
         ctx.plan = plan
         ctx.box = box
@@ -53,11 +62,11 @@ class FmmCoulomb(torch.autograd.Function):
         gF = None if gF is None else gF.to(x.dtype).contiguous()
         if w is None and gphi is None and gF is None:
             w = torch.zeros(1, dtype=torch.float64, device=x.device)
-        _order_streams(ctx.plan, x.device, (w, gphi, gF))
-        if gphi is not None or gF is not None:
-            adj = ctx.plan.eval_adjoint_full(x, qA, qB, site, lam, gE=w, gphi=gphi, gF=gF, box=ctx.box)
-        else:
-            adj = ctx.plan.eval_adjoint(x, qA, qB, site, lam, w, box=ctx.box)
+        with _on_plan_stream(ctx.plan, x.device):
+            if gphi is not None or gF is not None:
+                adj = ctx.plan.eval_adjoint_full(x, qA, qB, site, lam, gE=w, gphi=gphi, gF=gF, box=ctx.box)
+            else:
+                adj = ctx.plan.eval_adjoint(x, qA, qB, site, lam, w, box=ctx.box)
         return (adj["grad_x"] if ctx.needs_input_grad[0] else None,
                 adj["grad_qA"] if ctx.needs_input_grad[1] else None,
                 adj["grad_qB"] if ctx.needs_input_grad[2] else None,

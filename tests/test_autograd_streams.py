@@ -1,0 +1,99 @@
+"""Streams of the autograd wrapper: a plan on a stream of its own runs after
+the work queued on autograd's stream, and what autograd's stream does next runs
+after the plan's kernels, in forward and in backward."""
+import numpy as np
+import pytest
+
+from paper_2410_01626_amd import workloads as W
+
+
+class _Stream:
+    """A stream that only writes down who waits for whom."""
+
+    def __init__(self, handle, log):
+        self.cuda_stream, self.log = handle, log
+
+    def wait_stream(self, other):
+        self.log.append("%d waits for %d" % (self.cuda_stream, other.cuda_stream))
+
+
+@pytest.mark.parametrize("own", [True, False])
+@pytest.mark.parametrize("used", ["E", "F"])
+def test_plan_stream_is_ordered_both_ways(monkeypatch, used, own):
+    import torch
+    from paper_2410_01626_amd.autograd import fmm_coulomb
+    log = []
+    here = _Stream(1, log)
+    monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: here)
+    monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device=None: _Stream(handle, log))
+    monkeypatch.setattr(torch.Tensor, "record_stream", lambda self, s: None)
+
+    class _Plan:
+        stream = _Stream(2 if own else 1, log)
+
+        def _run(self, name, x, lam):
+            log.append(name)
+            n, S = x.shape[0], lam.numel()
+            out = {k: torch.zeros(s, dtype=torch.float64) for k, s in
+                   (("E", 1), ("F", (n, 3)), ("phi", n), ("dVdl", S), ("grad_x", (n, 3)), ("grad_qA", n),
+                    ("grad_qB", n), ("grad_lambda", S))}
+            return out
+
+        def eval(self, x, qA, qB, site, lam, box=None):
+            return self._run("eval", x, lam)
+
+        def eval_adjoint(self, x, qA, qB, site, lam, gE, box=None):
+            return self._run("adjoint", x, lam)
+
+        def eval_adjoint_full(self, x, qA, qB, site, lam, gE=None, gphi=None, gF=None, box=None):
+            return self._run("adjoint", x, lam)
+
+    x = torch.zeros((4, 3), dtype=torch.float64, requires_grad=True)
+    q = torch.zeros(4, dtype=torch.float64, requires_grad=True)
+    lam = torch.zeros(2, dtype=torch.float64)
+    E, F, _, _ = fmm_coulomb(_Plan(), x, q, q, torch.zeros(4, dtype=torch.int32), lam)
+    torch.autograd.grad((E if used == "E" else F).sum(), [x, q])
+    order = [["2 waits for 1", k, "1 waits for 2"] if own else [k] for k in ("eval", "adjoint")]
+    assert log == order[0] + order[1]
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("used", ["E", "E+F"])
+def test_own_stream_without_device_waits(used):
+    """Forward, loss, backward and a reader of the gradients one after the
+    other on the caller's stream, which is kept busy before each, and the
+    memory of what is dropped given out again: the values of a plan on that
+    stream."""
+    import torch
+    from paper_2410_01626_amd import fmm
+    from paper_2410_01626_amd.autograd import fmm_coulomb
+    dev = torch.device("cuda:0")
+    d = W.tiny_periodic(98, n=400, edge=1.5, n_sites=3, depth=2, order=6)
+    rng = np.random.default_rng(6)
+    wF = torch.tensor(rng.standard_normal((400, 3)), device=dev)
+    site = torch.tensor(d["site"], device=dev)
+    busy = torch.zeros(1 << 24, device=dev)
+
+    def steps(stream):
+        plan = fmm.Plan(2, 6, periodic=True, precision="fp64", max_atoms=400, max_sites=3, device=dev,
+                        stream=stream)
+        got = []
+        for s in range(4):
+            for _ in range(8):
+                busy.add_(1.0)
+            x, qA, qB, lam = (torch.tensor(d[k], device=dev).mul_(1.0 + 0.01 * s).requires_grad_(True)
+                              for k in ("x", "qA", "qB", "lam"))
+            E, F, phi, _ = fmm_coulomb(plan, x, qA, qB, site, lam, d["box"])
+            loss = 0.5 * E.sum() + ((wF * F).sum() if used == "E+F" else 0.0)
+            g = torch.autograd.grad(loss, [x, qA, qB, lam])
+            got.append([t.clone() for t in (E, F, phi, *g)])
+            del E, F, phi, loss, g, x, qA, qB, lam
+            junk = [torch.full(s, 7.0, dtype=torch.float64, device=dev) for s in ((400, 3), (400,), (3,), (1,)) * 3]
+            del junk
+        torch.cuda.synchronize()
+        plan.close()
+        return [[t.detach().cpu().numpy() for t in ts] for ts in got]
+
+    for a, b in zip(steps(torch.cuda.Stream(dev)), steps(None)):
+        for u, v in zip(a, b):
+            np.testing.assert_array_equal(u, v)
