@@ -568,6 +568,8 @@ void launch_m2l_bf(fmm_plan_t P, const Geo& g, const fmmk::M2LGeom& mg, dim3 nt,
                                                  (const uint4*)P->zrow, loc, part);
 }
 
+constexpr int64_t kMaxGridY = 32768;  // blocks in y of an FP32 / FP64 M2L launch (the device takes 65,536)
+
 // From 256 boxes above the leaves (over all replicas) on, the downward pass is a
 // matter of throughput: the M2L sums formed once by the reduction launch and
 // k_l2l_leaves, against k_downward with its inline sums and ancestor chains (16
@@ -616,7 +618,9 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
         const bool root = sum_down && want_root;
         const RootArgs ra{P->ws.root_part, P->ws.box_part, P->latT, P->lat_seg,
                           P->ws.root_m, root ? P->ws.root_l : nullptr, P->ws.dom};
-        const dim3 grid(nx + (root ? 1u : 0u), (unsigned)((groups + ml.groups - 1) / ml.groups));
+        // column tiles in y, in even rows over z past half of what y may have
+        const int64_t tiles = (groups + ml.groups - 1) / ml.groups, nz = (tiles + kMaxGridY - 1) / kMaxGridY;
+        const dim3 grid(nx + (root ? 1u : 0u), (unsigned)((tiles + nz - 1) / nz), (unsigned)nz);
         const int threads = 64 * ml.groups * (P->mma.rtb / ml.rtw);
         for_order(g.p, [&](auto pc) {
             constexpr int PV = decltype(pc)::value;

@@ -130,7 +130,8 @@ __device__ __forceinline__ void transpose_rows(float (&r)[4]) {
 }
 
 // One work-group: one task (row part, chunk of offsets; FP32: one class) and
-// one tile of up to kGroups 16-column groups (blockIdx.y).  Wavefront w
+// one tile of up to kGroups 16-column groups (grid y, and z past the 65,536
+// blocks that y may have: 15 FP64 systems at depth 6 make 70,217 tiles).  Wavefront w
 // takes column group w / NRG and row tiles RTW (w % NRG) ...
 // olist entries: operator slot << 16 | canonical offset index.  masks[cls][kq]:
 // the reflection signs of class cls as bits: [0] bit i for the lane's i-th
@@ -146,11 +147,12 @@ __global__ __launch_bounds__((64 * MmaDims<T, P>::kGroups * (MmaDims<T, P>::RTB 
     constexpr int E = 16 / (int)sizeof(T);  // elements of a 16-byte piece
     // two distinct objects: the copy into one provably leaves the other alone
     __shared__ uint4 op0[D::a_chunks], op1[D::a_chunks];
+    const int tile = (int)(blockIdx.z * gridDim.y + blockIdx.y);
     if (ra.root_l && blockIdx.x + 1 == gridDim.x) {
         // the extra last work-groups of a periodic tree form the root's local
         // expansion from the level-1 shares (each of them some replicas')
         __shared__ double rt[2 * D::K + kTreeThreads];
-        for (int r = blockIdx.y; r < ma.R; r += gridDim.y) {
+        for (int r = tile; r < ma.R; r += gridDim.y * gridDim.z) {
             periodic_root_wg<16>(g, r, ra.root_part, ra.box_part, ra.latT, ra.lat_seg, ra.root_m, ra.root_l, ra.dom,
                                  rt, rt + 2 * D::K, rt + D::K, blockDim.x);
             __syncthreads();
@@ -172,7 +174,7 @@ __global__ __launch_bounds__((64 * MmaDims<T, P>::kGroups * (MmaDims<T, P>::RTB 
     int ol_reg = ol[min(o0 + lane, 188)];
     if (o0 < o1) issue(__builtin_amdgcn_readlane(ol_reg, 0) >> 16, op0);
     // this lane's column: replica, class, level and box
-    const int u = ((int)blockIdx.y * cgs + cg) * 16 + row;
+    const int u = (tile * cgs + cg) * 16 + row;
     const int per = ma.merged ? 8 * ma.ncol : ma.ncol;
     const int rep = u / per, rem = u - rep * per;
     const int cls = ma.merged ? rem / ma.ncol : tk.cls;
