@@ -68,6 +68,7 @@ struct MmaShape {
     int nf = 0;        // whole chunks of 16 k
     int groups = 0;    // 16-column groups per work-group, at most
     int narrow = 0;    // row tiles of a wavefront in the narrow form
+    int seq_groups = 0;  // 16-column groups of a work-group that sums the chunks itself, at most
 };
 
 struct fmm_plan_s {
@@ -431,7 +432,7 @@ MmaShape mma_shape(int p) {
     MmaShape m;
     for_order(p, [&](auto pc) {
         using D = fmmk::MmaDims<T, decltype(pc)::value>;
-        m = {D::NPART, D::RTB, D::a_chunks, D::NF, D::kGroups, D::kNarrow};
+        m = {D::NPART, D::RTB, D::a_chunks, D::NF, D::kGroups, D::kNarrow, D::kSeqGroups};
     });
     return m;
 }
@@ -608,13 +609,15 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
                           (!g.periodic || (want_root && g.depth >= 2)) && g.depth - 1 >= (g.periodic ? 0 : g.lmin) &&
                           !many_boxes(g, R);
     if (P->m2l_mode != 3) {
-        // one chunk where the workspace holds no partials (static scratch)
+        // FP64 where the workspace holds no partials (static scratch): each work
+        // item sums the plan's chunks itself
         const bool own = nchunk == mg.nchunk;
         const M2LTask* tasks = own ? P->tasks : P->tasks1;
         const unsigned nx = own ? (unsigned)P->n_tasks : (unsigned)P->n_tasks1;
-        const MmaArgs ma{R, mg.ncol, P->fp64 ? 1 : 0, nchunk, mg.nt_all};
+        const MmaArgs ma{R, mg.ncol, P->fp64 ? 1 : 0, mg.nchunk, mg.nt_all};
         const int64_t groups = ((int64_t)R * mg.ncol * (P->fp64 ? 8 : 1) + 15) / 16;
-        const MmaLaunch ml = mma_launch(P->mma, P->fp64, mg.KP, mg.ncol, nx, R, nchunk, 0.0, nullptr);
+        MmaLaunch ml = mma_launch(P->mma, P->fp64, mg.KP, mg.ncol, nx, R, nchunk, 0.0, nullptr);
+        if (!own) ml = {std::min(ml.groups, P->mma.seq_groups), P->mma.narrow};
         const bool root = sum_down && want_root;
         const RootArgs ra{P->ws.root_part, P->ws.box_part, P->latT, P->lat_seg,
                           P->ws.root_m, root ? P->ws.root_l : nullptr, P->ws.dom};
@@ -628,6 +631,8 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
             if constexpr (sizeof(T) == 8 || PV <= 10) {
                 using D = MmaDims<T, PV>;
                 auto kern = ml.rtw == D::RTB ? k_m2l_mma<T, PV, D::RTB> : k_m2l_mma<T, PV, D::kNarrow>;
+                if constexpr (sizeof(T) == 8)
+                    if (!own) kern = k_m2l_mma<T, PV, D::kNarrow, true>;
                 kern<<<grid, threads, 0, st>>>(g, ma, tasks, P->mlist, (const T*)P->ws.mult, (const T*)P->zrow,
                                                (const uint4*)P->bank_mma, (const uint64_t*)P->mma_masks, loc, part, ra);
             }
@@ -781,7 +786,8 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     mark(P, 2);
     // periodic trees whose M2L ends in a reduction launch form the root there;
     // the level-1 M2M blocks then also leave their shares of the root multipole
-    const bool root_in_reduce = g.periodic && g.depth >= 1 && P->m2l_mode != 0 && P->ws.nchunk > 1;
+    // (by the plan's chunks: without room for partials the root is formed alike)
+    const bool root_in_reduce = g.periodic && g.depth >= 1 && P->m2l_mode != 0 && P->mg.nchunk > 1;
     // folded: the leaf kernel left each leaf's term of level d - 1, and the
     // first launch (level d - 2) forms level d - 1 from them first
     const int top = folded ? g.depth - 2 : g.depth - 1;
@@ -808,11 +814,14 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     }
     // deep periodic trees whose M2L launches did not form the root (no
     // offset chunks): the root once (a single root block of the reduction
-    // kernel), instead of in every block of a downward pass of several rounds
-    if (g.periodic && !root_ready && !fused && g.depth >= 1 && (1u << (3 * (g.depth - 1))) > 256) {
+    // kernel), instead of in every block of a downward pass of several rounds;
+    // also where the reduction launch would have formed it
+    if (g.periodic && !root_ready && !fused && g.depth >= 1 &&
+        (root_in_reduce || (1u << (3 * (g.depth - 1))) > 256)) {
         k_m2l_reduce<T><<<dim3(1, R), kTreeThreads, 0, st>>>(
             g, P->mg, (const T*)P->ws.m2l_part, loc, 1, mult, (const T*)P->m2mT, (const T*)P->m2m_seg,
-            P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l, P->ws.dom, nullptr, 0);
+            P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l, P->ws.dom,
+            root_in_reduce && g.depth >= 2 ? P->ws.root_part : nullptr, 0);
         root_ready = true;
     }
     // downward pass: ancestors' local expansions and the L2L into the leaves
@@ -1461,7 +1470,7 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         // what fmm_eval_noalloc counts its scratch with, so that its size limit
         // does not follow the chunk rule above: up to order 8 the partials of
         // the chunk count for 2048 work items per class tiling, in FP64 above
-        // it none (it then runs one chunk where the plan's do not fit)
+        // it none (where the plan's do not fit, the M2L adds them in registers)
         P->scratch_nchunk = mg.nchunk;
         if (P->m2l_mode == 2 && K > 96) {
             P->scratch_nchunk = 1;
@@ -1747,7 +1756,8 @@ fmm_status fmm_eval_noalloc(fmm_plan_t P, int64_t n, const void* x, const void* 
     }
     P->err.clear();
     Workspace sw;
-    // the plan's offset chunks where their partials fit, else one
+    // room for the partials of the plan's offset chunks, or (FP64) for none:
+    // the M2L then adds the chunks' sums in registers, in the same order
     const bool fits = ws_layout(P, n, S, 1, false, nullptr, nullptr, P->mg.nchunk) <= kScratchBytes;
     ws_layout(P, n, S, 1, false, (char*)base, &sw, fits ? P->mg.nchunk : 1);
     const fmmk::RepDesc rd{0, n, 0, S, L, 0};

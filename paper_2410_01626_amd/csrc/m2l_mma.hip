@@ -59,6 +59,9 @@ struct MmaDims {
     // fetched and signed once for all of them), or for small FP64 trees two
     // (four SIMDs share the rows of a few columns)
     static constexpr int kNarrow = sizeof(T) == 8 && RTB > 2 && RTB % 2 == 0 ? 2 : RTB;
+    // Column groups of a work-group that sums the chunks itself (kSeq): as many
+    // as the registers allow
+    static constexpr int kSeqGroups = RTB / kNarrow > 2 || (RTB / kNarrow == 2 && KP > 112) ? 2 : kGroups;
     static constexpr int RPB = 16 * RTB;           // operator rows of a part
     // 16-byte chunks of a part's image, in whole wavefront copies
     static constexpr int a_chunks = (RPB * KP * (int)sizeof(T) / 16 + 63) & ~63;
@@ -89,7 +92,7 @@ struct MmaArgs {
     int32_t R;        // replicas
     int32_t ncol;     // target columns per class (all levels)
     int32_t merged;   // 1: columns of all classes and replicas in one list
-    int32_t nchunk;   // offset chunks
+    int32_t nchunk;   // offset chunks (kSeq: chunks to sum in registers)
     int64_t nt_all;   // boxes at levels >= lmin (partial-buffer stride)
 };
 
@@ -137,8 +140,13 @@ __device__ __forceinline__ void transpose_rows(float (&r)[4]) {
 // the reflection signs of class cls as bits: [0] bit i for the lane's i-th
 // source coefficient of the whole chunks, [1] bit s for tail coefficient
 // 16 NF + 4 s + kq, [2] bit 4 rt + v for row 16 rt + 4 kq + v.
-template <typename T, int P, int RTW>
-__global__ __launch_bounds__((64 * MmaDims<T, P>::kGroups * (MmaDims<T, P>::RTB / RTW))) void k_m2l_mma(
+//
+// kSeq: one work item runs through every offset and adds the nchunk chunks' sums
+// itself, in m2l_chunk_sum's order (four interleaved sums in registers), so that
+// a workspace without room for partials gives the same bits (FP64, p = 9, depth
+// 3, chunks of one offset: 700 us an evaluation against 240 with partials).
+template <typename T, int P, int RTW, bool kSeq = false>
+__global__ __launch_bounds__((64 * (kSeq ? MmaDims<T, P>::kSeqGroups : MmaDims<T, P>::kGroups) * (MmaDims<T, P>::RTB / RTW))) void k_m2l_mma(
     Geo g, MmaArgs ma, const M2LTask* __restrict__ tasks, const int32_t* __restrict__ olist,
     const T* __restrict__ mult_all, const T* __restrict__ zrow, const uint4* __restrict__ bank,
     const uint64_t* __restrict__ masks, T* __restrict__ loc_all, T* __restrict__ part_all, RootArgs ra) {
@@ -304,13 +312,46 @@ __global__ __launch_bounds__((64 * MmaDims<T, P>::kGroups * (MmaDims<T, P>::RTB 
             for (int t = 0; t < RTW; ++t) acc[t] = mma4(at[s][t], b, acc[t]);
         }
     };
+    Acc sum[kSeq ? 4 : 1][kSeq ? RTW : 1];
+    int chunk = 0, ce = 0;  // the current chunk and its last offset + 1
+    if constexpr (kSeq) {
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+            for (int t = 0; t < RTW; ++t) sum[q][t] = Acc{T(0), T(0), T(0), T(0)};
+        ce = 189 / ma.nchunk;
+    }
+    // the chunk that ends at offset oc goes to its sum
+    auto fold = [&](int oc) {
+        if constexpr (kSeq) {
+            if (oc + 1 < ce) return;
+            const int q = chunk < (ma.nchunk & ~3) ? chunk & 3 : 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i)  // (an addend of 0 and no branch: the sums stay in registers)
+#pragma unroll
+                for (int t = 0; t < RTW; ++t)
+#pragma unroll
+                    for (int v = 0; v < 4; ++v) sum[i][t][v] += i == q ? acc[t][v] : T(0);
+#pragma unroll
+            for (int t = 0; t < RTW; ++t) acc[t] = Acc{T(0), T(0), T(0), T(0)};
+            ++chunk;
+            ce = (chunk + 1) * 189 / ma.nchunk;
+        }
+    };
     for (int oc = o0; oc < o1; oc += 2) {
         step(oc, op0, op1, b0, b1);
-        if (oc + 1 < o1) step(oc + 1, op1, op0, b1, b0);
+        fold(oc);
+        if (oc + 1 < o1) {
+            step(oc + 1, op1, op0, b1, b0);
+            fold(oc + 1);
+        }
     }
     if (!active || !cok) return;
+    if constexpr (kSeq)
+#pragma unroll
+        for (int t = 0; t < RTW; ++t) acc[t] = (sum[0][t] + sum[1][t]) + (sum[2][t] + sum[3][t]);
     const int64_t box = lev_offset(lev) + morton(tx, ty, tz);
-    T* dst = ma.nchunk == 1 ? loc_all + ((size_t)rep * g.nbox + box) * g.Kp
+    T* dst = kSeq || ma.nchunk == 1 ? loc_all + ((size_t)rep * g.nbox + box) * g.Kp
                             : part_all + (((size_t)rep * ma.nchunk + tk.chunk) * ma.nt_all +
                                           (box - lev_offset(g.lmin))) * g.Kp;
 #pragma unroll
