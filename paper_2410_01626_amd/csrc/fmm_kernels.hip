@@ -2436,13 +2436,15 @@ template <typename T> __device__ __forceinline__ T inv_sqrt(T v);
 // hardware reciprocal square root (about 1 ulp); pair distances squared are
 // far from the denormal range, so no range scaling is needed
 template <> __device__ __forceinline__ float inv_sqrt<float>(float v) { return __builtin_amdgcn_rsqf(v); }
-// FP64: the hardware estimate and one third-order step (the library function's
-// own refinement, without its test for zero and infinity: a zero distance is
-// handled by the caller, and infinite ones do not occur)
+// FP64: the hardware estimate y of v^-1/2 and the third-order step
+// y + y e (1/2 + 3/8 e), e = 1 - v y^2 (the binomial series of (1 - e)^-1/2).  A
+// zero v is handled by the caller; an infinite one (distances from 1.3e154 on)
+// has y = 0 and gives 0, with the largest finite number in its place in e.
 __device__ __forceinline__ double inv_sqrt_est(double v) { return __builtin_amdgcn_rsq(v); }
+__device__ __forceinline__ double finite_arg(double v) { return __builtin_fmin(v, 0x1.fffffffffffffp+1023); }
 template <> __device__ __forceinline__ double inv_sqrt<double>(double v) {
     const double y = inv_sqrt_est(v);
-    const double e = __builtin_fma(-(y * v), y, 1.0);
+    const double e = __builtin_fma(-(y * finite_arg(v)), y, 1.0);
     return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
 }
 
@@ -2826,7 +2828,7 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
                         __builtin_amdgcn_sched_barrier(0);
                         T e[4], g3[4];
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) e[k] = -(ri[k] * r2[k]);
+                        for (int k = 0; k < 4; ++k) e[k] = -(ri[k] * finite_arg(r2[k]));
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int k = 0; k < 4; ++k) e[k] = fma_(e[k], ri[k], T(1));
