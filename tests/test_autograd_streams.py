@@ -24,12 +24,14 @@ def test_plan_stream_is_ordered_both_ways(monkeypatch, used, own):
     from paper_2410_01626_amd.autograd import fmm_coulomb
     log = []
     here = _Stream(1, log)
+    monkeypatch.setattr(torch._C, "_cuda_getCurrentRawStream", lambda index: here.cuda_stream)
     monkeypatch.setattr(torch.cuda, "current_stream", lambda device=None: here)
     monkeypatch.setattr(torch.cuda, "ExternalStream", lambda handle, device=None: _Stream(handle, log))
     monkeypatch.setattr(torch.Tensor, "record_stream", lambda self, s: None)
 
     class _Plan:
         stream = _Stream(2 if own else 1, log)
+        device = torch.device("cuda:0")
 
         def _run(self, name, x, lam):
             log.append(name)
