@@ -681,7 +681,21 @@ bool launch_m2l_mma(fmm_plan_t P, const Geo& g, int R, bool want_root, bool* fus
 // with eight slices, for p2p_waves = 8, would gain with 4,096 leaves of 37 and 49
 // atoms (153 -> 123, 199 -> 173 us) and lose with fuller ones (98 atoms: 520
 // against 557 us; 16 systems of 512 leaves of 68: 559 against 667 us).
-constexpr int64_t kSmallLeaves = 4096, kSmallFill = 48;
+constexpr int64_t kSmallLeaves = 4096;
+template <typename T>
+bool near_small(fmm_plan_t P, const fmmk::Geo& g, int R, int64_t maxn) {
+    return sizeof(T) == 4 && P->p2p_waves == fmmk::kSmallWaves && P->p2p_split == 1 && P->p2p_blocks == 1 &&
+           g.nleaf % (8 * fmmk::kSmallWaves) == 0 && (int64_t)g.nleaf * R >= kSmallLeaves &&
+           maxn <= (int64_t)fmmk::kSmallFill * g.nleaf;
+}
+// Blocks of that launch for crowded leaves, per replica: about four per CU over
+// all replicas, a multiple of 8 (the XCDs).
+int crowd_blocks(int R) { return std::max(64, 1024 / R & ~7); }
+// Whether the downward launch orders the leaves by work (its launch exists and
+// the tree is small enough).
+bool leaves_ordered(const fmmk::Geo& g) {
+    return g.nleaf <= fmmk::kOrderCap && g.depth >= 1 && g.depth - 1 >= (g.periodic ? 0 : g.lmin);
+}
 
 // Binning and leaf multipoles of R replicas (grid y = replica): replica
 // descriptors, the open bounding cube, leaf keys, the counting sort and the
@@ -691,7 +705,7 @@ constexpr int64_t kSmallLeaves = 4096, kSmallFill = 48;
 template <typename T>
 void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
                      const T* x, const T* qA, const T* qB, const int32_t* site, const double* lam,
-                     const fmmk::FormArgs<T>& fa, int64_t maxn, int64_t S_tot, bool fold) {
+                     const fmmk::FormArgs<T>& fa, int64_t maxn, int64_t S_tot, bool fold, int32_t* crowded) {
     using namespace fmmk;
     hipStream_t st = P->stream;
     const int nstore = (int)rd.size();
@@ -757,7 +771,7 @@ void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
         // (leaves without bins: more than kScanFuseCap of them, or of sites)
         k_leaf_p2m_small<T><<<dim3(g.nleaf / (kLeafThreads / 64), R), kLeafThreads, lds, st>>>(
             g, reps, x, qA, qB, site, lam, fa, P->ws.dom, P->ws.leaf_start, P->ws.perm, (V4*)P->ws.pos, P->status,
-            (T*)P->ws.mult, P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp, lb);
+            (T*)P->ws.mult, P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp, lb, crowded);
         return;
     }
     // the folded first M2M step is its own instantiation (it needs more
@@ -766,7 +780,7 @@ void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
     leaf<<<dim3(g.nleaf, R), kLeafThreads, lds, st>>>(
         g, reps, x, qA, qB, site, lam, fa, P->ws.dom, P->ws.leaf_start, P->ws.perm, (V4*)P->ws.pos, P->status,
         (T*)P->ws.mult, P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp, bins, lb, (const T*)P->m2mT,
-        (const T*)P->m2m_seg, fold ? P->ws.m2m_part : nullptr);
+        (const T*)P->m2m_seg, fold ? P->ws.m2m_part : nullptr, crowded);
 }
 
 // The tree passes of R expansion slots (grid y = slot): M2M per level, the
@@ -831,7 +845,7 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     // leaves for the near field by decreasing work
     int32_t* order = nullptr;
     if (g.depth >= 1 && g.depth - 1 >= l0) {
-        if (want_order && g.nleaf <= kOrderCap) order = P->ws.leaf_order;
+        if (want_order && leaves_ordered(g)) order = P->ws.leaf_order;
         // up to 64 boxes above the leaves: two blocks per box (four leaves
         // each), so that the latency-bound chain runs on twice the CUs (one
         // block of 512 threads fits a CU; four blocks per box would leave the
@@ -894,7 +908,11 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
     // the tree is small enough for launch latency to matter (deeper trees
     // keep the separate launch, which then costs little next to the work)
     const bool fold = P->ws.m2m_part != nullptr && g.depth - 2 >= g.lmin && g.nleaf <= kScanFuseCap;
-    enqueue_bin_p2m<T>(P, g, rd, R, x, qA, qB, site, lam, fa, maxn, S_tot, fold);
+    // wavefront-per-leaf near field: crowded leaves are found in the order of
+    // work or else listed by the leaf kernel (in the order's place)
+    const bool small = near_small<T>(P, g, R, maxn);
+    int32_t* crowded = small && !leaves_ordered(g) ? P->ws.leaf_order : nullptr;
+    enqueue_bin_p2m<T>(P, g, rd, R, x, qA, qB, site, lam, fa, maxn, S_tot, fold, crowded);
     int32_t* order = enqueue_tree<T>(P, g, R, true, fold);
     const RepDesc* reps = P->ws.reps;
     const unsigned ab = nblocks(maxn, 256);
@@ -909,16 +927,13 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
     if constexpr (sizeof(T) == 8)
         if (P->p2p_blocks == 1 && P->p2p_waves == 8 && (int64_t)g.nleaf * P->p2p_split * R > 256)
             near = k_near_far<T, 8, false, 4>;
-    bool small = false;
-    if constexpr (sizeof(T) == 4) {
-        small = P->p2p_waves == kSmallWaves && P->p2p_split == 1 && P->p2p_blocks == 1 &&
-                g.nleaf % (8 * kSmallWaves) == 0 && (int64_t)g.nleaf * R >= kSmallLeaves &&
-                maxn <= kSmallFill * g.nleaf;
-        if (small)
-            k_near_small<T><<<dim3(g.nleaf / kSmallWaves, R), 64 * kSmallWaves, near_small_lds<T>(g.K), st>>>(
+    if constexpr (sizeof(T) == 4)
+        if (small) {
+            const int nc = crowd_blocks(R);
+            k_near_small<T><<<dim3(g.nleaf / kSmallWaves + nc, R), 64 * kSmallWaves, near_small_lds<T>(g.K), st>>>(
                 g, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx, (const T*)P->gcoef, qA, qB,
-                site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status);
-    }
+                site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status, crowded, nc);
+        }
     if (!small)
         near<<<dim3(g.nleaf * P->p2p_split * P->p2p_blocks, R), 64 * P->p2p_waves, 0, st>>>(
             g, P->p2p_split, P->p2p_blocks, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx,
@@ -941,7 +956,7 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
                                                        ham && S_tot > 0 ? P->ws.hc_dl : nullptr,
                                                        P->ws.leaf_count, P->ws.site_count,
                                                        P->excl_n > 0 ? P->excl_e : nullptr, (int)ab,
-                                                       nullptr, nullptr, P->ws.ovf_n);
+                                                       nullptr, nullptr, P->ws.ovf_n, crowded);
     mark(P, -1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(P, FMM_E_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
@@ -986,7 +1001,7 @@ fmm_status enqueue_adjoint_full(fmm_plan_t P, const fmmk::RepDesc& r0, const T* 
     const RepSpan rd(rd2, 2);
     const FormArgs<T> fa{nullptr, nullptr, nullptr};
     mark(P, 0);
-    enqueue_bin_p2m<T>(P, g, rd, 1, x, qA, qB, site, lam, fa, n, S, false);
+    enqueue_bin_p2m<T>(P, g, rd, 1, x, qA, qB, site, lam, fa, n, S, false, nullptr);
     using V4 = vec4_t<T>;
     k_leaf_src2<T><<<g.nleaf, kLeafThreads, src2_lds_bytes<T>(g.K), st>>>(
         g, (const V4*)P->ws.pos, P->ws.perm, P->ws.leaf_start, gphi, gF, P->ws.dom, (V4*)P->ws.adj_src2, (T*)P->ws.mult,
@@ -1006,7 +1021,7 @@ fmm_status enqueue_adjoint_full(fmm_plan_t P, const fmmk::RepDesc& r0, const T* 
                                                     P->ws.site_members, P->ws.cphi, E ? E : P->ws.E_tmp, dVdl,
                                                     P->status, qA, qB, lam, fa, nullptr, P->ws.reps, nullptr,
                                                     nullptr, P->ws.leaf_count, P->ws.site_count, nullptr, 0,
-                                                    P->ws.adj_cphi2, glam, P->ws.ovf_n);
+                                                    P->ws.adj_cphi2, glam, P->ws.ovf_n, nullptr);
     mark(P, -1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(P, FMM_E_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
@@ -1770,6 +1785,9 @@ fmm_status fmm_eval_noalloc(fmm_plan_t P, int64_t n, const void* x, const void* 
                                                                             std::max<int64_t>(S, 1), 0);
     fmmk::k_fill_f64<<<1, 64, 0, st>>>(sw.dom, 8, 0.0);
     if (sw.ovf_n) fmmk::k_fill_i32<<<1, 64, 0, st>>>(sw.ovf_n, 1, 0);
+    const Geo g = make_geo(P);
+    if (!P->fp64 && near_small<float>(P, g, 1, n) && !leaves_ordered(g))
+        fmmk::k_fill_i32<<<1, 64, 0, st>>>(sw.leaf_order + g.nleaf - 3, 3, 0);  // the list of crowded leaves
     if (sw.msplit) {
         const int64_t words = (int64_t)(msplit_bytes(P, 1) / 4);
         fmmk::k_fill_i32<<<(unsigned)std::min<int64_t>(1024, (words + 255) / 256), 256, 0, st>>>(

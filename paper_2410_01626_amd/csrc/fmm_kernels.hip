@@ -896,6 +896,36 @@ __device__ __forceinline__ double form_charge(const T* __restrict__ qA, const T*
     return q;
 }
 
+// Crowded leaves of each replica (more than kSmallSolo atoms) for k_near_small
+// without an order of work, filed by the leaf kernels in nleaf entries: the
+// fullest (more than a round of targets) from entry 0 up, the others from entry
+// nleaf - 4 down; the last three entries hold how many of each there are and the
+// next one to take.  A call that runs k_near_small has at most kSmallFill atoms a
+// leaf on average, so fewer than 3/4 of the entries are used.  k_reduce clears
+// the three.  list == null: not wanted.
+constexpr int kSmallSolo = 64;  // atoms of a leaf that one wavefront of k_near_small takes alone
+constexpr int kSmallFill = 48;  // mean population up to which trees of many leaves run the small forms
+constexpr int kSmallRound = 256;  // targets of a round of k_near_small's blocks
+struct CrowdList {
+    int32_t *entry, *fullest, *others, *ticket;
+    int last;  // entry of the first of the others
+    __device__ CrowdList(int32_t* list, int64_t nleaf, int rep) {
+        entry = list + (size_t)rep * nleaf;
+        fullest = entry + nleaf - 3;
+        others = entry + nleaf - 2;
+        ticket = entry + nleaf - 1;
+        last = (int)nleaf - 4;
+    }
+    __device__ void clear() const { *fullest = *others = *ticket = 0; }
+};
+static_assert(4 * kSmallFill < 3 * (kSmallSolo + 1), "the list holds every crowded leaf");
+__device__ __forceinline__ void file_crowded(int32_t* list, int64_t nleaf, int rep, int leaf, int n) {
+    if (!list || n <= kSmallSolo) return;
+    const CrowdList c(list, nleaf, rep);
+    const int at = n > kSmallRound ? atomicAdd(c.fullest, 1) : c.last - atomicAdd(c.others, 1);
+    if (at >= 0 && at <= c.last) c.entry[at] = leaf;
+}
+
 // Per leaf, one block of 256 threads: sort the leaf's atoms by caller index
 // (stable binning; leaves of up to 256 atoms by counting ranks, larger ones by
 // a bitonic sort), gather (x - c_leaf, q) into the sorted particle array with
@@ -922,7 +952,7 @@ __device__ __forceinline__ void leaf_block(
     int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
     T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
     int split_kp, Bins bins, LeafBinArgs lb, const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
-    double* __restrict__ m2m_part_all) {
+    double* __restrict__ m2m_part_all, int32_t* __restrict__ crowded) {
     static_assert(2 * kLeafThreads == kTreeThreads, "two tree-operator shares per leaf thread");
     extern __shared__ __align__(16) unsigned char leaf_lds[];
     __shared__ double ps[2][kLeafThreads / 64];
@@ -989,6 +1019,7 @@ __device__ __forceinline__ void leaf_block(
         b = leaf_start[leaf];
         n = leaf_start[leaf + 1] - b;
     }
+    if (tid == 0) file_crowded(crowded, g.nleaf, blockIdx.y, leaf, n);
     auto fill_members = [&](int32_t* dst) {
         for (int r = tid; r < min(n, bins.cap); r += kLeafThreads) dst[r] = bk[r];
         if (n > bins.cap) {
@@ -1181,10 +1212,10 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
     int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
     T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
     int split_kp, Bins bins, LeafBinArgs lb, const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
-    double* __restrict__ m2m_part_all) {
+    double* __restrict__ m2m_part_all, int32_t* __restrict__ crowded) {
     __shared__ RhoLds<T> rho;
     leaf_block<T, FOLD>(blockIdx.x, rho, g, reps, x, qA, qB, site, lam, fa, dom_all, leaf_start_all, perm, pos, status,
-                        mult_all, leaf_part_all, msplit_all, split_kp, bins, lb, m2m0, m2m0_seg, m2m_part_all);
+                        mult_all, leaf_part_all, msplit_all, split_kp, bins, lb, m2m0, m2m0_seg, m2m_part_all, crowded);
 }
 
 // The same for trees of many small leaves: one wavefront per leaf (up to 64
@@ -1200,7 +1231,7 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m_small(
     FormArgs<T> fa, const double* __restrict__ dom_all, int32_t* __restrict__ leaf_start_all,
     int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
     T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
-    int split_kp, LeafBinArgs lb) {
+    int split_kp, LeafBinArgs lb, int32_t* __restrict__ crowded) {
     extern __shared__ __align__(16) unsigned char leaf_lds[];
     __shared__ RhoLds<T> rho;
     constexpr int kW = kLeafThreads / 64;
@@ -1211,9 +1242,11 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m_small(
     const int32_t* leaf_start = leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     load_rho_lds<T, kLeafThreads>(rho, g.p);
-    const int leaf = __builtin_amdgcn_readfirstlane(blockIdx.x * kW + wave);
+    // (one leaf of each quarter: crowded leaves, often neighbours, seldom meet)
+    const int leaf = __builtin_amdgcn_readfirstlane(blockIdx.x + wave * gridDim.x);
     const int b = __builtin_amdgcn_readfirstlane(leaf_start[leaf]);
     const int n = __builtin_amdgcn_readfirstlane(leaf_start[leaf + 1]) - b;
+    static_assert(kSmallSolo >= 64, "leaves of up to 64 atoms are not listed");
     const bool solo = n <= 64;
     const double edge = dom[3];
     const double h = edge / g.nb;
@@ -1316,11 +1349,11 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m_small(
         }
     }
     for (int w = 0; w < kW; ++w) {
-        const int big = blockIdx.x * kW + w;
+        const int big = blockIdx.x + w * gridDim.x;
         if (leaf_start[big + 1] - leaf_start[big] <= 64) continue;
         __syncthreads();  // the rows are free
         leaf_block<T, false>(big, rho, g, reps, x, qA, qB, site, lam, fa, dom_all, leaf_start_all, perm, pos, status,
-                             mult_all, leaf_part_all, msplit_all, split_kp, Bins{}, lb, unused, unused, nullptr);
+                             mult_all, leaf_part_all, msplit_all, split_kp, Bins{}, lb, unused, unused, nullptr, crowded);
     }
 }
 
@@ -3003,13 +3036,25 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
 // barriers) and repeats its set-up in every wavefront; here the wavefronts are
 // independent, sources pass through a window of kSmallWin each, the next four
 // are read while four are summed, and the lane groups of a far field take their
-// orders side by side.  Leaves of more than kSmallSolo atoms are done by the
-// whole block afterwards, in k_near_far's own split.  500,000 atoms at depth 5
-// (15 per leaf): 625 -> 290 us (the pair loop's issue cycles: about 140 us).
+// orders side by side.  500,000 atoms at depth 5 (15 per leaf): 625 -> 290 us
+// (the pair loop's issue cycles: about 140 us).
+//
+// Leaves of more than kSmallSolo atoms are done by a whole block each, in
+// k_near_far's own split, by the launch's first ncrowd blocks (of every replica):
+// where a system fills a part of its cell, most of the work is in few crowded
+// leaves, which need all wavefronts of the chip side by side and from the start
+// (a wavefront alone takes 50 us for 64 atoms among 27 leaves of 64).  Without an
+// order of work the leaf kernels have listed them, and the blocks take them off
+// the list; with one (512 leaves at most) block i looks at its slots i, i +
+// ncrowd, ...  From four chunks of targets on every wavefront sweeps all sources,
+// and the block stages them together.  Per evaluation, p = 6 (a wavefront each up
+// to 128 atoms and then its own block before; a block per leaf): 120,000 atoms in
+// three tenths of a depth-4 cell 545 -> 441 us (480), 300,000 in a ball of a tenth
+// of a depth-5 cell 1,227 -> 1,002 us (1,185), 8 x 15,000 in such balls at depth 3
+// 1,144 -> 615 us (912).
 // LDS: a window and the K gradient-table rows per wavefront, dynamic.
 constexpr int kSmallWaves = 4;
 constexpr int kSmallWin = 256;   // sources of a wavefront's window
-constexpr int kSmallSolo = 128;  // atoms of a leaf that one wavefront takes alone
 template <typename T>
 __host__ __device__ inline size_t near_small_lds(int K) {
     return (size_t)kSmallWaves * (kSmallWin + K) * sizeof(vec4_t<T>);
@@ -3023,34 +3068,55 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
     const T* __restrict__ qA, const T* __restrict__ qB, const int32_t* __restrict__ site,
     T* __restrict__ phi_out, T* __restrict__ F_out,
     double* __restrict__ leaf_energy_all, double* __restrict__ cphi, int unit_dq,
-    const int32_t* __restrict__ leaf_order_all, int32_t* __restrict__ status) {
+    const int32_t* __restrict__ leaf_order_all, int32_t* __restrict__ status,
+    int32_t* __restrict__ crowded_all, int ncrowd) {
     using V4 = vec4_t<T>;
     constexpr int kNW = kSmallWaves;
     constexpr int CAP = 2048;  // sources of a pass: what k_near_far stages at a time
-    extern __shared__ char near_lds[];
+    extern __shared__ __align__(16) char near_lds[];
+    // the launch's blocks in order of dispatch: those for crowded leaves, entry by
+    // entry over the replicas, then the others, replica by replica
+    const int R = gridDim.y, nblk = gridDim.x - ncrowd;  // (nleaf / kNW, a multiple of 8 as ncrowd)
+    const int L = (int)(blockIdx.y * gridDim.x + blockIdx.x) - ncrowd * R;
+    const bool crowd = L < 0;
+    const int rep = crowd ? (L + ncrowd * R) % R : L / nblk, first = crowd ? (L + ncrowd * R) / R : L - rep * nblk;
+    const int32_t* leaf_start = leaf_start_all + (size_t)rep * (g.nleaf + 1);
+    const int32_t* order = leaf_order_all ? leaf_order_all + (size_t)rep * g.nleaf : nullptr;
+    auto leaf_of = [&](int slot) { return order ? order[slot] : slot; };
+    const CrowdList listed(crowded_all, g.nleaf, rep);
+    const int nfull = crowd && crowded_all ? min(*listed.fullest, listed.last + 1) : 0;
+    const int ncand = !crowd ? 0 : crowded_all ? min(nfull + *listed.others, listed.last + 1) : g.nleaf;  // candidates
+    auto cand_slot = [&](int e) { return !crowded_all ? e : listed.entry[e < nfull ? e : listed.last - (e - nfull)]; };
+    auto slot_pop = [&](int slot) {
+        const int lf = leaf_of(slot);
+        return leaf_start[lf + 1] - leaf_start[lf];
+    };
+    if (crowd) {
+        // most such blocks have no crowded leaf and end here
+        bool any = false;
+        for (int e = first + (int)(threadIdx.x & 63) * ncrowd; e < ncand; e += 64 * ncrowd)
+            any |= slot_pop(cand_slot(e)) > kSmallSolo;
+        if (!__ballot(any)) return;
+    }
     __shared__ int nb_start[kNW][28], nb_pre[kNW][32];
     __shared__ T nb_off[kNW][27][3];
     __shared__ RhoLds<T> rho;
     load_rho_lds<T, 64 * kNW>(rho, g.p);
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
-    V4* tile = (V4*)near_lds + (size_t)wave * (kSmallWin + g.K);
-    V4* coef = tile + kSmallWin;  // (local coefficient, its three gradient rows)
-    const int64_t n_sites = reps[blockIdx.y].S;
-    const int32_t* leaf_start = leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1);
-    const double* dom = dom_all + 8 * blockIdx.y;
-    const T* loc = loc_all + (size_t)blockIdx.y * g.nbox * g.Kp;
-    double* leaf_energy = leaf_energy_all + (size_t)blockIdx.y * g.nleaf;
-    const int32_t* order = leaf_order_all ? leaf_order_all + (size_t)blockIdx.y * g.nleaf : nullptr;
-    const int nblk = gridDim.x;  // nleaf / kNW, a multiple of 8
+    V4* const tiles = (V4*)near_lds;  // the wavefronts' windows
+    V4* coef = tiles + kNW * kSmallWin + wave * g.K;  // (local coefficient, its three gradient rows)
+    const int64_t n_sites = reps[rep].S;
+    const double* dom = dom_all + 8 * rep;
+    const T* loc = loc_all + (size_t)rep * g.nbox * g.Kp;
+    double* leaf_energy = leaf_energy_all + (size_t)rep * g.nleaf;
     // a block takes one leaf of each quarter of the order (leaves sorted by
     // work, or neighbours of one cluster, do not meet in a block); without an
     // order of work each XCD (blocks b, b + 8, ...) walks runs of up to 64
     // neighbouring leaves, whose sources its L2 then holds
     const int run = min(64, nblk >> 3);
-    const int bx = blockIdx.x % (8 * run);
-    const int b0 = order ? (int)blockIdx.x : (int)blockIdx.x - bx + (bx & 7) * run + (bx >> 3);
+    const int bx = first % (8 * run);
+    const int b0 = order ? first : first - bx + (bx & 7) * run + (bx >> 3);
     auto slot_of = [&](int w) -> int { return b0 + w * nblk; };
-    auto leaf_of = [&](int slot) { return order ? order[slot] : slot; };
     const bool far = g.has_far;
     const double edge = dom[3];
     const double h = edge / g.nb;
@@ -3115,16 +3181,21 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
         wb = we = 0;
         wave_lds_fence();
     };
-    // sources [s, min(s + kSmallWin, total)) into the window
-    auto stage = [&](int s) {
-        constexpr int G = kSmallWin / 64;
-        wave_lds_fence();
-        const int cnt = min(kSmallWin, total - s);
+    // sources [s, min(s + kSmallWin, total)) into the wavefront's window, or
+    // (whole: by all wavefronts in step) four times as many into all of them
+    auto stage = [&](int s, auto whole) {
+        constexpr bool W = decltype(whole)::value;
+        constexpr int G = kSmallWin / 64, N = W ? kNW * kSmallWin : kSmallWin, NT = W ? 64 * kNW : 64;
+        const int t = W ? tid : lane;
+        V4* tile = W ? tiles : tiles + wave * kSmallWin;
+        if constexpr (W) __syncthreads();  // the previous window's readers are done
+        else wave_lds_fence();
+        const int cnt = min(N, total - s);
         V4 a[G];
         int lo_[G];
 #pragma unroll
         for (int m = 0; m < G; ++m) {
-            const int gsrc = s + min(lane + 64 * m, cnt - 1);
+            const int gsrc = s + min(t + NT * m, cnt - 1);
             int lo = 0;  // largest i with nb_pre[i] <= gsrc (i < 27: gsrc < nb_pre[27])
 #pragma unroll
             for (int b = 16; b >= 1; b >>= 1)
@@ -3134,20 +3205,23 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
         }
 #pragma unroll
         for (int m = 0; m < G; ++m)
-            if (lane + 64 * m < cnt) {
+            if (t + NT * m < cnt) {
                 V4 v = a[m];
                 v.x += nb_off[wave][lo_[m]][0];
                 v.y += nb_off[wave][lo_[m]][1];
                 v.z += nb_off[wave][lo_[m]][2];
-                tile[lane + 64 * m] = v;
+                tile[t + NT * m] = v;
             }
         wb = s;
         we = s + cnt;
-        wave_lds_fence();
+        if constexpr (W) __syncthreads();
+        else wave_lds_fence();
     };
     // slice `slice` of `wpc` of a chunk of targets (lane groups of gsz lanes;
     // tj: this lane's target in the leaf), summed over the lane groups
-    auto run_slice = [&](const V4& me, bool tv, int tj, int slice, int wpc, int gsz, T& ph, T& fx, T& fy, T& fz) {
+    auto run_slice = [&](const V4& me, bool tv, int tj, int slice, int wpc, int gsz, T& ph, T& fx, T& fy, T& fz,
+                         auto whole) {
+        V4* tile = decltype(whole)::value ? tiles : tiles + wave * kSmallWin;
         const int ngrp = 64 / gsz, grp = lane / gsz, lg = 6 - (31 - __builtin_clz(gsz));  // ngrp = 1 << lg
         ph = fx = fy = fz = T(0);
         for (int s0 = 0; s0 < total; s0 += CAP) {
@@ -3156,7 +3230,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
             const int jb = s0 + slice * sl, je = s0 + min(slice * sl + sl, cnt);
             // only the own leaf (neighbour 13, [own_b, own_e)) can hold a source at distance 0
             for (int cur = jb; cur < je;) {
-                if (cur < wb || cur >= we) stage(cur);
+                if (cur < wb || cur >= we) stage(cur, whole);
                 const int end = min(je, we);
                 // lane group grp takes sources j0 + c, j0 + c + ngrp, ... of the
                 // slice's interleaving; nf of them in every group (a uniform
@@ -3164,8 +3238,8 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
                 // while they are summed.
                 auto sweep = [&](int j0, int j1, auto guard) {
                     if (j0 >= j1) return;
-                    const int first = j0 + ((grp - (j0 - jb)) & (ngrp - 1));
-                    const V4* src = tile + (first - wb);
+                    const int j_own = j0 + ((grp - (j0 - jb)) & (ngrp - 1));
+                    const V4* src = tile + (j_own - wb);
                     const int nf = (j1 - j0) >> lg, n4 = nf >> 2;
                     auto pair = [&](const V4& s) {
                         const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
@@ -3180,6 +3254,32 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
                         fz = fma_(qr3, dz, fz);
                     };
                     V4 sa[4], sb[4];
+                    if constexpr (decltype(whole)::value) {
+                        // full chunk: the range is the same for every lane (reads
+                        // run at most 8 entries past it, within the LDS; never used)
+                        if (__builtin_amdgcn_readfirstlane(lg) == 0) {
+                            int i = __builtin_amdgcn_readfirstlane(j0 - wb);
+                            const int e = __builtin_amdgcn_readfirstlane(j1 - wb);
+#pragma unroll
+                            for (int t = 0; t < 4; ++t) sa[t] = tile[i + t];
+                            for (; i + 7 < e; i += 8) {
+#pragma unroll
+                                for (int t = 0; t < 4; ++t) sb[t] = tile[i + 4 + t];
+                                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                                for (int t = 0; t < 4; ++t) pair(sa[t]);
+                                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                                for (int t = 0; t < 4; ++t) sa[t] = tile[i + 8 + t];
+                                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                                for (int t = 0; t < 4; ++t) pair(sb[t]);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                            for (; i < e; ++i) pair(tile[i]);
+                            return;
+                        }
+                    }
                     if (n4 > 0) {
                         auto load = [&](int blk, V4(&v)[4]) {
                             const V4* q = src + (min(blk, n4 - 1) << (lg + 2));
@@ -3207,12 +3307,12 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
                     const int last = j1 - wb - 1;  // the last entry of the range
                     V4 sr[4];
 #pragma unroll
-                    for (int t = 0; t < 3; ++t) sr[t] = tile[min(first - wb + ((4 * n4 + t) << lg), last)];
-                    sr[3] = tile[min(first - wb + (nf << lg), last)];
+                    for (int t = 0; t < 3; ++t) sr[t] = tile[min(j_own - wb + ((4 * n4 + t) << lg), last)];
+                    sr[3] = tile[min(j_own - wb + (nf << lg), last)];
 #pragma unroll
                     for (int t = 0; t < 3; ++t)
                         if (4 * n4 + t < nf) pair(sr[t]);
-                    if (first + (nf << lg) < j1) pair(sr[3]);
+                    if (j_own + (nf << lg) < j1) pair(sr[3]);
                 };
                 sweep(cur, min(end, own_b), std::false_type{});
                 sweep(max(cur, own_b), min(end, own_e), std::true_type{});
@@ -3319,56 +3419,53 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
         }
     };
 
-    const int slot = __builtin_amdgcn_readfirstlane(slot_of(wave));
-    const int leaf = __builtin_amdgcn_readfirstlane(leaf_of(slot));
-    const int ln = __builtin_amdgcn_readfirstlane(leaf_start[leaf + 1] - leaf_start[leaf]);
-    if (ln == 0 && lane == 0) leaf_energy[slot] = 0.0;
-    if (ln > 0 && ln <= kSmallSolo) {
-        static_assert(kSmallSolo == 128, "two chunks");
+    if (!crowd) {
+        const int slot = __builtin_amdgcn_readfirstlane(slot_of(wave));
+        const int leaf = __builtin_amdgcn_readfirstlane(leaf_of(slot));
+        const int ln = __builtin_amdgcn_readfirstlane(leaf_start[leaf + 1] - leaf_start[leaf]);
+        if (ln == 0 && lane == 0) leaf_energy[slot] = 0.0;
+        if (ln == 0 || ln > kSmallSolo) return;
+        static_assert(kSmallSolo <= 64, "one chunk");
         setup(leaf);
-        const int nch = ln > 64 ? 2 : 1;
-        int w[kNW];
-        split(ln, nch, w);
-        double esum = 0.0;
-        for (int c = 0; c < nch; ++c) {
-            const int tc = min(64, ln - 64 * c), gsz = pow2_lanes(tc);
-            const int grp = lane / gsz, tl = lane & (gsz - 1), wpc = c ? w[1] : w[0];
-            const bool tv = tl < tc;
-            const int tj = 64 * c + tl;
-            V4 me;
-            me.x = me.y = me.z = me.w = T(0);
-            int32_t i = 0, st = -1;
-            double dq = 0.0;
-            if (tv) {
-                me = pos[lb + tj];
-                i = perm[lb + tj];
-                st = site[i];
-                dq = unit_dq ? 1.0 : (double)qB[i] - (double)qA[i];
-            }
-            T p = T(0), ex = T(0), ey = T(0), ez = T(0);
-            for (int slice = 0; slice < wpc; ++slice) {
-                T ph, fx, fy, fz;
-                run_slice(me, tv, tj, slice, wpc, gsz, ph, fx, fy, fz);
-                p += ph;
-                ex += fx;
-                ey += fy;
-                ez += fz;
-            }
-            double e = 0.0;
-            if (tv && grp == 0) e = finish(me, i, st, dq, p, ex, ey, ez);
-            esum += e;
+        const int gsz = pow2_lanes(ln), grp = lane / gsz, tl = lane & (gsz - 1);
+        const bool tv = tl < ln;
+        V4 me;
+        me.x = me.y = me.z = me.w = T(0);
+        int32_t i = 0, st = -1;
+        double dq = 0.0;
+        if (tv) {
+            me = pos[lb + tl];
+            i = perm[lb + tl];
+            st = site[i];
+            dq = unit_dq ? 1.0 : (double)qB[i] - (double)qA[i];
         }
+        T p = T(0), ex = T(0), ey = T(0), ez = T(0);
+        for (int slice = 0; slice < kNW; ++slice) {
+            T ph, fx, fy, fz;
+            run_slice(me, tv, tl, slice, kNW, gsz, ph, fx, fy, fz, std::false_type{});
+            p += ph;
+            ex += fx;
+            ey += fy;
+            ez += fz;
+        }
+        double esum = 0.0;
+        if (tv && grp == 0) esum = finish(me, i, st, dq, p, ex, ey, ez);
         esum = wave_sum<double>(esum);
         if (lane == 0) leaf_energy[slot] = esum;
+        return;
     }
 
-    // fuller leaves, by the whole block (uniform conditions); a slice's sums
+    // crowded leaves, by the whole block (uniform conditions); a slice's sums
     // and a chunk's energies pass through the wavefronts' own windows
-    auto part = [&](int w, int a) { return (T*)((V4*)near_lds + (size_t)w * (kSmallWin + g.K)) + 64 * a; };
-    for (int b = 0; b < kNW; ++b) {
-        const int bslot = slot_of(b), bleaf = leaf_of(bslot);
-        const int tn = leaf_start[bleaf + 1] - leaf_start[bleaf];
-        if (tn <= kSmallSolo) continue;
+    auto part = [&](int w, int a) { return (T*)(tiles + w * kSmallWin) + 64 * a; };
+    __shared__ int next[2];
+    for (int e = first, it = 0; e < ncand;) {
+        const int bslot = __builtin_amdgcn_readfirstlane(cand_slot(e));
+        const int bleaf = __builtin_amdgcn_readfirstlane(leaf_of(bslot));
+        const int tn = __builtin_amdgcn_readfirstlane(leaf_start[bleaf + 1] - leaf_start[bleaf]);
+        if (!crowded_all) e += ncrowd;
+        if (tn <= kSmallSolo) continue;  // (with an order of work only)
+        if (crowded_all && tid == 0) next[it & 1] = ncrowd + atomicAdd(listed.ticket, 1);
         setup(bleaf);
         double esum = 0.0;
         for (int t0 = 0; t0 < tn; t0 += 64 * kNW) {
@@ -3395,7 +3492,12 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
             me.x = me.y = me.z = me.w = T(0);
             if (tv) me = pos[lb + tj];
             T ph, fx, fy, fz;
-            run_slice(me, tv, tj, slice, wpc, gsz, ph, fx, fy, fz);
+            if (nch == kNW) {
+                run_slice(me, tv, tj, 0, 1, gsz, ph, fx, fy, fz, std::true_type{});
+                __syncthreads();  // every sweep is done with the windows
+            } else {
+                run_slice(me, tv, tj, slice, wpc, gsz, ph, fx, fy, fz, std::false_type{});
+            }
             wave_lds_fence();
             if (grp == 0) {
                 part(wave, 0)[tl] = ph;
@@ -3430,6 +3532,7 @@ __global__ __launch_bounds__(64 * kSmallWaves, 4) void k_near_small(
             esum = wave_sum<double>(esum);
             if (lane == 0) leaf_energy[bslot] = esum;
         }
+        if (crowded_all) e = __builtin_amdgcn_readfirstlane(next[it++ & 1]);  // (written before the barriers above)
     }
 }
 
@@ -3684,7 +3787,8 @@ __global__ __launch_bounds__(256) void k_reduce(Geo g, int R, int64_t nparts,
                                                 int32_t* __restrict__ site_count,
                                                 const double* __restrict__ excl_e, int excl_parts,
                                                 const double* __restrict__ cphi2,
-                                                double* __restrict__ glam, int32_t* __restrict__ ovf_n) {
+                                                double* __restrict__ glam, int32_t* __restrict__ ovf_n,
+                                                int32_t* __restrict__ crowded) {
     __shared__ double red[4], red_t[4];
     __shared__ int32_t mem[kSiteCap];
     const int t = threadIdx.x;
@@ -3694,6 +3798,7 @@ __global__ __launch_bounds__(256) void k_reduce(Geo g, int R, int64_t nparts,
     if (b < R) {
         for (int i = t; i < g.nleaf; i += 256) leaf_count[(size_t)b * g.nleaf + i] = 0;
         if (b == 0 && t == 0 && ovf_n) *ovf_n = 0;
+        if (t == 0 && crowded) CrowdList(crowded, g.nleaf, b).clear();
     } else if (t == 0) {
         site_count[b - R] = 0;
     }
