@@ -324,11 +324,13 @@ __device__ __forceinline__ void store_reps(const RepSet& set, RepDesc* reps) {
 
 // ------------------------------------------------------------------ domain
 
-// Root cube of an open system from its extent: dom = {lo_x, lo_y, lo_z, edge}.
+// Root cube of an open system from its extent: dom = {lo_x, lo_y, lo_z, edge},
+// dom[5] the extent.
 // The edge is the largest extent, enlarged by a relative 2^-20 so no atom sits
 // on the far face.
 __device__ __forceinline__ void root_cube(double (&mn)[3], const double (&mx)[3], double* __restrict__ dom) {
     double e = fmax(mx[0] - mn[0], fmax(mx[1] - mn[1], mx[2] - mn[2]));
+    dom[5] = e;
     if (!(e > 0) || !(e < 1e300)) {  // no atoms, or all atoms at one point
         e = 1.0;
         if (!(mn[0] < 1e300)) mn[0] = mn[1] = mn[2] = 0.0;
@@ -525,7 +527,7 @@ __global__ __launch_bounds__(256) void k_charge_key(
     const int64_t il = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (g.periodic && il == 0) {
         dom[0] = dom[1] = dom[2] = 0.0;
-        dom[3] = box;
+        dom[3] = dom[5] = box;
     }
     if (rd.n == 0) return;
     // every input of the lane is loaded up front (idle lanes read the
@@ -2473,13 +2475,20 @@ template <> __device__ __forceinline__ float inv_sqrt<float>(float v) { return _
 // y + y e (1/2 + 3/8 e), e = 1 - v y^2 (the binomial series of (1 - e)^-1/2).  A
 // zero v is handled by the caller; an infinite one (distances from 1.3e154 on)
 // has y = 0 and gives 0, with the largest finite number in its place in e.
+// inv_sqrt_finite leaves that out (30k box: 1 us of 70).
 __device__ __forceinline__ double inv_sqrt_est(double v) { return __builtin_amdgcn_rsq(v); }
-__device__ __forceinline__ double finite_arg(double v) { return __builtin_fmin(v, 0x1.fffffffffffffp+1023); }
-template <> __device__ __forceinline__ double inv_sqrt<double>(double v) {
-    const double y = inv_sqrt_est(v);
-    const double e = __builtin_fma(-(y * finite_arg(v)), y, 1.0);
+__device__ __forceinline__ double inv_sqrt_step(double y, double v) {
+    const double e = __builtin_fma(-(y * v), y, 1.0);
     return __builtin_fma(y * e, __builtin_fma(e, 0.375, 0.5), y);
 }
+template <> __device__ __forceinline__ double inv_sqrt<double>(double v) {
+    return inv_sqrt_step(inv_sqrt_est(v), __builtin_fmin(v, 0x1.fffffffffffffp+1023));
+}
+__device__ __forceinline__ float inv_sqrt_finite(float v) { return inv_sqrt<float>(v); }
+__device__ __forceinline__ double inv_sqrt_finite(double v) { return inv_sqrt_step(inv_sqrt_est(v), v); }
+// Systems whose pair distances may have an infinite square in FP64 (dom[5]: the
+// cell edge, or the extent of the atoms)
+constexpr double kWideExtent = 1e153;
 
 
 // Per target leaf (kNW wavefronts, one lane per target): the sources of the 27
@@ -2563,6 +2572,7 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     const bool tpre = tid < tn;
     const int32_t pre_i = tpre ? perm[tb + tid] : 0;
     const double edge = dom[3];
+    const bool wide = sizeof(T) == 8 && !(dom[5] < kWideExtent);
     const double h = edge / g.nb;
     int cx, cy, cz;
     unmorton((uint32_t)leaf, cx, cy, cz);
@@ -2794,8 +2804,8 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
                     const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
                     const T r2 = fma_(dz, dz, fma_(dx, dx, dy * dy));
                     T ri;
-                    if constexpr (decltype(guard)::value) ri = r2 > T(0) ? inv_sqrt<T>(r2) : T(0);
-                    else ri = inv_sqrt<T>(r2);
+                    if constexpr (decltype(guard)::value) ri = r2 > T(0) ? inv_sqrt_finite(r2) : T(0);
+                    else ri = inv_sqrt_finite(r2);
                     const T qr3 = (s.w * ri) * (ri * ri);
                     ph = fma_(s.w, ri, ph);
                     fx = fma_(qr3, dx, fx);
@@ -2861,7 +2871,7 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
                         __builtin_amdgcn_sched_barrier(0);
                         T e[4], g3[4];
 #pragma unroll
-                        for (int k = 0; k < 4; ++k) e[k] = -(ri[k] * finite_arg(r2[k]));
+                        for (int k = 0; k < 4; ++k) e[k] = -(ri[k] * r2[k]);
                         __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                         for (int k = 0; k < 4; ++k) e[k] = fma_(e[k], ri[k], T(1));
@@ -2902,9 +2912,24 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
                 }
             };
             if (kBig && !busy) continue;  // (uniform per wavefront; the barriers are above)
-            sweep(jb, min(je, own_b), std::false_type{});
-            sweep(max(jb, own_b), min(je, own_e), std::true_type{});
-            sweep(max(jb, own_e), je, std::false_type{});
+            if (wide) {
+                // the same sums with a check of every pair
+                for (int j = jb + grp; j < je; j += ngrp) {
+                    const vec4_t<T> s = tile[j];
+                    const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
+                    const T r2 = fma_(dz, dz, fma_(dx, dx, dy * dy));
+                    const T ri = r2 > T(0) || j < own_b || j >= own_e ? inv_sqrt<T>(r2) : T(0);
+                    const T qr3 = (s.w * ri) * (ri * ri);
+                    ph = fma_(s.w, ri, ph);
+                    fx = fma_(qr3, dx, fx);
+                    fy = fma_(qr3, dy, fy);
+                    fz = fma_(qr3, dz, fz);
+                }
+            } else {
+                sweep(jb, min(je, own_b), std::false_type{});
+                sweep(max(jb, own_b), min(je, own_e), std::true_type{});
+                sweep(max(jb, own_e), je, std::false_type{});
+            }
             if (g.check && tv) {
                 // check mode: a zero distance to any source of the own leaf
                 // other than the target itself is a coincident pair
