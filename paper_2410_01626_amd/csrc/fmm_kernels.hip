@@ -3883,7 +3883,16 @@ __global__ __launch_bounds__(256) void k_reduce(Geo g, int R, int64_t nparts,
             double e = 0.5 * g.coulomb_k * red[0];
             if (hc_e) {  // Hamiltonian interpolation: the replica's site corrections, in order
                 const RepDesc rd = reps[b];
-                for (int64_t q = 0; q < rd.S; ++q) e += hc_e[rd.s0 + q];
+                const double* h = hc_e + rd.s0;
+                int q = 0;
+                for (; q + 8 <= (int)rd.S; q += 8) {  // (eight loads in flight)
+                    double v8[8];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) v8[j] = h[q + j];
+#pragma unroll
+                    for (int j = 0; j < 8; ++j) e += v8[j];
+                }
+                for (; q < (int)rd.S; ++q) e += h[q];
             }
             if (E) E[b] = e;
         } else {
