@@ -1003,14 +1003,15 @@ fmm_status enqueue_adjoint_full(fmm_plan_t P, const fmmk::RepDesc& r0, const T* 
     mark(P, 0);
     enqueue_bin_p2m<T>(P, g, rd, 1, x, qA, qB, site, lam, fa, n, S, false, nullptr);
     using V4 = vec4_t<T>;
+    int32_t* weighed = (int32_t*)P->ws.leaf_energy;  // per leaf (this call has no energy partials there)
     k_leaf_src2<T><<<g.nleaf, kLeafThreads, src2_lds_bytes<T>(g.K), st>>>(
         g, (const V4*)P->ws.pos, P->ws.perm, P->ws.leaf_start, gphi, gF, P->ws.dom, (V4*)P->ws.adj_src2, (T*)P->ws.mult,
-        P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp);
+        P->ws.leaf_part, (uint16_t*)P->ws.msplit, P->split_kp, weighed);
     enqueue_tree<T>(P, g, 2, false, false);
     mark(P, 6);
     k_near_adj<T, kAdjWaves><<<g.nleaf, 64 * kAdjWaves, 0, st>>>(g, (const V4*)P->ws.pos, (const V4*)P->ws.adj_src2,
                                                    P->ws.leaf_start, P->ws.perm, P->ws.dom, (const T*)P->ws.loc,
-                                                   P->gidx, (const T*)P->gcoef, (T*)P->ws.adj_acc);
+                                                   P->gidx, (const T*)P->gcoef, (T*)P->ws.adj_acc, weighed);
     const unsigned nb = nblocks(n, 256);
     k_adj_combine<T><<<nb, 256, 0, st>>>(g, n, S, x, qA, qB, site, lam, gphi, gF, gE_dev, gE, P->ws.dom,
                                          P->excl_n > 0 ? P->excl_start : nullptr, P->excl_idx,
