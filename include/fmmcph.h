@@ -94,10 +94,15 @@ typedef enum { FMM_FP64 = 0, FMM_MIXED_F32 = 1, FMM_MIXED_BF16X3 = 2 } fmm_preci
  *   m2l_chunk   offsets per matrix-core M2L work-group (0 = automatic, else 1..189)
  *   p2p_waves   wavefronts per near-field block: 4, 8 or 16 (0 = automatic: 4
  *               when max_atoms / (max_replicas 8^d) <= 32, else 8)
- *   p2p_split   near-field blocks per leaf, 1 to 4 (0 = automatic: 1, or in FP64
- *               trees of few leaves one per 32 atoms): with more than one, block s
+ *   p2p_split   near-field blocks per leaf, 1 to 4: with more than one, block s
  *               of a leaf takes its targets 32 s .. 32 s + 31 (the last block all
- *               the rest), so the hardware can balance uneven leaves
+ *               the rest), so the hardware can balance uneven leaves.  0 =
+ *               automatic: 1, except with 8 wavefronts per block and at most 128
+ *               leaves (max_replicas 8^d), by the mean population max_atoms /
+ *               (max_replicas 8^d): above 512 atoms four blocks share the rounds
+ *               of 512 targets of a leaf, above 256 two (forces and potentials
+ *               bit for bit those of one block); in FP64 above 24 and up to 256,
+ *               1.25 blocks per 32 atoms, rounded up, at most 4
  *   graph       1 = record the launch sequence of an evaluation in a HIP graph on
  *               first use and replay the graph while every argument (pointers,
  *               sizes, boxes, replica offsets) is unchanged; needs a non-NULL

@@ -1158,10 +1158,11 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
     }
     // Few, full leaves (up to 128 over all replicas, more than 256 atoms each on
     // average): two blocks per round of 512 targets, at most four, so that the
-    // wavefronts of a leaf do not pile up on one CU.  From the plan's maxima
+    // wavefronts of a leaf do not pile up on one CU (not with an explicit
+    // p2p_split, whose blocks per leaf are what it says).  From the plan's maxima
     // alone, so every call of a plan sums in one order.  (With 384 leaves of 86
     // atoms the half-empty blocks cost more than they spread: 130 -> 202 us.)
-    if (P->p2p_waves == 8 && P->p2p_split == 1) {
+    if (prm->p2p_split == 0 && P->p2p_waves == 8 && P->p2p_split == 1) {
         const double leaves = (double)std::max(prm->max_replicas, 1) * std::ldexp(1.0, 3 * prm->depth);
         const double per_leaf = (double)prm->max_atoms / leaves;
         if (leaves <= 128 && per_leaf > 256.0) P->p2p_blocks = per_leaf <= 512.0 ? 2 : 4;
@@ -2058,7 +2059,7 @@ fmm_status fmm_plan_info(fmm_plan_t P, int64_t out[10]) {
     out[5] = (int64_t)P->m2l_lds;
     out[6] = (int64_t)P->ws_bytes;
     out[7] = P->prm.graph;
-    out[8] = P->p2p_split;
+    out[8] = (int64_t)P->p2p_split * P->p2p_blocks;
     out[9] = 0;
     return FMM_OK;
 }
