@@ -117,7 +117,6 @@ struct fmm_plan_s {
     int64_t n_tasks = 0;
     fmmk::M2LTask* tasks = nullptr;
     int16_t* olist = nullptr;
-    int16_t* cstart = nullptr;
     void *bank_mma = nullptr;
     // FP32 / FP64 M2L (m2l_mma.hip): work items of one offset chunk (FP64, when
     // the scratch array has no room for partials), the offset lists with their
@@ -750,11 +749,6 @@ void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
                                                  P->ws.site_rank, P->status, bins);
     if (binned) {
         // nothing between the key and leaf launches
-    } else if (g.nleaf <= kScanFuseCap && S_tot <= kScanFuseCap) {
-        k_scan_scatter<<<dim3(ab, R), 256, 0, st>>>(g, reps, P->ws.key, P->ws.rank, P->ws.leaf_count,
-                                                    P->ws.leaf_start, P->ws.perm, site, P->ws.site_rank,
-                                                    P->ws.site_count, P->ws.site_start, (int)S_tot,
-                                                    P->ws.site_members);
     } else {
         k_scan2<<<R + 1, 1024, 0, st>>>(reps, R, P->ws.leaf_count, P->ws.leaf_start, g.nleaf,
                                         P->ws.site_count, P->ws.site_start, S_tot);
@@ -846,12 +840,11 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
     int32_t* order = nullptr;
     if (g.depth >= 1 && g.depth - 1 >= l0) {
         if (want_order && leaves_ordered(g)) order = P->ws.leaf_order;
-        // up to 64 boxes above the leaves: two blocks per box (four leaves
-        // each), so that the latency-bound chain runs on twice the CUs (one
-        // block of 512 threads fits a CU; four blocks per box would leave the
-        // order block without one)
+        // k_downward, up to 64 boxes above the leaves: two blocks per box (four
+        // leaves each), so that the latency-bound chain runs on twice the CUs
+        // (one block of 512 threads fits a CU; four blocks per box would leave
+        // the order block without one)
         const unsigned nbox1 = 1u << (3 * (g.depth - 1));
-        const bool half = nbox1 <= 64;
         if (!fused && (root_ready || !g.periodic) && many_boxes(g, R)) {
             // deep trees: the levels from l0 + 1 to d - 2 one launch each (every
             // box once), the leaves' launch from there (its blocks would
@@ -867,10 +860,11 @@ int32_t* enqueue_tree(fmm_plan_t P, const fmmk::Geo& g, int R, bool want_order, 
                 g, l_start, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, P->ws.root_l, (const T*)P->l2l_cls, P->cls, P->ws.leaf_start, order);
             return order;
         }
-        const unsigned nbx = nbox1 * (half ? 2u : 1u) + (order ? 1u : 0u);
+        // (depth <= kDownDepth here: deeper trees have many boxes, no fused sums
+        // and a root formed above)
+        const unsigned nbx = 2 * nbox1 + (order ? 1u : 0u);
         const bool root = g.periodic && !root_ready;
-        auto down = root ? (half ? k_downward<T, 4, true> : k_downward<T, 8, true>)
-                         : (half ? k_downward<T, 4, false> : k_downward<T, 8, false>);
+        auto down = root ? k_downward<T, true> : k_downward<T, false>;
         down<<<dim3(nbx, R), kTreeThreads, 0, st>>>(
             g, l0, loc, (const T*)P->l2lT, (const T*)P->l2l_seg, mult, (const T*)P->m2mT,
             (const T*)P->m2m_seg, P->ws.leaf_part, P->ws.box_part, P->latT, P->lat_seg, P->ws.root_m, P->ws.root_l,
@@ -1505,12 +1499,11 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         const std::vector<int16_t>& ol = cls_off;
         bool ok2 = !ol.empty();
         ok2 &= dev_alloc(P, (void**)&P->tasks, tl.size() * sizeof(fmmk::M2LTask));
-        ok2 &= dev_alloc(P, (void**)&P->olist, ol.size() * sizeof(int16_t));
-        ok2 &= dev_alloc(P, (void**)&P->cstart, cstart.size() * sizeof(int16_t));
         const size_t nb = (size_t)189 * mg.RP * mg.KP;
         const size_t nb1 = (size_t)189 * P->mma.npart * P->mma.a_chunks * 16;
         ok2 &= dev_alloc(P, &P->bank_mma, P->m2l_mode == 3 ? nb * 4 * (P->m2l_rs ? 1 : 8) : nb1);
         if (P->m2l_mode == 3) {
+            ok2 &= dev_alloc(P, (void**)&P->olist, ol.size() * sizeof(int16_t));
             ok2 &= dev_alloc(P, &P->sign_tab, 8 * 4 * fmmk::kM2LMaxKs * 16);
             ok2 &= dev_alloc(P, &P->zrow, kZrowBytes);
         } else {
@@ -1525,8 +1518,7 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         }
         up(P->tasks, tl.data(), tl.size() * sizeof(fmmk::M2LTask));
         if (e == hipSuccess) e = hipMemset(P->zrow, 0, kZrowBytes);
-        up(P->olist, ol.data(), ol.size() * sizeof(int16_t));
-        up(P->cstart, cstart.data(), cstart.size() * sizeof(int16_t));
+        if (P->m2l_mode == 3) up(P->olist, ol.data(), ol.size() * sizeof(int16_t));
         if (P->m2l_mode != 3) {
             // operator slots: class 0's offsets in ascending order; a class's
             // offset o runs on the slot of its mirror image P o

@@ -12,7 +12,7 @@ constexpr int kKgMax = kPMax * kPMax;       // gradient coefficients (order p-1)
 constexpr int kSortCap = 4096;              // largest leaf sorted in LDS
 constexpr int kSiteCap = 1024;              // largest site sorted in LDS
 constexpr int kMaxSplit = 4;                // near-field blocks per leaf, at most
-constexpr int kScanFuseCap = 4096;          // leaf / site counts scanned inside the scatter kernel
+constexpr int kScanFuseCap = 4096;          // leaf / site counts up to which leaves are binned in buckets
 constexpr double kPi = 3.14159265358979323846;
 constexpr int kLeafBucketMin = 256;         // leaf bucket capacity, at least (one leaf block's threads)
 

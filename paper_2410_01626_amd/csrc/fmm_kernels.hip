@@ -706,35 +706,6 @@ __device__ void block_scan_256(const int32_t* __restrict__ cnt, int n, int32_t b
     __syncthreads();
 }
 
-// Counting-sort placement with the scans fused in (nleaf and the site count
-// at most kScanFuseCap): every block scans its replica's leaf counts and all
-// site counts in LDS, block 0 of each replica publishes leaf_start (and block
-// (0, 0) site_start), then atoms are placed at start + rank.
-__global__ __launch_bounds__(256) void k_scan_scatter(
-    Geo g, const RepDesc* __restrict__ reps, const int32_t* __restrict__ key,
-    const int32_t* __restrict__ rank, const int32_t* __restrict__ leaf_count_all,
-    int32_t* __restrict__ leaf_start_all, int32_t* __restrict__ perm, const int32_t* __restrict__ site,
-    const int32_t* __restrict__ site_rank, const int32_t* __restrict__ site_count,
-    int32_t* __restrict__ site_start, int S_tot, int32_t* __restrict__ site_members) {
-    __shared__ int32_t ls[kScanFuseCap + 1], ss[kScanFuseCap + 1], tmp[256];
-    const int r = blockIdx.y;
-    const RepDesc rd = reps[r];
-    block_scan_256(leaf_count_all + (size_t)r * g.nleaf, (int)g.nleaf, (int32_t)rd.a0, ls, tmp);
-    if (S_tot > 0) block_scan_256(site_count, S_tot, 0, ss, tmp);
-    if (blockIdx.x == 0) {
-        int32_t* leaf_start = leaf_start_all + (size_t)r * (g.nleaf + 1);
-        for (int i = threadIdx.x; i <= g.nleaf; i += 256) leaf_start[i] = ls[i];
-        if (r == 0)
-            for (int i = threadIdx.x; i <= S_tot; i += 256) site_start[i] = S_tot > 0 ? ss[i] : 0;
-    }
-    const int64_t il = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (il >= rd.n) return;
-    const int64_t i = rd.a0 + il;
-    perm[ls[key[i]] + rank[i]] = (int32_t)i;
-    const int32_t s = site[i];
-    if (s >= 0 && s < rd.S) site_members[ss[rd.s0 + s] + site_rank[i]] = (int32_t)i;
-}
-
 // Bitonic sort of up to kSortCap ints in LDS (ascending), block-wide.
 template <int CAP>
 __device__ void lds_sort(int32_t* v, int n) {
@@ -1907,10 +1878,11 @@ __global__ __launch_bounds__(kTreeThreads, 4) void k_l2l_leaves(
     }
 }
 
-// Downward pass in one launch: 8 / NC blocks per box b of level depth - 1,
+// Downward pass of trees of depth <= 3 in one launch (deeper ones: k_l2l_leaves):
+// two blocks per box b of level depth - 1,
 // each of which forms lambda~ of b and its ancestors from level l0 down (L2L
 // of the parent's total plus the box's own M2L sum, in FP64) and adds the L2L
-// of lambda~_b into NC of its 8 leaves (fewer leaves per block: more blocks
+// of lambda~_b into four of its 8 leaves (fewer leaves per block: more blocks
 // share the latency-bound work, each box's chain is formed by each of its
 // blocks).  Periodic systems (l0 = 0) start from the root: every block forms
 // mu~_0 by M2M from the 8 level-1 multipoles and lambda~_0 = Lat mu~_0 +
@@ -1919,9 +1891,9 @@ __global__ __launch_bounds__(kTreeThreads, 4) void k_l2l_leaves(
 // only the leaf expansions are stored.  Open systems start at level l0 from
 // its M2L sum alone.  Only kRoot's blocks form the periodic root; otherwise it
 // was formed by an earlier launch and is read from root_l (an instantiation
-// of its own: the root's operators take half the registers).  500,000 atoms at
-// depth 5, p = 10: 154 -> 132 us with the leaves' products by sign classes.
-template <typename T, int NC, bool kRoot>
+// of its own: the root's operators take half the registers).
+constexpr int kDownDepth = 3;  // deepest tree it serves
+template <typename T, bool kRoot>
 __global__ __launch_bounds__(kTreeThreads) void k_downward(
     Geo g, int l0, T* __restrict__ loc_all, const T* __restrict__ l2l0, const T* __restrict__ l2l0_seg,
     const T* __restrict__ mult_all, const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
@@ -1941,10 +1913,12 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
         return;
     }
     __shared__ double v[kKMax], ps[16];
-    __shared__ T anc[kDMax * kKMax];
+    // M2L sums of at most kDownDepth - 1 ancestors (levels 1 or 2 to depth - 1)
+    constexpr int kAnc = (kDownDepth - 1) * kKMax;
+    __shared__ T anc[kAnc];
     TriPart<T, kTriUpper> tp;
     tp.load(g.K, l2l0_seg);
-    static_assert(8 % NC == 0, "whole leaf groups per block");
+    constexpr int NC = 4;  // leaves of a block
     const int rp = blockIdx.y, K = g.K, D = g.depth;
     T* loc = loc_all + (size_t)rp * g.nbox * g.Kp;
     // box b of level D - 1, its leaves c0 .. c0 + NC - 1
@@ -1952,7 +1926,7 @@ __global__ __launch_bounds__(kTreeThreads) void k_downward(
     // prefetch, all loads in flight together: the M2L sums of the ancestors at
     // levels la .. D - 1 and the NC leaves' own expansions
     const int la = g.periodic ? l0 + 1 : l0;
-    constexpr int kAncPer = (kDMax * kKMax + kTreeThreads - 1) / kTreeThreads;
+    constexpr int kAncPer = (kAnc + kTreeThreads - 1) / kTreeThreads;
     const int nanc = (D - la) * K;
     T av[kAncPer], lv[kGatherPer];
 #pragma unroll
@@ -2463,8 +2437,6 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2l_reduce(
     }
 }
 
-// ------------------------------------------------------------------ downward pass
-
 // ------------------------------------------------------------------ near + far field
 
 template <typename T> __device__ __forceinline__ T inv_sqrt(T v);
@@ -2489,7 +2461,6 @@ __device__ __forceinline__ double inv_sqrt_finite(double v) { return inv_sqrt_st
 // Systems whose pair distances may have an infinite square in FP64 (dom[5]: the
 // cell edge, or the extent of the atoms)
 constexpr double kWideExtent = 1e153;
-
 
 // Per target leaf (kNW wavefronts, one lane per target): the sources of the 27
 // neighbour leaves (periodic images through integer leaf offsets) are staged
