@@ -1493,8 +1493,10 @@ fmm_status fmm_plan_create(const fmm_params* prm, void* hip_stream, fmm_plan_t* 
         const int KC = mg.KP / 8;
         if (P->m2l_mode != 3) {
             P->m2l_lds = (size_t)2 * 16 * P->mma.a_chunks;  // two operator buffers: static LDS
+        } else if (P->m2l_rs) {
+            P->m2l_lds = 16 * (size_t)(2 * fmmk::m2l_rs_op_chunks(P->m2l_rt) + fmmk::m2l_rs_src_chunks(P->m2l_rt));
         } else {
-            P->m2l_lds = 0;  // static
+            P->m2l_lds = (size_t)16 * 2 * 2 * KC * mg.RP;  // two operator buffers
         }
         const std::vector<int16_t>& ol = cls_off;
         bool ok2 = !ol.empty();
@@ -2047,6 +2049,12 @@ fmm_status fmm_plan_info(fmm_plan_t P, int64_t out[10]) {
     out[1] = P->m2l_mode ? P->mg.csize : 0;
     out[2] = P->m2l_mode ? P->mg.nchunk : 0;
     out[3] = P->n_tasks;
+    if (P->m2l_mode == 1 || P->m2l_mode == 2) {
+        // (each task of k_m2l_mma runs in every column tile)
+        const int64_t groups = ((int64_t)P->mg.ncol * (P->fp64 ? 8 : 1) + 15) / 16;
+        const MmaLaunch ml = mma_launch(P->mma, P->fp64, P->mg.KP, P->mg.ncol, P->n_tasks, 1, P->mg.nchunk, 0.0, nullptr);
+        out[3] *= (groups + ml.groups - 1) / ml.groups;
+    }
     out[4] = P->p2p_waves;
     out[5] = (int64_t)P->m2l_lds;
     out[6] = (int64_t)P->ws_bytes;
