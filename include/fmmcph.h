@@ -87,10 +87,12 @@ typedef enum { FMM_FP64 = 0, FMM_MIXED_F32 = 1, FMM_MIXED_BF16X3 = 2 } fmm_preci
  *   max_sites   largest S (same)
  *   max_replicas largest replica count of fmm_eval_batched (>= 1)
  *   check       1 = run the device-side input checks described above
- *   m2l_kernel  0 = automatic, 1 = plain (vector ALU) M2L, 2 = matrix-core M2L
- *               (available for p <= 10; FP64 needs p <= 8), 3 = matrix-core M2L
- *               that copies every column's source per offset even where the
- *               bf16x3 kernel could keep a class's sources resident (depth <= 3)
+ *   m2l_kernel  0 = automatic (matrix cores: FP64 at every order, the mixed
+ *               precisions up to p = 10, plain above), 1 = plain (vector ALU)
+ *               M2L, 2 = matrix-core M2L (accepted for p <= 10; FP64 for p <= 8),
+ *               3 = as 2, with every column's source read per offset even where
+ *               the bf16x3 kernel could keep a class's sources resident (depth
+ *               <= 3)
  *   m2l_chunk   offsets per matrix-core M2L work-group (0 = automatic, else 1..189)
  *   p2p_waves   wavefronts per near-field block: 4, 8 or 16 (0 = automatic: 4
  *               when max_atoms / (max_replicas 8^d) <= 32, else 8)
@@ -140,7 +142,10 @@ typedef struct {
 /* Create a plan on the current HIP device.  hip_stream is a hipStream_t (NULL =
  * the default stream).  Builds the FP64 translation operators for order_p (and
  * the periodic lattice operator) on the host, uploads them, and allocates the
- * workspace.  *out receives the plan on FMM_OK. */
+ * workspace.  *out receives the plan on FMM_OK.  Device memory: fmm_plan_info's
+ * out[6]; the M2L operators of a bf16x3 plan take 99 MB at p = 10 and 56 MB at p =
+ * 8 and depth >= 4 (a copy for each of the eight child classes; 7 MB at p = 8 and
+ * depth <= 3, where one serves all). */
 fmm_status fmm_plan_create(const fmm_params* params, void* hip_stream, fmm_plan_t* out);
 
 /* One evaluation (one system).

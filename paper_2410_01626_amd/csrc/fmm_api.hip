@@ -215,8 +215,6 @@ bool dev_alloc(fmm_plan_t p, void** ptr, size_t bytes) {
     return true;
 }
 
-// Reflection parity bits of real coefficient k (bit 2: x -> -x, bit 1:
-// y -> -y, bit 0: z -> -z), as the kernels' refl_bits.
 // Lay out a plan's per-evaluation buffers for up to N atoms, S sites and RM
 // expansion slots (adjoint: with the adjoint's buffers) from base, each
 // buffer aligned to 256 bytes; returns the arena size.  base = NULL only
@@ -296,6 +294,8 @@ size_t ws_layout(const fmm_plan_s* P, int64_t N, int64_t S, size_t RM, bool adjo
     return off;
 }
 
+// Reflection parity bits of real coefficient k (bit 2: x -> -x, bit 1:
+// y -> -y, bit 0: z -> -z), as the kernels' refl_bits.
 int refl_bits_host(int k) {
     const int l = (int)std::floor(std::sqrt((double)k + 0.5));
     const int rem = k - l * l;

@@ -1,8 +1,10 @@
 // fmm_kernels.hip -- gfx950 kernels of the lambda-interpolated FMM Coulomb
 // solve.  One evaluation runs, in stream order:
-//   bbox (open only) -> charge_key -> scan -> scatter -> leaf_sort_gather ->
-//   p2m -> m2m (per level) -> root (periodic lattice, FP64) -> m2l (all levels)
-//   -> l2l (per level) -> near_far (P2P + L2P + output) -> reduce
+//   bbox (open only) -> charge_key -> (more than 4,096 leaves or sites: scan2 ->
+//   scatter) -> leaf_p2m (sort, gather, P2M, first M2M step of small trees) ->
+//   m2m (per level) -> m2l (all levels; the periodic root in an extra work-group
+//   or in m2l_reduce) -> downward (or l2l_level, l2l_leaves) -> near_far (P2P +
+//   L2P + output) -> reduce
 // Box indices are Morton codes at every level; level l occupies
 // [lev_off[l], lev_off[l] + 8^l) of the expansion arrays.  Particles are kept
 // sorted by leaf with coordinates relative to their leaf centre, so periodic
@@ -1569,12 +1571,7 @@ __device__ void leaf_work_order(const Geo& g, const int32_t* __restrict__ leaf_s
     }
 }
 
-// Periodic root of replica rp (a block of kTreeThreads threads): mu~_0 by
-// M2M from the 8 level-1 multipoles and lambda~_0 = Lat mu~_0 +
-// (2 pi / 3) sum q |s/L|^2 e_0, left in v (FP64); with `store` it also writes
-// mu~_0, lambda~_0 and dom[4] = Q.  xs: 8 kKMax doubles, part: 8 kTreeThreads
-// doubles, ps: 16 doubles of LDS.
-// As periodic_root, from the eight level-1 shares of the root multipole
+// As periodic_root (below), from the eight level-1 shares of the root multipole
 // (k_m2m at level 1) and the level-1 partial sums of q |s/L|^2 and q.
 __device__ void periodic_root_from_shares(const Geo& g, int rp, const double* __restrict__ root_part_all,
                                           const double* __restrict__ box_part_all,
@@ -1656,6 +1653,11 @@ __device__ void periodic_root_wg(const Geo& g, int rp, const double* __restrict_
     if (t == 0) dom_all[8 * rp + 4] = qs;
 }
 
+// Periodic root of replica rp (a block of kTreeThreads threads): mu~_0 by
+// M2M from the 8 level-1 multipoles and lambda~_0 = Lat mu~_0 +
+// (2 pi / 3) sum q |s/L|^2 e_0, left in v (FP64); with `store` it also writes
+// mu~_0, lambda~_0 and dom[4] = Q.  xs: 8 kKMax doubles, part: kTreeThreads
+// doubles, ps: 16 doubles of LDS.
 template <typename T>
 __device__ void periodic_root(const Geo& g, int rp, const T* __restrict__ mult_all,
                               const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
