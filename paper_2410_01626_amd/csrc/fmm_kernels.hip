@@ -2772,13 +2772,15 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
             const int own_b = nb_pre[13] - s0, own_e = nb_pre[14] - s0;
             auto sweep = [&](int j0, int j1, auto guard) {
                 const int first = j0 + ((grp - (j0 - jb)) & (ngrp - 1));
-                // (multiply-adds spelled out: every form of the loop rounds alike)
-                auto pair = [&](const vec4_t<T>& s) {
+                // (multiply-adds spelled out: every form of the loop rounds alike;
+                // wide systems take the forms that check each square)
+                auto pair = [&](const vec4_t<T>& s, auto finite) {
                     const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
                     const T r2 = fma_(dz, dz, fma_(dx, dx, dy * dy));
                     T ri;
-                    if constexpr (decltype(guard)::value) ri = r2 > T(0) ? inv_sqrt_finite(r2) : T(0);
-                    else ri = inv_sqrt_finite(r2);
+                    if constexpr (decltype(finite)::value) ri = inv_sqrt_finite(r2);
+                    else ri = inv_sqrt<T>(r2);
+                    if constexpr (decltype(guard)::value) ri = r2 > T(0) ? ri : T(0);
                     const T qr3 = (s.w * ri) * (ri * ri);
                     ph = fma_(s.w, ri, ph);
                     fx = fma_(qr3, dx, fx);
@@ -2792,7 +2794,7 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
                     // while they are summed (reads run at most 8 entries past
                     // the range, into the tile's padding; never used)
                     const int js = __builtin_amdgcn_readfirstlane(j), je_ = __builtin_amdgcn_readfirstlane(j1);
-                    if (__builtin_amdgcn_readfirstlane(ngrp) == 1 && js < je_) {
+                    if (__builtin_amdgcn_readfirstlane(ngrp) == 1 && js < je_ && !wide) {
                         vec4_t<T> s0[4], s1[4];
                         int i = js;
 #pragma unroll
@@ -2802,25 +2804,25 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
                             for (int k = 0; k < 4; ++k) s1[k] = tile[i + 4 + k];
                             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int k = 0; k < 4; ++k) pair(s0[k]);
+                            for (int k = 0; k < 4; ++k) pair(s0[k], std::true_type{});
                             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
                             for (int k = 0; k < 4; ++k) s0[k] = tile[i + 8 + k];
                             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
-                            for (int k = 0; k < 4; ++k) pair(s1[k]);
+                            for (int k = 0; k < 4; ++k) pair(s1[k], std::true_type{});
                             __builtin_amdgcn_sched_barrier(0);
                         }
-                        for (; i < je_; ++i) pair(tile[i]);
+                        for (; i < je_; ++i) pair(tile[i], std::true_type{});
                         return;
                     }
-                    for (; j < j1; j += ngrp) pair(tile[j]);
+                    for (; j < j1; j += ngrp) pair(tile[j], std::false_type{});
                 } else if constexpr (sizeof(T) == 8) {
                     // four sources side by side, stage by stage (the scheduling
                     // barriers keep the compiler from running them one after the
                     // other): the FP64 chain of a pair is long and only two
                     // wavefronts share a SIMD (30k box: 99 -> 89 us)
-                    for (; j + 3 * ngrp < j1; j += 4 * ngrp) {
+                    for (; !wide && j + 3 * ngrp < j1; j += 4 * ngrp) {
                         vec4_t<T> s4[4];
                         T dx[4], dy[4], dz[4], r2[4], ri[4];
 #pragma unroll
@@ -2878,31 +2880,16 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
                             fz = fma_(e[k], dz[k], fz);
                         }
                     }
-                    for (; j < j1; j += ngrp) pair(tile[j]);
+                    for (; j < j1; j += ngrp) pair(tile[j], std::false_type{});
                 } else {
 #pragma unroll 4
-                    for (; j < j1; j += ngrp) pair(tile[j]);
+                    for (; j < j1; j += ngrp) pair(tile[j], std::false_type{});
                 }
             };
             if (kBig && !busy) continue;  // (uniform per wavefront; the barriers are above)
-            if (wide) {
-                // the same sums with a check of every pair
-                for (int j = jb + grp; j < je; j += ngrp) {
-                    const vec4_t<T> s = tile[j];
-                    const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
-                    const T r2 = fma_(dz, dz, fma_(dx, dx, dy * dy));
-                    const T ri = r2 > T(0) || j < own_b || j >= own_e ? inv_sqrt<T>(r2) : T(0);
-                    const T qr3 = (s.w * ri) * (ri * ri);
-                    ph = fma_(s.w, ri, ph);
-                    fx = fma_(qr3, dx, fx);
-                    fy = fma_(qr3, dy, fy);
-                    fz = fma_(qr3, dz, fz);
-                }
-            } else {
-                sweep(jb, min(je, own_b), std::false_type{});
-                sweep(max(jb, own_b), min(je, own_e), std::true_type{});
-                sweep(max(jb, own_e), je, std::false_type{});
-            }
+            sweep(jb, min(je, own_b), std::false_type{});
+            sweep(max(jb, own_b), min(je, own_e), std::true_type{});
+            sweep(max(jb, own_e), je, std::false_type{});
             if (g.check && tv) {
                 // check mode: a zero distance to any source of the own leaf
                 // other than the target itself is a coincident pair
