@@ -4,6 +4,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <climits>
 #include <cmath>
 #include <cstdio>
 #include <cstring>
@@ -695,6 +696,16 @@ int crowd_blocks(int R) { return std::max(64, 1024 / R & ~7); }
 bool leaves_ordered(const fmmk::Geo& g) {
     return g.nleaf <= fmmk::kOrderCap && g.depth >= 1 && g.depth - 1 >= (g.periodic ? 0 : g.lmin);
 }
+// Whether the leaf kernels of such a tree may list crowded leaves (64 leaves: the
+// smallest tree that k_near_small takes).
+bool may_list(const fmmk::Geo& g) { return g.nleaf >= 64 && !leaves_ordered(g); }
+// Blocks of a k_near_far launch for crowded leaves, per replica: fewer than
+// nleaf / kCrowdTimes leaves have kCrowdTimes the mean population.  Not for deeper
+// trees, whose mean leaf is small.
+int crowd_blocks_far(fmm_plan_t P, const fmmk::Geo& g) {
+    return P->p2p_split == 1 && g.nleaf > fmmk::kOrderCap && g.nleaf <= fmmk::kScanFuseCap
+               ? g.nleaf / fmmk::kCrowdTimes : 0;
+}
 
 // Binning and leaf multipoles of R replicas (grid y = replica): replica
 // descriptors, the open bounding cube, leaf keys, the counting sort and the
@@ -704,7 +715,7 @@ bool leaves_ordered(const fmmk::Geo& g) {
 template <typename T>
 void enqueue_bin_p2m(fmm_plan_t P, const fmmk::Geo& g, RepSpan rd, int R,
                      const T* x, const T* qA, const T* qB, const int32_t* site, const double* lam,
-                     const fmmk::FormArgs<T>& fa, int64_t maxn, int64_t S_tot, bool fold, int32_t* crowded) {
+                     const fmmk::FormArgs<T>& fa, int64_t maxn, int64_t S_tot, bool fold, fmmk::Crowd crowded) {
     using namespace fmmk;
     hipStream_t st = P->stream;
     const int nstore = (int)rd.size();
@@ -902,10 +913,12 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
     // the tree is small enough for launch latency to matter (deeper trees
     // keep the separate launch, which then costs little next to the work)
     const bool fold = P->ws.m2m_part != nullptr && g.depth - 2 >= g.lmin && g.nleaf <= kScanFuseCap;
-    // wavefront-per-leaf near field: crowded leaves are found in the order of
-    // work or else listed by the leaf kernel (in the order's place)
+    // crowded leaves are found in the order of work or else listed by the leaf
+    // kernel (in the order's place)
     const bool small = near_small<T>(P, g, R, maxn);
-    int32_t* crowded = small && !leaves_ordered(g) ? P->ws.leaf_order : nullptr;
+    const int nc = small ? crowd_blocks(R) : crowd_blocks_far(P, g);
+    int32_t* list = nc > 0 && may_list(g) ? P->ws.leaf_order : nullptr;
+    const Crowd crowded{list, small ? kSmallSolo : (int)std::min<int64_t>(kCrowdTimes * maxn / g.nleaf, INT_MAX)};
     enqueue_bin_p2m<T>(P, g, rd, R, x, qA, qB, site, lam, fa, maxn, S_tot, fold, crowded);
     int32_t* order = enqueue_tree<T>(P, g, R, true, fold);
     const RepDesc* reps = P->ws.reps;
@@ -922,17 +935,15 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
         if (P->p2p_blocks == 1 && P->p2p_waves == 8 && (int64_t)g.nleaf * P->p2p_split * R > 256)
             near = k_near_far<T, 8, false, 4>;
     if constexpr (sizeof(T) == 4)
-        if (small) {
-            const int nc = crowd_blocks(R);
+        if (small)
             k_near_small<T><<<dim3(g.nleaf / kSmallWaves + nc, R), 64 * kSmallWaves, near_small_lds<T>(g.K), st>>>(
                 g, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx, (const T*)P->gcoef, qA, qB,
-                site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status, crowded, nc);
-        }
+                site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order, P->status, list, nc);
     if (!small)
-        near<<<dim3(g.nleaf * P->p2p_split * P->p2p_blocks, R), 64 * P->p2p_waves, 0, st>>>(
+        near<<<dim3(g.nleaf * P->p2p_split * P->p2p_blocks + nc, R), 64 * P->p2p_waves, 0, st>>>(
             g, P->p2p_split, P->p2p_blocks, reps, pos, P->ws.leaf_start, P->ws.perm, P->ws.dom, loc, P->gidx,
             (const T*)P->gcoef, qA, qB, site, phi, F, P->ws.leaf_energy, P->ws.cphi, fa.qC != nullptr, order,
-            P->status);
+            P->status, list, nc, crowded.over);
     if (P->excl_n > 0)
         k_excl<T><<<dim3(ab, R), 256, 0, st>>>(g, reps, x, qA, qB, site, lam, fa, P->ws.dom, P->excl_start,
                                                P->excl_idx, phi, F, P->ws.cphi, fa.qC != nullptr,
@@ -950,7 +961,7 @@ fmm_status enqueue_eval(fmm_plan_t P, RepSpan rd, const T* x,
                                                        ham && S_tot > 0 ? P->ws.hc_dl : nullptr,
                                                        P->ws.leaf_count, P->ws.site_count,
                                                        P->excl_n > 0 ? P->excl_e : nullptr, (int)ab,
-                                                       nullptr, nullptr, P->ws.ovf_n, crowded);
+                                                       nullptr, nullptr, P->ws.ovf_n, list);
     mark(P, -1);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return fail(P, FMM_E_HIP, std::string("kernel launch: ") + hipGetErrorString(e));
@@ -995,7 +1006,7 @@ fmm_status enqueue_adjoint_full(fmm_plan_t P, const fmmk::RepDesc& r0, const T* 
     const RepSpan rd(rd2, 2);
     const FormArgs<T> fa{nullptr, nullptr, nullptr};
     mark(P, 0);
-    enqueue_bin_p2m<T>(P, g, rd, 1, x, qA, qB, site, lam, fa, n, S, false, nullptr);
+    enqueue_bin_p2m<T>(P, g, rd, 1, x, qA, qB, site, lam, fa, n, S, false, {nullptr, 0});
     using V4 = vec4_t<T>;
     int32_t* weighed = (int32_t*)P->ws.leaf_energy;  // per leaf (this call has no energy partials there)
     k_leaf_src2<T><<<g.nleaf, kLeafThreads, src2_lds_bytes<T>(g.K), st>>>(
@@ -1782,7 +1793,7 @@ fmm_status fmm_eval_noalloc(fmm_plan_t P, int64_t n, const void* x, const void* 
     fmmk::k_fill_f64<<<1, 64, 0, st>>>(sw.dom, 8, 0.0);
     if (sw.ovf_n) fmmk::k_fill_i32<<<1, 64, 0, st>>>(sw.ovf_n, 1, 0);
     const Geo g = make_geo(P);
-    if (!P->fp64 && near_small<float>(P, g, 1, n) && !leaves_ordered(g))
+    if (may_list(g) && ((!P->fp64 && near_small<float>(P, g, 1, n)) || crowd_blocks_far(P, g) > 0))
         fmmk::k_fill_i32<<<1, 64, 0, st>>>(sw.leaf_order + g.nleaf - 3, 3, 0);  // the list of crowded leaves
     if (sw.msplit) {
         const int64_t words = (int64_t)(msplit_bytes(P, 1) / 4);

@@ -871,16 +871,22 @@ __device__ __forceinline__ double form_charge(const T* __restrict__ qA, const T*
     return q;
 }
 
-// Crowded leaves of each replica (more than kSmallSolo atoms) for k_near_small
-// without an order of work, filed by the leaf kernels in nleaf entries: the
+// Crowded leaves of each replica for a near field without an order of work (for
+// k_near_small those of more than kSmallSolo atoms, for k_near_far those of more
+// than kCrowdTimes the mean), filed by the leaf kernels in nleaf entries: the
 // fullest (more than a round of targets) from entry 0 up, the others from entry
 // nleaf - 4 down; the last three entries hold how many of each there are and the
 // next one to take.  A call that runs k_near_small has at most kSmallFill atoms a
 // leaf on average, so fewer than 3/4 of the entries are used.  k_reduce clears
-// the three.  list == null: not wanted.
+// the three.
+struct Crowd {
+    int32_t* list;  // null: not wanted
+    int over;       // leaves of more atoms than this are crowded
+};
 constexpr int kSmallSolo = 64;  // atoms of a leaf that one wavefront of k_near_small takes alone
 constexpr int kSmallFill = 48;  // mean population up to which trees of many leaves run the small forms
 constexpr int kSmallRound = 256;  // targets of a round of k_near_small's blocks
+constexpr int kCrowdTimes = 32;
 struct CrowdList {
     int32_t *entry, *fullest, *others, *ticket;
     int last;  // entry of the first of the others
@@ -894,9 +900,9 @@ struct CrowdList {
     __device__ void clear() const { *fullest = *others = *ticket = 0; }
 };
 static_assert(4 * kSmallFill < 3 * (kSmallSolo + 1), "the list holds every crowded leaf");
-__device__ __forceinline__ void file_crowded(int32_t* list, int64_t nleaf, int rep, int leaf, int n) {
-    if (!list || n <= kSmallSolo) return;
-    const CrowdList c(list, nleaf, rep);
+__device__ __forceinline__ void file_crowded(const Crowd& crowd, int64_t nleaf, int rep, int leaf, int n) {
+    if (!crowd.list || n <= crowd.over) return;
+    const CrowdList c(crowd.list, nleaf, rep);
     const int at = n > kSmallRound ? atomicAdd(c.fullest, 1) : c.last - atomicAdd(c.others, 1);
     if (at >= 0 && at <= c.last) c.entry[at] = leaf;
 }
@@ -927,7 +933,7 @@ __device__ __forceinline__ void leaf_block(
     int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
     T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
     int split_kp, Bins bins, LeafBinArgs lb, const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
-    double* __restrict__ m2m_part_all, int32_t* __restrict__ crowded) {
+    double* __restrict__ m2m_part_all, Crowd crowded) {
     static_assert(2 * kLeafThreads == kTreeThreads, "two tree-operator shares per leaf thread");
     extern __shared__ __align__(16) unsigned char leaf_lds[];
     __shared__ double ps[2][kLeafThreads / 64];
@@ -1187,7 +1193,7 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m(
     int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
     T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
     int split_kp, Bins bins, LeafBinArgs lb, const T* __restrict__ m2m0, const T* __restrict__ m2m0_seg,
-    double* __restrict__ m2m_part_all, int32_t* __restrict__ crowded) {
+    double* __restrict__ m2m_part_all, Crowd crowded) {
     __shared__ RhoLds<T> rho;
     leaf_block<T, FOLD>(blockIdx.x, rho, g, reps, x, qA, qB, site, lam, fa, dom_all, leaf_start_all, perm, pos, status,
                         mult_all, leaf_part_all, msplit_all, split_kp, bins, lb, m2m0, m2m0_seg, m2m_part_all, crowded);
@@ -1206,7 +1212,7 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m_small(
     FormArgs<T> fa, const double* __restrict__ dom_all, int32_t* __restrict__ leaf_start_all,
     int32_t* __restrict__ perm, vec4_t<T>* __restrict__ pos, int32_t* __restrict__ status,
     T* __restrict__ mult_all, double* __restrict__ leaf_part_all, uint16_t* __restrict__ msplit_all,
-    int split_kp, LeafBinArgs lb, int32_t* __restrict__ crowded) {
+    int split_kp, LeafBinArgs lb, Crowd crowded) {
     extern __shared__ __align__(16) unsigned char leaf_lds[];
     __shared__ RhoLds<T> rho;
     constexpr int kW = kLeafThreads / 64;
@@ -1221,8 +1227,8 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_p2m_small(
     const int leaf = __builtin_amdgcn_readfirstlane(blockIdx.x + wave * gridDim.x);
     const int b = __builtin_amdgcn_readfirstlane(leaf_start[leaf]);
     const int n = __builtin_amdgcn_readfirstlane(leaf_start[leaf + 1]) - b;
-    static_assert(kSmallSolo >= 64, "leaves of up to 64 atoms are not listed");
     const bool solo = n <= 64;
+    if (lane == 0 && solo) file_crowded(crowded, g.nleaf, blockIdx.y, leaf, n);
     const double edge = dom[3];
     const double h = edge / g.nb;
     const T ih = (T)(1.0 / h);
@@ -1529,7 +1535,8 @@ __global__ __launch_bounds__(kTreeThreads) void k_m2m(Geo g, int lev, T* __restr
 // go largest first.  Key: octant, count (capped at 2^16 - 1), leaf index
 // (ties: lower leaf first).  Trees of more than kOrderCap leaves go unordered: their
 // tail is short and sorting 4,096 leaves in one block held the near field up by
-// 75 us (near field of 15 to 49 atoms a leaf: 43, 201 us ordered, 45, 204 not).
+// 75 us (near field of 15 to 49 atoms a leaf: 43, 201 us ordered, 45, 204 not);
+// k_near_far's first blocks take their crowded leaves.
 // buf: kOrderCap ints of LDS.
 constexpr int kOrderCap = 512;
 __device__ void leaf_work_order(const Geo& g, const int32_t* __restrict__ leaf_start,
@@ -2482,6 +2489,12 @@ constexpr double kWideExtent = 1e153;
 // (the longest wavefront sums 64 targets over 24,000 sources: 68 issue cycles
 // per source, 680 us at 2.4 GHz).
 //
+// ncrowd: the launch's first blocks (of every replica) take the listed crowded
+// leaves of a tree of more than kOrderCap leaves, so that the fullest, a chain of
+// thousands of sources for each of many rounds of targets, start first (150,000
+// atoms with a Gaussian profile, depth 4, bf16x3: 8.0 to 10.1 ms a call as they fell
+// before, 7.9 ms now; uniform 385 to 392 us before and now).
+//
 // kOcc: wavefronts per SIMD the registers are capped for.  FP64 with more
 // blocks than CUs takes 4 (two blocks per CU at the price of some spills: 30k
 // box 89 -> 79 us), with fewer 1 (64 leaves: 26 us against 31).
@@ -2494,7 +2507,8 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     const T* __restrict__ qA, const T* __restrict__ qB, const int32_t* __restrict__ site,
     T* __restrict__ phi_out, T* __restrict__ F_out,
     double* __restrict__ leaf_energy_all, double* __restrict__ cphi, int unit_dq,
-    const int32_t* __restrict__ leaf_order_all, int32_t* __restrict__ status) {
+    const int32_t* __restrict__ leaf_order_all, int32_t* __restrict__ status, int32_t* __restrict__ crowded_all,
+    int ncrowd, int crowd_over) {
     constexpr int NT = 64 * kNW;
     // sources staged per pass: the whole 27-leaf neighbourhood of a typical leaf
     constexpr int CAP = sizeof(T) == 4 ? 2048 : 1024;
@@ -2502,7 +2516,15 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     const int32_t* leaf_start = leaf_start_all + (size_t)blockIdx.y * (g.nleaf + 1);
     const double* dom = dom_all + 8 * blockIdx.y;
     const T* loc = loc_all + (size_t)blockIdx.y * g.nbox * g.Kp;
-    double* leaf_energy = leaf_energy_all + (size_t)blockIdx.y * gridDim.x;
+    // this block's place past the blocks for crowded leaves (and its energy's)
+    int place = (int)blockIdx.x - ncrowd, crowd_leaf = -1;
+    double* leaf_energy = leaf_energy_all + (size_t)blockIdx.y * (gridDim.x - ncrowd);
+    if (!kBig && place < 0) {
+        const CrowdList listed(crowded_all, g.nleaf, blockIdx.y);
+        const int e = blockIdx.x, nfull = *listed.fullest;
+        if (e >= nfull + *listed.others) return;
+        place = crowd_leaf = listed.entry[e < nfull ? e : listed.last - (e - nfull)];
+    }
     __shared__ vec4_t<T> tile[CAP + (kBig ? 16 : 0)];
     __shared__ int nb_start[28], nb_cnt[28], nb_pre[29];
     __shared__ T nb_off[27][3];
@@ -2518,15 +2540,17 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     // block of the leaf all the rest); one block per leaf takes them all
     // leaves in the order given by leaf_work_order (largest first), if any
     // (kBig: slot-major over the nblk blocks of every leaf)
-    const int lslot = kBig ? blockIdx.x % g.nleaf : blockIdx.x / nsplit;
-    const int sub = kBig ? 0 : blockIdx.x - lslot * nsplit, unit0 = kBig ? blockIdx.x / g.nleaf : 0;
+    const int lslot = kBig ? place % g.nleaf : place / nsplit;
+    const int sub = kBig ? 0 : place - lslot * nsplit, unit0 = kBig ? place / g.nleaf : 0;
     const int leaf = leaf_order_all ? leaf_order_all[(size_t)blockIdx.y * g.nleaf + lslot] : lslot;
     const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
     const int lb = leaf_start[leaf], ln = leaf_start[leaf + 1] - lb;
+    // (crowded leaves: only one block per leaf, no order of work)
+    if (!kBig && ncrowd > 0 && crowd_leaf < 0 && ln > crowd_over) return;
     const int ta = 32 * sub;
     const int tb = lb + ta, tn = kBig || sub + 1 == nsplit ? ln - ta : min(32, ln - ta);
     if (tn <= 0 || (kBig && 64 * kNW * (unit0 >> 1) >= tn)) {
-        if (tid == 0) leaf_energy[blockIdx.x] = 0.0;
+        if (tid == 0) leaf_energy[place] = 0.0;
         return;
     }
     const bool far = g.has_far;
@@ -3008,7 +3032,7 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     }
     if (wave == 0) {
         esum = wave_sum<double>(esum);
-        if (lane == 0) leaf_energy[blockIdx.x] = esum;
+        if (lane == 0) leaf_energy[place] = esum;
     }
 }
 

@@ -100,3 +100,66 @@ def test_more_crowded_leaves_than_blocks(prec, periodic):
         else:
             for k in ("F", "phi", "dVdl", "E"):
                 np.testing.assert_array_equal(r[k], ref[k], err_msg="%s %s" % (key, k))
+
+
+@pytest.mark.parametrize("prec,split", [("f32", 0), ("fp64", 0), ("f32", 3)])
+def test_crowded_leaves_of_4096(prec, split):
+    """Depth 4, a block (or several) per leaf: leaves of more than 32 times the
+    mean population come first.  Every leaf is done once (outputs start as NaN),
+    the energy is the charges' potentials', and repeated calls give the same
+    bits."""
+    import torch
+    from paper_2410_01626_amd import fmm
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(10)
+    pop = np.full(4096, 5)
+    pop[rng.permutation(4096)[:60]] = [13, 24, 300, 200, 190, 600] * 10
+    pop[:8] = 0
+    leaf = np.repeat(np.arange(4096), pop)
+    o = np.stack([leaf >> 8, (leaf >> 4) & 15, leaf & 15], 1)
+    x = (o + np.floor(rng.uniform(0.05, 0.95, (len(leaf), 3)) * 4096) / 4096) * 0.5
+    n = len(x)
+    q, site = _charges(n, 11)
+    plan = fmm.Plan(4, 4, periodic=True, precision=prec, max_atoms=n, max_sites=3, p2p_waves=8, p2p_split=split,
+                    device=dev)
+    got = []
+    t = _tensors(plan, x, q, site, 1)
+    for _ in range(2):
+        out = plan.eval(*t, box=[8.0] * 3)
+        for v in out.values():
+            v.fill_(float("nan"))
+        plan.eval(*t, box=[8.0] * 3, out=out)
+        torch.cuda.synchronize()
+        r = {k: v.double().cpu().numpy() for k, v in out.items()}
+        assert all(np.isfinite(v).all() for v in r.values())
+        lam = np.linspace(0, 1, 3)[site] * (site >= 0)
+        e = 0.5 * ((1 - 0.5 * lam) * q * r["phi"])
+        assert abs(r["E"][0] - e.sum()) <= 4 * 2.0 ** (-24 if prec == "f32" else -52) * n ** 0.5 * np.abs(e).max()
+        got.append(r)
+    plan.close()
+    for k in ("F", "phi", "E", "dVdl"):
+        np.testing.assert_array_equal(got[0][k], got[1][k], err_msg=k)
+
+
+def test_lists_of_both_forms_in_one_plan():
+    """One plan, depth 4: a call with more atoms than the wavefront form takes
+    lists other leaves than the next, which runs that form."""
+    import torch
+    from paper_2410_01626_amd import fmm
+    dev = torch.device("cuda:0")
+    rng = np.random.default_rng(12)
+    many = rng.uniform(0, 8.0, (48 * 4096 + 1, 3))
+    many[:5000] = 0.5 + rng.uniform(0, 0.5, (5000, 3))
+    many = many.astype(np.float32).astype(np.float64)
+    few = np.concatenate([rng.uniform(0, 8.0, (9000, 3)), 3.01 + rng.uniform(0, 0.48, (700, 3)),
+                          rng.uniform(0, 0.5, (90, 3))]).astype(np.float32).astype(np.float64)
+    got = []
+    for first in (many, None):
+        plan = fmm.Plan(4, 4, periodic=True, precision="f32", max_atoms=len(many), max_sites=3, p2p_waves=4, device=dev)
+        for x in ([many, few] if first is not None else [few]):
+            r = plan.eval(*_tensors(plan, x, *_charges(len(x), 13), 1), box=[8.0] * 3)
+        torch.cuda.synchronize()
+        got.append({k: v.cpu().numpy() for k, v in r.items()})
+        plan.close()
+    for k in ("F", "phi", "E", "dVdl"):
+        np.testing.assert_array_equal(got[0][k], got[1][k], err_msg=k)
