@@ -877,8 +877,8 @@ __device__ __forceinline__ double form_charge(const T* __restrict__ qA, const T*
 // fullest (more than a round of targets) from entry 0 up, the others from entry
 // nleaf - 4 down; the last three entries hold how many of each there are and the
 // next one to take.  A call that runs k_near_small has at most kSmallFill atoms a
-// leaf on average, so fewer than 3/4 of the entries are used.  k_reduce clears
-// the three.
+// leaf on average, so fewer than 3/4 of the entries are used (k_near_far: fewer
+// than one in kCrowdTimes).  k_reduce clears the three.
 struct Crowd {
     int32_t* list;  // null: not wanted
     int over;       // leaves of more atoms than this are crowded
@@ -886,6 +886,9 @@ struct Crowd {
 constexpr int kSmallSolo = 64;  // atoms of a leaf that one wavefront of k_near_small takes alone
 constexpr int kSmallFill = 48;  // mean population up to which trees of many leaves run the small forms
 constexpr int kSmallRound = 256;  // targets of a round of k_near_small's blocks
+// Only the leaves that set the time of the launch by themselves: 8 and 32 times the
+// mean give the same time on a Gaussian profile (7.8 to 7.9 ms, see k_near_far), and
+// 32 needs a quarter of the extra blocks.
 constexpr int kCrowdTimes = 32;
 struct CrowdList {
     int32_t *entry, *fullest, *others, *ticket;
@@ -2517,6 +2520,7 @@ __global__ __launch_bounds__(64 * kNW, kOcc) void k_near_far(
     const double* dom = dom_all + 8 * blockIdx.y;
     const T* loc = loc_all + (size_t)blockIdx.y * g.nbox * g.Kp;
     // this block's place past the blocks for crowded leaves (and its energy's)
+    if (kBig) ncrowd = 0;  // (few leaves: they have an order)
     int place = (int)blockIdx.x - ncrowd, crowd_leaf = -1;
     double* leaf_energy = leaf_energy_all + (size_t)blockIdx.y * (gridDim.x - ncrowd);
     if (!kBig && place < 0) {
