@@ -218,8 +218,10 @@ __global__ __launch_bounds__(kLeafThreads) void k_leaf_src2(
 // neighbourhood has a weight (weights on a part of the atoms, or weights that are
 // zero), the pairs' second terms are exact zeros and left out: forward and
 // backward of a loss with weights of zero on the forces, 20,000 atoms at depth 2
-// 1,437 -> 1,019 us, 50,000 at depth 3 587 -> 486 us (with weights 30,000 atoms
-// take 102 us here instead of 100).
+// 1,437 -> 1,019 us, 50,000 at depth 3 587 -> 486 us (with weights everywhere, this
+// launch: 30,000 atoms at depth 3 99 us as before, 20,000 at depth 2 870 -> 884).
+// FP64 systems that may hold pairs at an infinite squared distance run a loop of
+// their own (kWideExtent; the look costs 3%).
 constexpr int kAdjWaves = 8;
 template <typename T, int kNW>
 __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
@@ -295,6 +297,7 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
     }
     __syncthreads();
     const bool weights = __builtin_amdgcn_readfirstlane(any_sh) != 0;
+    const bool wide = sizeof(T) == 8 && !(dom_all[5] < kWideExtent);
     if (far) {
         for (int e = tid; e < 3 * g.Kg; e += NT) {
             const int a = e / g.Kg, r = e - a * g.Kg;
@@ -374,10 +377,12 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
                             tilew[nb_pre[nbk] + j] = src2[nb_start[nbk] + j];
                         }
                 } else {
-                    // stage the pass's sources, CAP / NT of each kind in flight per thread
+                    // stage the pass's sources, CAP / NT in flight per thread; the second
+                    // rows follow entry by entry (all in flight: 903 us where 20,000
+                    // atoms at depth 2 take 884 so)
                     constexpr int G = CAP / NT;
-                    N4 a[G], aw[G];
-                    int lo_[G];
+                    vec4_t<T> a[G];
+                    int lo_[G], src_[G];
 #pragma unroll
                     for (int m = 0; m < G; ++m) {
                         const int gsrc = s0 + min(tid + m * NT, cnt - 1);
@@ -390,18 +395,18 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
                         }
                         lo_[m] = lo;
                         const int src = nb_start[lo] + (gsrc - nb_pre[lo]);
-                        a[m] = ((const N4*)pos)[src];
-                        aw[m] = ((const N4*)src2)[src];
+                        a[m] = pos[src];
+                        src_[m] = src;
                     }
 #pragma unroll
                     for (int m = 0; m < G; ++m) {
                         if (tid + m * NT < cnt) {
-                            N4 v = a[m];
+                            vec4_t<T> v = a[m];
                             v.x += nb_off[lo_[m]][0];
                             v.y += nb_off[lo_[m]][1];
                             v.z += nb_off[lo_[m]][2];
-                            ((N4*)tile)[tid + m * NT] = v;
-                            ((N4*)tilew)[tid + m * NT] = aw[m];
+                            tile[tid + m * NT] = v;
+                            tilew[tid + m * NT] = src2[src_[m]];
                         }
                     }
                 }
@@ -412,7 +417,7 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
                     // r = 0, which zeroes every term) runs on that range alone.
                     // Lane group grp takes the sources grp, grp + ngrp, ...
                     const int own_b = nb_pre[13] - s0, own_e = nb_pre[14] - s0;
-                    auto sweep = [&](int j0, int j1, auto guard) {
+                    auto sweep = [&](int j0, int j1, auto guard, auto finite) {
                         const int first = j0 + ((grp - j0) & (ngrp - 1));
 #pragma unroll 4
                         for (int j = first; j < j1; j += ngrp) {
@@ -422,8 +427,9 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
                             const T dx = me.x - s.x, dy = me.y - s.y, dz = me.z - s.z;
                             const T r2 = dx * dx + dy * dy + dz * dz;
                             T ri;
-                            if constexpr (decltype(guard)::value) ri = r2 > T(0) ? inv_sqrt<T>(r2) : T(0);
+                            if constexpr (decltype(finite)::value) ri = inv_sqrt_finite(r2);
                             else ri = inv_sqrt<T>(r2);
+                            if constexpr (decltype(guard)::value) ri = r2 > T(0) ? ri : T(0);
                             const T ri2 = ri * ri;
                             const T ri3 = ri * ri2;
                             const T qr = s.w * ri;
@@ -443,9 +449,13 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
                             }
                         }
                     };
-                    sweep(0, min(cnt, max(own_b, 0)), std::false_type{});
-                    sweep(max(own_b, 0), min(cnt, own_e), std::true_type{});
-                    sweep(max(own_e, 0), cnt, std::false_type{});
+                    auto sweeps = [&](auto finite) {
+                        sweep(0, min(cnt, max(own_b, 0)), std::false_type{}, finite);
+                        sweep(max(own_b, 0), min(cnt, own_e), std::true_type{}, finite);
+                        sweep(max(own_e, 0), cnt, std::false_type{}, finite);
+                    };
+                    if (wide) sweeps(std::false_type{});
+                    else sweeps(std::true_type{});
                 }
             }
             if (far && tv) {
@@ -481,7 +491,9 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
                 ey -= g0[1] * ih2;
                 ez -= g0[2] * ih2;
                 // A: potential of slot 1 plus w . (far field of the charges)
-                A += f1 * ih - (mw.x * g0[0] + mw.y * g0[1] + mw.z * g0[2]) * ih2;
+                // (products and sums paired off here and below: both forms, and any other
+                // build of the loop, round alike)
+                A += fma_(f1, ih, -(fma_(mw.z, g0[2], fma_(mw.x, g0[0], mw.y * g0[1])) * ih2));
                 // B: field of slot 1 minus the charges' field gradient along w
                 bx += (d0[0] - g1[0]) * ih2;
                 by += (d0[1] - g1[1]) * ih2;
@@ -515,10 +527,10 @@ __global__ __launch_bounds__(64 * kNW, sizeof(T) == 4 ? 4 : 1) void k_near_adj(
                                          (double)me.z + (cz + 0.5) * h - 0.5 * edge};
                     const double w[3] = {(double)mw.x, (double)mw.y, (double)mw.z};
                     const double t2 = t[0] * t[0] + t[1] * t[1] + t[2] * t[2];
-                    const double tw = t[0] * w[0] + t[1] * w[1] + t[2] * w[2];
+                    const double tw = __builtin_fma(t[2], w[2], __builtin_fma(t[1], w[1], t[0] * w[0]));
                     const double c2 = 2.0 * kPi / 3.0 / V, c4 = 4.0 * kPi / 3.0 / V;
                     v[0] += c2 * Q0 * t2;
-                    v[4] += c2 * G1 * t2 - c4 * Q0 * tw;
+                    v[4] += __builtin_fma(c2 * G1, t2, -(c4 * Q0 * tw));
 #pragma unroll
                     for (int a = 0; a < 3; ++a) {
                         v[1 + a] -= c4 * Q0 * t[a];
